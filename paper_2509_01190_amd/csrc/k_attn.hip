@@ -16,8 +16,8 @@
 // Causal blocks skip key tiles above the diagonal and are scheduled
 // heaviest-first.
 //
-// fp32 (and any other head_dim): one thread per query with the row in
-// registers, 32-key LDS tiles, the same online softmax.
+// fp32 (and bf16 at any other head_dim): the same transposed scores on the
+// fp32 matrix instruction, four waves sharing 32 queries' keys.
 #include <math.h>
 
 #include "zsa_internal.h"
@@ -337,85 +337,203 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
     lse[static_cast<int64_t>(h) * T + lo + qrow] = (m_run * scale_log2 + log2f(l_run)) * kLn2;
 }
 
+// fp32 storage (and bf16 at head dims 16 and 32): every product on
+// v_mfma_f32_32x32x2_f32, fp32 operands and sums. One workgroup of four
+// waves per (32 queries, head, sequence); the waves take the 32-key tiles in
+// turn and their (max, sum, O) are merged through LDS in wave order, so a
+// short sequence still spreads over the four SIMDs. The matrix instruction
+// is slow enough (64 cycles for 4096 FLOP) that operands come straight from
+// memory: 16 bytes of a K row a lane, and single V elements, 32 consecutive
+// channels of a row a half-wave. S^T = K Q^T leaves a lane with 16 keys of
+// one query, which is the B operand of O^T += V^T P^T (the two keys of a
+// step are those of the two lane halves). A vector-ALU kernel with one
+// query per thread held this place: 37.1 us on 4 x 64 rows, 4 heads of 32,
+// and 256 us on 8 ragged sequences of up to 200 rows, 12 heads of 64 (now 6.3
+// and 21.0).
+template <typename T>
+__device__ __forceinline__ float4 load4(const T* p);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* p) {
+  return *reinterpret_cast<const float4*>(p);
+}
+template <>
+__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+
 template <typename T, int HD>
-__global__ __launch_bounds__(64) void attn_valu_kernel(const T* __restrict__ Q,
+__global__ __launch_bounds__(256) void attn_f32_kernel(const T* __restrict__ Q,
                                                        const T* __restrict__ K,
                                                        const T* __restrict__ V, int64_t rs,
                                                        int kv_group, int causal, float scale,
                                                        const int32_t* __restrict__ cu,
                                                        T* __restrict__ O, int64_t os,
                                                        float* __restrict__ lse, int Tn) {
-  constexpr int BKEY = 32;
-  __shared__ float Ks[BKEY][HD];
-  __shared__ float Vs[BKEY][HD];
+  constexpr int NW = 4, KK = HD / 8;
+  constexpr int CT = HD < 32 ? 1 : HD / 32;  // 32-channel blocks of O (half empty at HD 16)
+  constexpr int HP = 33;                     // merge row stride: [channel][query]
+  __shared__ float so[NW][HD * HP];
+  __shared__ float sm[NW][32], sl[NW][32];
   const int b = blockIdx.z, h = blockIdx.y;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
-  const int qbase = blockIdx.x * 64;
-  if (qbase >= n) return;
-  const int q = qbase + threadIdx.x;
-  const bool active = q < n;
-  float qv[HD], o[HD];
+  const int nqb = (n + 31) / 32;
+  if (static_cast<int>(blockIdx.x) >= nqb) return;
+  const int qb = causal ? nqb - 1 - static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x);
+  const int q0 = qb * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  const int qrow = q0 + l32;
+  const T* kb = K + static_cast<int64_t>(lo) * rs + (h / kv_group) * HD;
+  const T* vb = V + static_cast<int64_t>(lo) * rs + (h / kv_group) * HD;
+  const bool vch = HD >= 32 || l32 < HD;  // lanes whose channel exists
+  float4 qf[KK];
 #pragma unroll
-  for (int c = 0; c < HD; ++c) {
-    qv[c] = active ? to_f32(Q[static_cast<int64_t>(lo + q) * rs + h * HD + c]) * scale : 0.f;
-    o[c] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int kend = causal ? min(n, qbase + 64) : n;
-  for (int j0 = 0; j0 < kend; j0 += BKEY) {
-    for (int e = threadIdx.x; e < BKEY * HD; e += 64) {
-      const int r = e / HD, c = e % HD;
-      const int j = j0 + r;
-      Ks[r][c] = j < n ? to_f32(K[static_cast<int64_t>(lo + j) * rs + (h / kv_group) * HD + c]) : 0.f;
-      Vs[r][c] = j < n ? to_f32(V[static_cast<int64_t>(lo + j) * rs + (h / kv_group) * HD + c]) : 0.f;
+  for (int s = 0; s < KK; ++s)
+    qf[s] = load4<T>(Q + static_cast<int64_t>(lo + min(qrow, n - 1)) * rs + h * HD + 8 * s + 4 * half);
+  float m_run = -INFINITY, l_run = 0.f;  // of the scaled scores; l_run: this lane's keys only
+  f32x16_t o[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
+  const int kend = causal ? min(n, q0 + 32) : n;
+  for (int j0 = wave * 32; j0 < kend; j0 += 32 * NW) {
+    float vr[CT][16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      // rows past the sequence count as zeros (their probability is 0)
+      const int j = j0 + 8 * (r >> 2) + 4 * half + (r & 3);
+      const T* vp = vb + static_cast<int64_t>(min(j, n - 1)) * rs;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        vr[ct][r] = j < n && vch ? to_f32(vp[ct * 32 + (HD < 32 ? l32 % HD : l32)]) : 0.f;
     }
-    __syncthreads();
-    if (active) {
-      for (int jj = 0; jj < BKEY; ++jj) {
-        const int j = j0 + jj;
-        if (j >= n || (causal && j > q)) continue;
-        float sc = 0.f;
+    f32x16_t s = {};
+    const T* kp = kb + static_cast<int64_t>(min(j0 + l32, n - 1)) * rs + 4 * half;
 #pragma unroll
-        for (int c = 0; c < HD; ++c) sc += qv[c] * Ks[jj][c];
-        if (sc > m) {
-          const float corr = expf(m - sc);
-          l *= corr;
+    for (int t = 0; t < KK; ++t) {
+      const float4 k4 = load4<T>(kp + 8 * t);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.x, qf[t].x, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.y, qf[t].y, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.z, qf[t].z, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.w, qf[t].w, s, 0, 0, 0);
+    }
+    // s[r]: key j0 + 8 (r/4) + 4 half + r%4, query qrow
+    const bool edge = j0 + 32 > n || (causal && j0 + 31 > q0);
+    float mloc = -INFINITY;
 #pragma unroll
-          for (int c = 0; c < HD; ++c) o[c] *= corr;
-          m = sc;
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + 8 * (r >> 2) + 4 * half + (r & 3);
+      s[r] = edge && (j >= n || (causal && j > qrow)) ? -INFINITY : s[r] * scale;
+      mloc = fmaxf(mloc, s[r]);
+    }
+    mloc = half_swap_max(mloc);
+    const float m_new = fmaxf(m_run, mloc);
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+      const float alpha = m_new == -INFINITY ? 1.0f : __expf(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __expf(s[r] - m_use);
+      l_run += s[r];
+    }
+    // A masked key's V row must not reach a query that cannot see it, also
+    // where it holds an infinity or a NaN, which a product with its zero
+    // probability would spread. Such rows are rare: the tile then goes
+    // through the vector ALU, key by key.
+    bool odd = false;
+    if (edge && causal) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) odd |= !(fabsf(vr[ct][r]) <= 3.402823466e38f);
+      odd = __builtin_amdgcn_ballot_w64(odd) != 0;
+    }
+    if (!odd) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          o[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[ct][r], s[r], o[ct], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 32; ++kk) {
+        // key j0 + kk: register (kk / 8) * 4 + kk % 4 of lane half (kk / 4) % 2
+        const float p = __shfl(s[(kk >> 3) * 4 + (kk & 3)], l32 + 32 * ((kk >> 2) & 1), 64);
+        if (j0 + kk <= qrow && j0 + kk < n) {
+          const T* vp = vb + static_cast<int64_t>(j0 + kk) * rs;
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int c = ct * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+              if (c < HD) o[ct][r] = fmaf(p, to_f32(vp[c]), o[ct][r]);
+            }
         }
-        const float p = expf(sc - m);
-        l += p;
-#pragma unroll
-        for (int c = 0; c < HD; ++c) o[c] += p * Vs[jj][c];
       }
     }
-    __syncthreads();
   }
-  if (active) {
-    const float inv = 1.0f / l;
+  l_run = half_swap_sum(l_run);
+  if (half == 0) {
+    sm[wave][l32] = m_run;
+    sl[wave][l32] = l_run;
+  }
 #pragma unroll
-    for (int c = 0; c < HD; ++c)
-      O[static_cast<int64_t>(lo + q) * os + h * HD + c] = from_f32<T>(o[c] * inv);
-    if (lse != nullptr) lse[static_cast<int64_t>(h) * Tn + lo + q] = m + logf(l);
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int c = ct * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+      if (c < HD) so[wave][c * HP + l32] = o[ct][r];
+    }
+  __syncthreads();
+  for (int it = tid; it < 32 * (HD / 4); it += 64 * NW) {
+    const int q = it / (HD / 4), c0 = (it % (HD / 4)) * 4;
+    if (q0 + q >= n) continue;
+    float m = sm[0][q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, sm[w][q]);
+    float l = 0.f, v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      // a wave without keys for this query holds the empty sum
+      if (sm[w][q] == -INFINITY && sl[w][q] == 0.f) continue;
+      const float f = __expf(sm[w][q] - (m == -INFINITY ? 0.f : m));
+      l = fmaf(f, sl[w][q], l);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(f, so[w][(c0 + e) * HP + q], v[e]);
+    }
+    const float inv = 1.0f / l;
+    T* op = O + static_cast<int64_t>(lo + q0 + q) * os + h * HD + c0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) op[e] = from_f32<T>(v[e] * inv);
+    if (c0 == 0 && lse != nullptr) lse[static_cast<int64_t>(h) * Tn + lo + q0 + q] = m + logf(l);
   }
 }
 
 template <typename T>
-hipError_t valu_dispatch(hipStream_t s, const void* q, const void* k, const void* v, int64_t rs,
+hipError_t f32_dispatch(hipStream_t s, const void* q, const void* k, const void* v, int64_t rs,
                          int H, int kvg, int hd, int causal, float scale, int B, int max_len, int Trows,
                          const int32_t* cu, void* out, int64_t os, float* lse) {
-  const dim3 grid((max_len + 63) / 64, H, B), block(64);
+  const dim3 grid((max_len + 31) / 32, H, B), block(256);
   const T* qp = static_cast<const T*>(q);
   const T* kp = static_cast<const T*>(k);
   const T* vp = static_cast<const T*>(v);
   T* op = static_cast<T*>(out);
   switch (hd) {
-    case 16: return launch(K_ATTENTION, attn_valu_kernel<T, 16>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
-    case 32: return launch(K_ATTENTION, attn_valu_kernel<T, 32>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
-    case 64: return launch(K_ATTENTION, attn_valu_kernel<T, 64>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
-    case 128: return launch(K_ATTENTION, attn_valu_kernel<T, 128>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
+    case 16: return launch(K_ATTENTION, attn_f32_kernel<T, 16>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
+    case 32: return launch(K_ATTENTION, attn_f32_kernel<T, 32>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
+    case 64: return launch(K_ATTENTION, attn_f32_kernel<T, 64>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
+    case 128: return launch(K_ATTENTION, attn_f32_kernel<T, 128>, grid, block, 0, s, qp, kp, vp, rs, kvg, causal, scale, cu, op, os, lse, Trows);
     default: return hipErrorInvalidValue;
   }
 }
@@ -453,9 +571,9 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
                   kv_group, causal, sl, cu_dev, op, out_stride, lse, T);
   }
   if (dtype == 1)
-    return valu_dispatch<bf16_t>(s, q, k, v, row_stride, H, kv_group, hd, causal, scale, B,
+    return f32_dispatch<bf16_t>(s, q, k, v, row_stride, H, kv_group, hd, causal, scale, B,
                                  max_len, T, cu_dev, out, out_stride, lse);
-  return valu_dispatch<float>(s, q, k, v, row_stride, H, kv_group, hd, causal, scale, B, max_len,
+  return f32_dispatch<float>(s, q, k, v, row_stride, H, kv_group, hd, causal, scale, B, max_len,
                               T, cu_dev, out, out_stride, lse);
 }
 

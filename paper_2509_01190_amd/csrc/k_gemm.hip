@@ -24,8 +24,10 @@
 //    v_mfma_f32_16x16x32_bf16 fragments;
 //  * gemm_bf16_mfma_kernel: the register-staged 128x128 original, kept as a
 //    tuning baseline (ZSA_GEMM_TILE).
-// The others use v_mfma_f32_32x32x16_bf16. fp32 storage: a 64x128
-// vector-ALU tile (4x8 outputs per thread).
+// The others use v_mfma_f32_32x32x16_bf16. fp32 storage: the fp32 matrix
+// instructions, 64x64 or 128x128 tiles through LDS (gemm_f32_tile_kernel) or
+// 32x32 outputs with K split over a workgroup's waves
+// (gemm_f32_direct_kernel).
 //
 // Epilogues (same order and precision in every kernel that takes them):
 // bias, exact GELU, SwiGLU on interleaved gate/up columns, residual add, or
@@ -1212,63 +1214,190 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// vector-ALU GEMM (fp32 storage, and any shape)
+// fp32 GEMM on the fp32 matrix instructions (fp32 storage, and bf16 products
+// whose K no bf16 kernel takes: operands widened on load, fp32 products)
 // ---------------------------------------------------------------------------
-constexpr int vBM = 64, vBN = 128, vBK = 16;
-
 template <typename T>
-__global__ __launch_bounds__(256) void gemm_valu_kernel(const T* __restrict__ X,
-                                                        const T* __restrict__ W, int M, int N,
-                                                        int K, EpiParams ep) {
-  __shared__ float As[vBK][vBM + 4];
-  __shared__ float Bs[vBK][vBN + 4];
-  __shared__ float tile[vBM * (vBN + 4)];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.x * vBM, n0 = blockIdx.y * vBN;
-  float acc[4][8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += vBK) {
-#pragma unroll
-    for (int i = 0; i < vBM * vBK / 256; ++i) {
-      const int e = tid + i * 256;
-      const int mm = e / vBK, kk = e % vBK;
-      const int gm = m0 + mm, gk = k0 + kk;
-      As[kk][mm] = (gm < M && gk < K) ? to_f32(X[static_cast<int64_t>(gm) * K + gk]) : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < vBN * vBK / 256; ++i) {
-      const int e = tid + i * 256;
-      const int nn = e / vBK, kk = e % vBK;
-      const int gn = n0 + nn, gk = k0 + kk;
-      Bs[kk][nn] = (gn < N && gk < K) ? to_f32(W[static_cast<int64_t>(gn) * K + gk]) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < vBK; ++kk) {
-      float a[4], b[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) b[j] = Bs[kk][tx * 8 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] += a[i] * b[j];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tile[(ty * 4 + i) * (vBN + 4) + tx * 8 + j] = acc[i][j];
-  __syncthreads();
-  epilogue_tile<T, vBM, vBN, 256>(tile, vBN + 4, m0, n0, M, N, ep);
+__device__ __forceinline__ float4 load4(const T* p);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* p) {
+  return *reinterpret_cast<const float4*>(p);
+}
+template <>
+__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
 }
 
+// BM x BN tile on four waves (2 x 2, TM x TN blocks of 32 x 32 each), K in
+// 32-wide slices through two LDS stages, the next slice's loads in registers
+// meanwhile. v_mfma_f32_32x32x2_f32: lane l gives row l % 32 and K slots
+// 4 (l / 32) + i of an 8-wide step i = 0 .. 3, for x and W alike. Bound by
+// the matrix instruction (64 cycles for 4096 FLOP, 157 TFLOP/s chip-wide):
+// a slice is 16 TM TN of them per wave against 4 (TM + TN) LDS reads.
+// K a multiple of 4; rows past M or N are clamped (their outputs are not
+// stored), K past the end reads as zeros.
+constexpr int fBK = 32, fLD = fBK + 4;
+
+template <typename T, int TM, int TN>
+__global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const T* __restrict__ X,
+                                                            const T* __restrict__ W, int M, int N,
+                                                            int K, EpiParams ep) {
+  constexpr int BM = 64 * TM, BN = 64 * TN;
+  constexpr int CPR = fBK / 4;                  // 4-element chunks per tile row
+  constexpr int ACH = BM * CPR / 256, BCH = BN * CPR / 256;
+  constexpr int STAGE = (BM + BN) * fLD;
+  constexpr int SM = 2 * STAGE > BM * (BN + 4) ? 2 * STAGE : BM * (BN + 4);
+  __shared__ __align__(16) float smem[SM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const T* xp[ACH];
+  const T* wp[BCH];
+  const int kc = (tid % CPR) * 4, r0 = tid / CPR;
+#pragma unroll
+  for (int i = 0; i < ACH; ++i) xp[i] = X + static_cast<int64_t>(min(m0 + r0 + 32 * i, M - 1)) * K + kc;
+#pragma unroll
+  for (int i = 0; i < BCH; ++i) wp[i] = W + static_cast<int64_t>(min(n0 + r0 + 32 * i, N - 1)) * K + kc;
+  float4 ar[ACH], br[BCH];
+  auto fetch = [&](int k0) {
+    const bool in = k0 + kc < K;
+#pragma unroll
+    for (int i = 0; i < ACH; ++i) ar[i] = in ? load4<T>(xp[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < BCH; ++i) br[i] = in ? load4<T>(wp[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  auto stash = [&](int buf) {
+    float* st = smem + buf * STAGE;
+#pragma unroll
+    for (int i = 0; i < ACH; ++i) *reinterpret_cast<float4*>(st + (r0 + 32 * i) * fLD + kc) = ar[i];
+#pragma unroll
+    for (int i = 0; i < BCH; ++i) *reinterpret_cast<float4*>(st + (BM + r0 + 32 * i) * fLD + kc) = br[i];
+  };
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  fetch(0);
+  stash(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += fBK, buf ^= 1) {
+    const bool more = k0 + fBK < K;
+    if (more) fetch(k0 + fBK);
+    const float* as = smem + buf * STAGE + (wm * 32 * TM + l32) * fLD + 4 * half;
+    const float* bs = smem + buf * STAGE + (BM + wn * 32 * TN + l32) * fLD + 4 * half;
+#pragma unroll
+    for (int s = 0; s < fBK / 8; ++s) {
+      float4 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const float4*>(as + i * 32 * fLD + 8 * s);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const float4*>(bs + j * 32 * fLD + 8 * s);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].x, b[j].x, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].y, b[j].y, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].z, b[j].z, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].w, b[j].w, acc[i][j], 0, 0, 0);
+        }
+    }
+    // the other stage was last read before the barrier that ended the step before
+    if (more) stash(buf ^ 1);
+    __syncthreads();
+  }
+  // acc[i][j][r]: row 32 i + 8 (r/4) + 4 half + r%4, column 32 j + l32 of the wave's part
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        smem[(wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3)) * (BN + 4) +
+             wn * 32 * TN + 32 * j + l32] = acc[i][j][r];
+  __syncthreads();
+  epilogue_tile<T, BM, BN, 256>(smem, BN + 4, m0, n0, M, N, ep);
+}
+
+// 32 x 32 outputs per workgroup, K split over its eight waves (sums added in
+// wave order through LDS): products with too few 64 x 64 tiles for the CUs.
+// v_mfma_f32_16x16x4_f32 on operands loaded straight from memory, 16 rows x
+// 64 bytes a load: lane l gives row l % 16 and K slots 4 (l / 16) + i.
+template <typename T>
+__global__ __launch_bounds__(512) void gemm_f32_direct_kernel(const T* __restrict__ X,
+                                                              const T* __restrict__ W, int M,
+                                                              int N, int K, int kchunk,
+                                                              EpiParams ep) {
+  constexpr int NW = 8, LDT = 36;
+  __shared__ __align__(16) float red[NW][32 * LDT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+  const int kb = wave * kchunk, ke = min(K, kb + kchunk);
+  const T* xp[2];
+  const T* wp[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    xp[i] = X + static_cast<int64_t>(min(m0 + 16 * i + l16, M - 1)) * K + 4 * g;
+    wp[i] = W + static_cast<int64_t>(min(n0 + 16 * i + l16, N - 1)) * K + 4 * g;
+  }
+  f32x4_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = {0.f, 0.f, 0.f, 0.f};
+  float4 a[2][2], b[2][2];  // [buffer][block]: the next step's loads fly during this step's products
+  auto fetch = [&](int u, int k) {
+    const bool in = k + 4 * g < ke;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a[u][i] = in ? load4<T>(xp[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      b[u][i] = in ? load4<T>(wp[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  auto step = [&](int u) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i].x, b[u][j].x, acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i].y, b[u][j].y, acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i].z, b[u][j].z, acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i].w, b[u][j].w, acc[i][j], 0, 0, 0);
+      }
+  };
+  fetch(0, kb);
+  for (int k = kb; k < ke; k += 32) {
+    fetch(1, k + 16);
+    step(0);
+    fetch(0, k + 32);
+    step(1);
+  }
+  // acc[i][j][r]: row 16 i + 4 g + r, column 16 j + l16
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][(16 * i + 4 * g + r) * LDT + 16 * j + l16] = acc[i][j][r];
+  __syncthreads();
+  for (int e = tid; e < 32 * 32; e += 64 * NW) {
+    const int at = (e >> 5) * LDT + (e & 31);
+    float v = red[0][at];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[w][at];
+    red[0][at] = v;
+  }
+  __syncthreads();
+  epilogue_tile<T, 32, 32, 64 * NW>(red[0], LDT, m0, n0, M, N, ep);
+}
 
 // ---------------------------------------------------------------------------
 // persistent bf16 GEMM, epilogue in registers (bias, GELU, residual)
@@ -2519,6 +2648,33 @@ hipError_t launch_dma(hipStream_t s, const void* x, int M, int K, const void* w,
                 static_cast<const bf16_t*>(w), M, N, K, ep, S > 1 ? kchunk : K, part);
 }
 
+// The fp32 kernels by size. A vector-ALU kernel with 64 x 128 tiles took
+// 41.4 us a product at 256 rows of the 128-wide stack (now 5.9, the split-K
+// kernel) and 297 us at about 900 rows of the 768-wide block (now 39: 44 for
+// the two on 64 x 64 tiles, 35 for the two on the split-K kernel). The 32 x
+// 32 split-K kernel where the 64 x 64
+// tiles would leave CUs without one and a rotary head lies within its 32
+// columns; 128 x 128 tiles (half the operand bytes per FLOP) from two of
+// them per CU on, and where a rotary head is wider than 64.
+template <typename T>
+hipError_t launch_f32(hipStream_t s, const void* x, int M, int K, const void* w, int N,
+                      const EpiParams& ep) {
+  const T* xp = static_cast<const T*>(x);
+  const T* wp = static_cast<const T*>(w);
+  const int head = ep.epi == EPI_ROPE ? ep.head_dim : 1;
+  auto tiles = [&](int b) { return static_cast<long>((M + b - 1) / b) * ((N + b - 1) / b); };
+  if (head <= 32 && tiles(64) < device_cus()) {
+    const int kchunk = ((K + 8 * 16 - 1) / (8 * 16)) * 16;
+    return launch(K_GEMM, gemm_f32_direct_kernel<T>, dim3((M + 31) / 32, (N + 31) / 32), dim3(512),
+                  0, s, xp, wp, M, N, K, kchunk, ep);
+  }
+  if (head > 64 || tiles(128) >= 2 * device_cus())
+    return launch(K_GEMM, gemm_f32_tile_kernel<T, 2, 2>, dim3((M + 127) / 128, (N + 127) / 128),
+                  dim3(256), 0, s, xp, wp, M, N, K, ep);
+  return launch(K_GEMM, gemm_f32_tile_kernel<T, 1, 1>, dim3((M + 63) / 64, (N + 63) / 64), dim3(256),
+                0, s, xp, wp, M, N, K, ep);
+}
+
 // ZSA_GEMM_TILE pins one kernel variant (a tuning aid; 0 or unset = by shape):
 // 128 / 256 / 2564 / 2568: register-staged 128x128, 256x128, 256x256 on 4 and
 // on 8 waves; 1281 / 2563 / 2562 / 2561: direct-to-LDS 128x128, 256x128,
@@ -2823,12 +2979,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* x, int M, int K, co
     if (persist_ok(M, N, K, ep)) return launch_persist_any<64, 2>(s, x, M, K, w, N, ep);
     return launch_dma<128, 128, 2, 2, 64, 2, 128>(s, x, M, K, w, N, ep);
   }
-  const dim3 grid((M + vBM - 1) / vBM, (N + vBN - 1) / vBN);
-  if (dtype == 1)
-    return launch(K_GEMM, gemm_valu_kernel<bf16_t>, grid, dim3(256), 0, s,
-                  static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), M, N, K, ep);
-  return launch(K_GEMM, gemm_valu_kernel<float>, grid, dim3(256), 0, s,
-                static_cast<const float*>(x), static_cast<const float*>(w), M, N, K, ep);
+  return dtype == 1 ? launch_f32<bf16_t>(s, x, M, K, w, N, ep) : launch_f32<float>(s, x, M, K, w, N, ep);
 }
 
 }  // namespace zsa

@@ -20,7 +20,7 @@
 // workgroups start at the first query that can see their keys and skip the
 // 32-key columns no query of a tile can see.
 //
-// fp32 / other head dims: one thread per key, vector ALU.
+// fp32 / other head dims: the same on the fp32 matrix instruction.
 #include <math.h>
 
 #include "zsa_internal.h"
@@ -190,78 +190,105 @@ __global__ __launch_bounds__(64 * kScoreWaves) __attribute__((amdgpu_waves_per_e
   }
 }
 
+// fp32 storage (and bf16 at head dims 16 and 32), on
+// v_mfma_f32_32x32x2_f32 with fp32 operands: one workgroup of four waves per
+// (32 keys, query head, sequence). A wave keeps its keys' operand in
+// registers and strides over the 32-query tiles; operands come straight
+// from memory (the matrix instruction, at 64 cycles, is the slower side).
+// One partial vector per head, as in the bf16 kernel. A vector-ALU kernel
+// that summed all heads of a key in one thread held this place: 94 us on
+// 4 x 64 rows, 4 heads of 32, and 1657 us on 8 ragged sequences of up
+// to 200 rows, 12 heads of 64 (now 4.1 and 12.2).
+template <typename T>
+__device__ __forceinline__ float4 load4(const T* p);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* p) {
+  return *reinterpret_cast<const float4*>(p);
+}
+template <>
+__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+
 template <typename T, int HD>
-__global__ __launch_bounds__(64) void score_valu_kernel(const T* __restrict__ Q,
+__global__ __launch_bounds__(256) void score_f32_kernel(const T* __restrict__ Q,
                                                         const T* __restrict__ K, int64_t rs,
-                                                        const float* __restrict__ lse, int H,
+                                                        const float* __restrict__ lse,
                                                         int kv_group, int causal, float scale,
                                                         const int32_t* __restrict__ cu, int Tn,
-                                                        int groups, float* __restrict__ partials) {
-  __shared__ float Qs[32][HD];
-  __shared__ float Ls[32];
-  const int b = blockIdx.z, g = blockIdx.y;
+                                                        float* __restrict__ partials) {
+  constexpr int NW = 4, KK = HD / 8;
+  __shared__ float red[NW][32];
+  const int b = blockIdx.z, h = blockIdx.y;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
-  const int jbase = blockIdx.x * 64;
-  if (jbase >= n) return;
-  const int j = jbase + threadIdx.x;
-  float acc = 0.f;
-  for (int h = g; h < H; h += groups) {
-    float kv[HD];
+  const int j0 = blockIdx.x * 32;
+  if (j0 >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  const int j = j0 + l32;
+  float4 kf[KK];
 #pragma unroll
-    for (int c = 0; c < HD; ++c)
-      kv[c] = j < n ? to_f32(K[static_cast<int64_t>(lo + j) * rs + (h / kv_group) * HD + c]) * scale : 0.f;
-    const int qstart = causal ? jbase : 0;
-    for (int i0 = qstart; i0 < n; i0 += 32) {
-      __syncthreads();
-      for (int e = threadIdx.x; e < 32 * HD; e += 64) {
-        const int r = e / HD, c = e % HD;
-        const int i = i0 + r;
-        Qs[r][c] = i < n ? to_f32(Q[static_cast<int64_t>(lo + i) * rs + h * HD + c]) : 0.f;
-      }
-      if (threadIdx.x < 32) {
-        const int i = i0 + threadIdx.x;
-        Ls[threadIdx.x] = i < n ? lse[static_cast<int64_t>(h) * Tn + lo + i] : 0.f;
-      }
-      __syncthreads();
-      if (j < n) {
-        for (int ii = 0; ii < 32; ++ii) {
-          const int i = i0 + ii;
-          if (i >= n || (causal && j > i)) continue;
-          float sc = 0.f;
+  for (int t = 0; t < KK; ++t)
+    kf[t] = load4<T>(K + static_cast<int64_t>(lo + min(j, n - 1)) * rs + (h / kv_group) * HD + 8 * t + 4 * half);
+  const float* lh = lse + static_cast<int64_t>(h) * Tn + lo;
+  float colsum = 0.f;
+  for (int i0 = (causal ? j0 : 0) + wave * 32; i0 < n; i0 += 32 * NW) {
+    float L[16];
 #pragma unroll
-          for (int c = 0; c < HD; ++c) sc += Qs[ii][c] * kv[c];
-          acc += expf(sc - Ls[ii]);
-        }
-      }
+    for (int r = 0; r < 16; ++r) L[r] = lh[min(i0 + 8 * (r >> 2) + 4 * half + (r & 3), n - 1)];
+    const T* qp = Q + static_cast<int64_t>(lo + min(i0 + l32, n - 1)) * rs + h * HD + 4 * half;
+    f32x16_t s = {};
+#pragma unroll
+    for (int t = 0; t < KK; ++t) {
+      const float4 q4 = load4<T>(qp + 8 * t);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(q4.x, kf[t].x, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(q4.y, kf[t].y, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(q4.z, kf[t].z, s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(q4.w, kf[t].w, s, 0, 0, 0);
+    }
+    // s[r]: query i0 + 8 (r/4) + 4 half + r%4, key j
+    const bool edge = i0 + 32 > n || (causal && j0 + 31 > i0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = i0 + 8 * (r >> 2) + 4 * half + (r & 3);
+      const float p = __expf(fmaf(s[r], scale, -L[r]));
+      colsum += edge && (i >= n || (causal && j > i)) ? 0.f : p;
     }
   }
-  if (j < n) partials[static_cast<int64_t>(g) * Tn + lo + j] = acc;
+  colsum = half_swap_sum(colsum);
+  if (half == 0) red[wave][l32] = colsum;
+  __syncthreads();
+  if (tid < 32 && j < n)
+    partials[static_cast<int64_t>(h) * Tn + lo + j] = red[0][l32] + red[1][l32] + red[2][l32] + red[3][l32];
 }
 
 template <typename T>
-hipError_t valu_dispatch(hipStream_t s, const void* q, const void* k, int64_t rs,
-                         const float* lse, int H, int kvg, int hd, int causal, float scale, int B,
-                         int max_len, int Trows, const int32_t* cu, float* partials,
-                         int groups) {
-  const dim3 grid((max_len + 63) / 64, groups, B), block(64);
+hipError_t f32_dispatch(hipStream_t s, const void* q, const void* k, int64_t rs,
+                        const float* lse, int H, int kvg, int hd, int causal, float scale, int B,
+                        int max_len, int Trows, const int32_t* cu, float* partials) {
+  const dim3 grid((max_len + 31) / 32, H, B), block(256);
   const T* qp = static_cast<const T*>(q);
   const T* kp = static_cast<const T*>(k);
   switch (hd) {
-    case 16: return launch(K_SCORE, score_valu_kernel<T, 16>, grid, block, 0, s, qp, kp, rs, lse, H, kvg, causal, scale, cu, Trows, groups, partials);
-    case 32: return launch(K_SCORE, score_valu_kernel<T, 32>, grid, block, 0, s, qp, kp, rs, lse, H, kvg, causal, scale, cu, Trows, groups, partials);
-    case 64: return launch(K_SCORE, score_valu_kernel<T, 64>, grid, block, 0, s, qp, kp, rs, lse, H, kvg, causal, scale, cu, Trows, groups, partials);
-    case 128: return launch(K_SCORE, score_valu_kernel<T, 128>, grid, block, 0, s, qp, kp, rs, lse, H, kvg, causal, scale, cu, Trows, groups, partials);
+    case 16: return launch(K_SCORE, score_f32_kernel<T, 16>, grid, block, 0, s, qp, kp, rs, lse, kvg, causal, scale, cu, Trows, partials);
+    case 32: return launch(K_SCORE, score_f32_kernel<T, 32>, grid, block, 0, s, qp, kp, rs, lse, kvg, causal, scale, cu, Trows, partials);
+    case 64: return launch(K_SCORE, score_f32_kernel<T, 64>, grid, block, 0, s, qp, kp, rs, lse, kvg, causal, scale, cu, Trows, partials);
+    case 128: return launch(K_SCORE, score_f32_kernel<T, 128>, grid, block, 0, s, qp, kp, rs, lse, kvg, causal, scale, cu, Trows, partials);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-// Partial vectors per row: one per query head on the MFMA path.
+// Partial vectors per row: one per query head.
 int score_groups(int dtype, int H, int hd, int T) {
+  (void)dtype;
+  (void)hd;
   (void)T;
-  return dtype == 1 && (hd == 64 || hd == 128) ? H : 1;
+  return H;
 }
 
 hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
@@ -269,8 +296,8 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
                         float scale, int B, int max_len, int T, const int32_t* cu_dev,
                         float* partials, int groups) {
   if (B == 0 || max_len == 0) return hipSuccess;
+  if (groups != H) return hipErrorInvalidValue;
   if (dtype == 1 && (hd == 64 || hd == 128)) {
-    if (groups != H) return hipErrorInvalidValue;
     const bf16_t* qp = static_cast<const bf16_t*>(q);
     const bf16_t* kp = static_cast<const bf16_t*>(k);
     const float sl = scale * kLog2e;
@@ -296,10 +323,10 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
 #undef ZSA_SCORE
   }
   if (dtype == 1)
-    return valu_dispatch<bf16_t>(s, q, k, row_stride, lse, H, kv_group, hd, causal, scale, B,
-                                 max_len, T, cu_dev, partials, groups);
-  return valu_dispatch<float>(s, q, k, row_stride, lse, H, kv_group, hd, causal, scale, B, max_len,
-                              T, cu_dev, partials, groups);
+    return f32_dispatch<bf16_t>(s, q, k, row_stride, lse, H, kv_group, hd, causal, scale, B,
+                                max_len, T, cu_dev, partials);
+  return f32_dispatch<float>(s, q, k, row_stride, lse, H, kv_group, hd, causal, scale, B, max_len,
+                             T, cu_dev, partials);
 }
 
 }  // namespace zsa
