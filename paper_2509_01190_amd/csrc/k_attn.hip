@@ -3,22 +3,25 @@
 // over packed variable-length rows; also writes the natural-log
 // log-sum-exp of every score row (used by the contribution scores).
 //
-// bf16, head_dim 64/128 (MFMA): one workgroup of NW waves per (32 NW-query
-// block, head, sequence); each wave owns 32 queries and walks 64-key tiles
-// staged in LDS (K row-major; V transposed at head_dim 64, row-major at 128
-// and read through transposing LDS reads). The wave computes the
-// *transposed* score tile S^T = K Q^T with v_mfma_f32_32x32x16_bf16, so a
-// lane holds 32 key scores of one query: the online-softmax max and sum are
-// in-lane plus one swap with lane l^32, and the probabilities already sit in
-// the B-operand layout of O^T += V^T P^T (P rounded to bf16), with no trip
-// through LDS. The k-slot order of P^T is whatever the accumulator gives; V^T
-// is read from LDS in that same order, which leaves the contraction unchanged.
-// Causal blocks skip key tiles above the diagonal and are scheduled
-// heaviest-first.
+// bf16, head_dim 64/128 (MFMA): every kernel computes the *transposed* score
+// tile S^T = K Q^T with v_mfma_f32_32x32x16_bf16, so a lane holds the scores
+// of one query: the softmax sums are in-lane plus one swap with lane l^32,
+// and the probabilities already sit in the B-operand layout of
+// O^T += V^T P^T (P rounded to bf16), with no trip through LDS. The k-slot
+// order of P^T is whatever the accumulator gives; V^T is read from LDS in
+// that same order, which leaves the contraction unchanged.
+//  * attn_wide_kernel (longer sequences): 32-key steps, each step's
+//    exponentials interleaved with the products of its neighbours, K/V tiles
+//    loaded straight into LDS;
+//  * attn_mfma_kernel (shorter ones): one workgroup of NW waves per 32
+//    NW-query block, 64-key tiles staged through registers.
 //
 // fp32 (and bf16 at any other head_dim): the same transposed scores on the
 // fp32 matrix instruction, four waves sharing 32 queries' keys.
 #include <math.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "zsa_internal.h"
 
@@ -31,8 +34,38 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// Head dim 64 fits four waves per SIMD (128 registers), 128 two. A workgroup
-// reads every K and V row of its sequence and head once, so the bytes moved
+// Which (sequence, head, query block) a workgroup takes. Workgroup L runs on XCD L % 8, in order of L within it. The (sequence,
+// head) pairs are dealt to the XCDs in turn (with a multiple of 8 heads each
+// XCD takes neighbouring ones, which share key/value heads and so its L2), and
+// an XCD walks `chunk` of its pairs at a time, last query block first. With
+// the query block in the grid's fastest dimension, as these kernels had it,
+// equal sequences put the same query block on the same XCD throughout: under
+// the causal mask one XCD got every longest block and another every shortest
+// (the same kernel: 4 x 4096 causal rows, 32 heads of 128, 918 -> 596 us; 8 x
+// 2048, 32 heads of 64, 286 -> 182; 12 ragged sequences of up to 4095 rows,
+// 1697 -> 852). Measured with attn_wide_kernel, us, one pair at a time / a
+// sequence's / all: causal, 8 x 2048 of 64 211 / 174 / 162, 16 x 1024, 12
+// heads of 64, 55.9 / 55.1 / 43.1; without a mask, where every block of a
+// sequence is as long and the neighbours' K and V are still in L2, 8 x 2048
+// of 64 267 / 263 / 282, 32 x 512, 12 heads, 36.0 / 35.8 / 37.4. So all of
+// them (the longest blocks first, the shortest at the end) under the mask or
+// with sequences of several lengths, and a sequence's otherwise.
+struct Place { int b, h, i; };
+// grid: x = 8 * chunk (XCD fastest), y = query blocks, z = chunks of pairs
+__device__ __forceinline__ bool place(int H, int pairs, Place* at) {
+  const int e = static_cast<int>((blockIdx.z * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7));
+  if (e >= pairs) return false;
+  at->b = e / H;
+  const int x = e - at->b * H;
+  at->h = H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
+  at->i = static_cast<int>(gridDim.y - 1 - blockIdx.y);
+  return true;
+}
+
+// Shorter sequences: four waves per SIMD at head dim 64 (128 registers), two
+// at 128, walking 64-key tiles staged in LDS (K row-major; V transposed at
+// head dim 64, row-major at 128 and read through transposing LDS reads). A
+// workgroup reads every K and V row of its sequence and head once, so the bytes moved
 // per query fall as the query block grows: the loads, not the MFMAs or the
 // exponentials, bound the kernel at these lengths (a copy without any of
 // the compute takes 35 of the 48.5 us of 32 sequences x 12 heads x 512 rows
@@ -41,7 +74,7 @@ template <int HD, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 4 : 2))) void attn_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     int64_t rs, int kv_group, int causal, float scale_log2, const int32_t* __restrict__ cu,
-    bf16_t* __restrict__ O, int64_t os, float* __restrict__ lse, int T) {
+    bf16_t* __restrict__ O, int64_t os, float* __restrict__ lse, int T, int H, int pairs) {
   constexpr int NT = 64 * NW, BQ = 32 * NW, BKEY = 64;
   constexpr int KLD = HD + 8;    // K tile row stride (bf16)
   // V^T tile row stride (bf16): 34 dwords. The fragment reads (32
@@ -79,13 +112,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   constexpr int VPR = VITEMS < NT ? 1 : VITEMS / NT;  // per thread (some idle if fewer)
   __shared__ __align__(16) unsigned char smem[SBYTES];
 
-  const int b = blockIdx.z, h = blockIdx.y;
+  Place at;
+  if (!place(H, pairs, &at)) return;
+  const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
-  const int nqb = (n + BQ - 1) / BQ;
-  if (static_cast<int>(blockIdx.x) >= nqb) return;
-  const int qb = causal ? nqb - 1 - static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x);
-  const int q0 = qb * BQ;
+  const int q0 = at.i * BQ;
+  if (q0 >= n) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, l32 = lane & 31;
   const int qrow = q0 + wave * 32 + l32;
@@ -337,6 +370,337 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
     lse[static_cast<int64_t>(h) * T + lo + qrow] = (m_run * scale_log2 + log2f(l_run)) * kLn2;
 }
 
+// Longer sequences. A wave owns 32 QB queries (QB = 2 at head dim 64: each K
+// and V fragment read from LDS serves two products; 1 at 128, whose output
+// and query fragments fill the registers) and goes over the keys in steps of
+// 32. In step u it issues the products S(u + 1) = K Q^T and O += V P(u - 1) one
+// at a time with the exponentials, sums and packing of step u between them,
+// in an order fixed by scheduling barriers: the matrix instruction takes 8
+// passes after its issue, which the vector instructions of the same wave fill
+// (probe: one product and 8 fma 18.5 ns interleaved at four waves per SIMD
+// against 14.0 + 10.3 apart; with 8 exponentials 32 against 14 + 30). Two
+// waves per SIMD: alone a wave issues a vector instruction every 5.6 cycles
+// where several reach 2.7, and a form with 64 queries of head dim 128 on one
+// wave per SIMD was slower (310 against 256 us on 8 x 2048 rows, 16 heads).
+//  * No row max per step. P is taken relative to a reference, the max
+//    over the first 64 keys; it moves (and O, the sum and this step's P are
+//    redone) only when a lane's 16 probabilities sum to over 2^12, which any
+//    one of them above that does. P up to 2^12 is exact enough: bf16 keeps
+//    its relative precision, the sums are fp32, and output and log-sum-exp
+//    are both taken relative to the reference.
+//  * K and V tiles of 64 keys go straight to LDS, two tiles ahead, one
+//    barrier per tile: staged through registers they cost 50 of 310 us (8 x
+//    2048 rows, 16 heads of 128). The loads are asm without outputs, as the
+//    compiler waits for a load it knows to write LDS before any later LDS
+//    read; turn_over() waits for them. Rows are unpadded; 16-byte chunk c of
+//    row r lies at c ^ ksw(r) (K: the 16 rows of a read phase fall on all 64
+//    banks) or c ^ vsw(r) (V: the four rows a transposing read takes do).
+// Same box, us, this kernel against the register-staged one below in the same
+// workgroup order: 4 x 4096 causal, 32 heads of 128, 543 / 603; 8 x 2048, 32
+// heads of 64, 186 / 205 causal, 291 / 331 without; 32 x 512, 12 heads of 64,
+// 37.2 / 40.7; 4 x 500 causal, 32 heads of 128, 20.7 / 22.7; and where it
+// loses: 8 x 300 of 128 27.6 / 23.8, 32 x 256, 12 of 64, 17.9 / 17.4, 128 x
+// 64 of 64 21.4 / 15.5 (graph replays, fresh outputs each call).
+template <int HD, int QB, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_wide_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    int64_t rs, int kv_group, int causal, float scale_log2, const int32_t* __restrict__ cu,
+    bf16_t* __restrict__ O, int64_t os, float* __restrict__ lse, int T, int H, int pairs) {
+  constexpr int WQ = 32 * QB, BQ = WQ * NW, BK = 64;
+  constexpr int KK = HD / 16, CT = HD / 32, CPR = HD / 8;
+  constexpr int RB = HD * 2, HALF = BK * RB, BUF = 2 * HALF, NB = 3, OLD = HD + 8;
+  constexpr int SBYTES = NB * BUF > NW * WQ * OLD * 2 ? NB * BUF : NW * WQ * OLD * 2;
+  constexpr int RPL = 1024 / RB, LPW = HALF / 1024 / NW;  // rows per load, loads per wave and operand
+  static_assert(LPW * NW * 1024 == HALF && NW % 4 == 0, "tile split");
+  __shared__ __align__(1024) unsigned char smem[SBYTES];
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef __attribute__((address_space(3))) const char lds_char;
+
+  Place at;
+  if (!place(H, pairs, &at)) return;
+  const int b = at.b, h = at.h;
+  const int lo = cu[b];
+  const int n = cu[b + 1] - lo;
+  const int q0 = at.i * BQ;
+  if (q0 >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int wq0 = q0 + wave * WQ;  // the wave's first query
+
+  const int hk = h / kv_group;
+  const uint32_t row_bytes = static_cast<uint32_t>(rs * 2);
+  const uint32_t seq_bytes = static_cast<uint32_t>(n) * row_bytes;
+  auto resource = [&](const bf16_t* p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p + static_cast<int64_t>(lo) * rs + hk * HD);
+    const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(seq_bytes))), 0x00020000u};
+    return r;
+  };
+  const u32x4 kres = resource(K), vres = resource(V);
+  // K row r keeps its 16-byte chunk c at c ^ ksw(r), V row r at c ^ vsw(r)
+  auto ksw = [](int r) { return HD == 64 ? (r >> 1) & 7 : r & 15; };
+  auto vsw = [](int r) { return HD == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
+  const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
+  const uint32_t koff = lrow * row_bytes + (((lane % CPR) ^ ksw(lrow)) << 4);
+  const uint32_t voff = lrow * row_bytes + (((lane % CPR) ^ vsw(lrow)) << 4);
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
+  // (m0, which the loads take their LDS address from, is set by the compiler
+  // right before each use of its own)
+  auto load_tile = [&](int t, int buf) {
+    const uint32_t t0 = static_cast<uint32_t>(t) * (BK * row_bytes);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t d = lds0 + buf * BUF + i * (NW * 1024), so = t0 + i * (NW * RPL) * row_bytes;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(koff + so), "s"(kres) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(voff + so), "s"(vres) : "memory");
+    }
+  };
+
+  const int kend = causal ? min(n, q0 + BQ) : n;
+  const int nt = (kend + BK - 1) / BK;
+  // the wave's own tiles: under the causal mask none past its last query
+  const int ntw = causal ? min(nt, (wq0 + WQ + BK - 1) / BK) : nt;
+  load_tile(0, 0);
+  if (nt > 1) load_tile(1, 1);
+
+  bf16x8_t qf[QB][KK];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      // rows past the sequence are clamped, not zeroed: their outputs are not stored
+      const int qr = min(wq0 + 32 * qb + l32, n - 1);
+      qf[qb][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
+                                                    Q + static_cast<int64_t>(lo + qr) * rs + h * HD + kk * 16 + half * 8));
+    }
+
+  float mu[QB], l_run[QB];  // reference max (scaled, exp2 units); sum over this lane's keys
+  f32x16_t o[QB][CT], sa[QB], sb[QB];
+  bf16x8_t pf[QB][2];  // P of the last step: [query block][16 keys]
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    l_run[qb] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[qb][ct][r] = 0.f;
+  }
+
+  // fragment addresses within a tile: K rows l32 (+ 32), chunk 2 kk + half;
+  // V key rows 4 half + r (+ 8, 16 ..), the channel runs of a transposing read
+  const uint32_t kf0 = l32 * RB, vrow = 4 * half + ((lane & 15) >> 2);
+  const int ks0 = ksw(l32), vs0 = vsw(vrow);
+  const uint32_t vf0 = HALF + vrow * RB + (lane & 1) * 8;
+  const int vch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+  uint32_t kaddr[KK], vaddr[CT];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) kaddr[kk] = kf0 + (((2 * kk + half) ^ ks0) << 4);
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) vaddr[ct] = vf0 + (((4 * ct + vch) ^ vs0) << 4);
+  auto read_k = [&](const unsigned char* base, int kk) {
+    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + kaddr[kk]));
+  };
+  auto read_v = [&](const unsigned char* base, int g, int ct) {
+    const unsigned char* vr = base + vaddr[ct] + g * (16 * RB);
+    const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)vr));
+    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(vr + 8 * RB)));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo4), h2 = __builtin_bit_cast(uint2, hi4);
+    const u32x4 av = {l2.x, l2.y, h2.x, h2.y};
+    return __builtin_bit_cast(bf16x8_t, av);
+  };
+  const f32x16_t zero = {};
+  auto row_max = [&](const f32x16_t& s) {
+    float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
+    return half_swap_max(fmaxf(mx, s[15]));
+  };
+  auto mask = [&](int u, f32x16_t (&s)[QB]) {
+    const int j0 = 32 * u;
+    if (j0 + 32 <= n && !(causal && j0 + 31 > wq0)) return;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      // keys from this lane's limit on are masked
+      int lim = (causal ? min(n, wq0 + 32 * qb + l32 + 1) : n) - j0 - 4 * half;
+      asm("" : "+v"(lim));  // the comparisons stay here (hoisted, their masks fill the scalar registers)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r >> 2) + (r & 3) >= lim) s[qb][r] = -INFINITY;
+    }
+  };
+  // one step: the exponentials of step u (scores s) beside the products of
+  // O += V P(u - 1) and S(u + 1) = sn (the first step: alone)
+  auto step = [&](int u, int bufn, int ksn, int bufp, int ksp, f32x16_t (&s)[QB], f32x16_t (&sn)[QB], auto first_c) {
+    constexpr bool first = decltype(first_c)::value;
+    if (!first) mask(u, s);
+    constexpr int FA = 2;                                   // fragments in flight ahead of their use
+    constexpr int NF = KK + 2 * CT, NS = QB * NF;           // operand fragments, matrix instructions
+    constexpr int NU = 16 * QB;                             // pieces of vector work
+    const unsigned char* kp = smem + bufn * BUF + ksn * (32 * RB);
+    const unsigned char* vp = smem + bufp * BUF + ksp * (32 * RB);
+    bf16x8_t fr[FA + 1];
+    auto read = [&](int f) { fr[f % (FA + 1)] = f < KK ? read_k(kp, f) : read_v(vp, (f - KK) / CT, (f - KK) % CT); };
+    auto product = [&](int i) {
+      const int f = i / QB, qb = i % QB;
+      if (f < KK)
+        sn[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f % (FA + 1)], qf[qb][f], f == 0 ? zero : sn[qb], 0, 0, 0);
+      else
+        o[qb][(f - KK) % CT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            fr[f % (FA + 1)], pf[qb][(f - KK) / CT], o[qb][(f - KK) % CT], 0, 0, 0);
+    };
+    float rsum[QB], a0 = 0.f, a1 = 0.f, p0 = 0.f, p1 = 0.f;
+    u32x4 pn[QB][2];
+    auto work = [&](int w) {
+      const int qb = w >> 4, r = w & 14;
+      if ((w & 1) == 0) {
+        p0 = __builtin_amdgcn_exp2f(fmaf(s[qb][r], scale_log2, -mu[qb]));
+        p1 = __builtin_amdgcn_exp2f(fmaf(s[qb][r + 1], scale_log2, -mu[qb]));
+        asm volatile("" : "+v"(p0), "+v"(p1));  // computed here, beside this step's products
+      } else {
+        uint32_t pw = pack_bf16x2(p0, p1);
+        a0 = r == 0 ? p0 : a0 + p0;
+        a1 = r == 0 ? p1 : a1 + p1;
+        asm volatile("" : "+v"(pw), "+v"(a0), "+v"(a1));
+        pn[qb][r >> 3][(r >> 1) & 3] = pw;
+        if (r == 14) rsum[qb] = a0 + a1;
+      }
+    };
+    if constexpr (first) {
+#pragma unroll
+      for (int k = 0; k < NU; ++k) work(k);
+    } else {
+#pragma unroll
+      for (int f = 0; f < FA; ++f) read(f);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        if (i % QB == 0 && i / QB + FA < NF) read(i / QB + FA);
+        product(i);
+#pragma unroll
+        for (int k = NU * i / NS; k < NU * (i + 1) / NS; ++k) work(k);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    bool high = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) high |= !(rsum[qb] <= 4096.f);
+    if (!first && __builtin_amdgcn_ballot_w64(high) != 0) {
+      // a score far above the reference: move it, and redo this step's P
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const float m_new = fmaxf(mu[qb], row_max(s[qb]) * scale_log2);
+        const float alpha = __builtin_amdgcn_exp2f(mu[qb] - m_new);
+        mu[qb] = m_new;
+        l_run[qb] *= alpha;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[qb][ct][r] *= alpha;
+        rsum[qb] = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const float e0 = __builtin_amdgcn_exp2f(fmaf(s[qb][r], scale_log2, -m_new));
+          const float e1 = __builtin_amdgcn_exp2f(fmaf(s[qb][r + 1], scale_log2, -m_new));
+          rsum[qb] += e0 + e1;
+          pn[qb][r >> 3][(r >> 1) & 3] = pack_bf16x2(e0, e1);
+        }
+      }
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      l_run[qb] += rsum[qb];
+      pf[qb][0] = __builtin_bit_cast(bf16x8_t, pn[qb][0]);
+      pf[qb][1] = __builtin_bit_cast(bf16x8_t, pn[qb][1]);
+    }
+  };
+  // every wave's loads have landed, and all are past the tile before last
+  auto turn_over = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  int bp = 2, bc = 0, bn = 1;  // buffers of tiles t - 1, t, t + 1
+  auto turn = [&]() {
+    const int f = bp;
+    bp = bc;
+    bc = bn;
+    bn = f;
+  };
+  turn_over();
+  // the first tile's scores, and the reference: the max over its 64 keys
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const bf16x8_t a0 = read_k(smem, kk), a1 = read_k(smem + 32 * RB, kk);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      sa[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qf[qb][kk], kk == 0 ? zero : sa[qb], 0, 0, 0);
+      sb[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, qf[qb][kk], kk == 0 ? zero : sb[qb], 0, 0, 0);
+    }
+  }
+  mask(0, sa);
+  mask(1, sb);
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+    mu[qb] = fmaxf(fmaxf(row_max(sa[qb]), row_max(sb[qb])) * scale_log2, -1e30f);
+  step(0, bc, 1, bp, 1, sa, sb, std::true_type());
+  if (nt > 2) load_tile(2, bp);
+  step(1, bn, 0, bc, 0, sb, sa, std::false_type());
+  int t = 1;
+  for (; t < ntw; ++t) {
+    turn();
+    step(2 * t, bc, 1, bp, 1, sa, sb, std::false_type());
+    turn_over();
+    if (t + 2 < nt) load_tile(t + 2, bp);
+    step(2 * t + 1, bn, 0, bc, 0, sb, sa, std::false_type());
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const bf16x8_t a = read_v(smem + bc * BUF + 32 * RB, g, ct);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+        o[qb][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[qb][g], o[qb][ct], 0, 0, 0);
+    }
+  for (; t < nt; ++t) {  // the tiles of the block's later queries
+    turn();
+    turn_over();
+    if (t + 2 < nt) load_tile(t + 2, bp);
+  }
+  turn_over();  // every wave is past the tiles before the output staging reuses them
+
+  // o[qb][ct][r] = O^T[channel ct*32 + 8 (r/4) + 4 half + r%4][query wq0 + 32 qb + l32]
+  bf16_t* Os = reinterpret_cast<bf16_t*>(smem) + wave * WQ * OLD;
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const float l = half_swap_sum(l_run[qb]);
+    const float inv_l = l > 0.f ? 1.0f / l : 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int r = 0; r < 16; r += 4) {
+        const uint2 w = {pack_bf16x2(o[qb][ct][r] * inv_l, o[qb][ct][r + 1] * inv_l),
+                         pack_bf16x2(o[qb][ct][r + 2] * inv_l, o[qb][ct][r + 3] * inv_l)};
+        *reinterpret_cast<uint2*>(Os + (32 * qb + l32) * OLD + ct * 32 + 2 * r + 4 * half) = w;
+      }
+    const int qrow = wq0 + 32 * qb + l32;
+    if (lse != nullptr && half == 0 && qrow < n)
+      lse[static_cast<int64_t>(h) * T + lo + qrow] = (mu[qb] + log2f(l)) * kLn2;
+  }
+  // each wave stores its own rows: its LDS writes are in order before its reads
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  for (int c = lane; c < WQ * CPR; c += 64) {
+    const int r = c / CPR, ch = (c % CPR) * 8;
+    const int qr = wq0 + r;
+    if (qr < n)
+      *reinterpret_cast<u32x4*>(O + static_cast<int64_t>(lo + qr) * os + h * HD + ch) =
+          *reinterpret_cast<const u32x4*>(Os + r * OLD + ch);
+  }
+}
+
 // fp32 storage (and bf16 at head dims 16 and 32): every product on
 // v_mfma_f32_32x32x2_f32, fp32 operands and sums. One workgroup of four
 // waves per (32 queries, head, sequence); the waves take the 32-key tiles in
@@ -546,29 +910,25 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
                             const int32_t* cu_dev, void* out, int64_t out_stride, float* lse) {
   if (B == 0 || max_len == 0) return hipSuccess;
   if (dtype == 1 && (hd == 64 || hd == 128)) {
-    const bf16_t* qp = static_cast<const bf16_t*>(q);
-    const bf16_t* kp = static_cast<const bf16_t*>(k);
-    const bf16_t* vp = static_cast<const bf16_t*>(v);
-    bf16_t* op = static_cast<bf16_t*>(out);
     const float sl = scale * kLog2e;
-    // 256-query blocks for the longer sequences (measured: head dim 64, 32
-    // sequences x 12 heads x 512 rows 48.5 -> 45.9 us; head dim 128, 4 x 32
-    // heads x 4096 rows, causal, 1212 -> 1168 us, x 2048 rows 327 -> 309 us,
-    // x 368 rows even)
-    if (hd == 64 && max_len > 128)
-      return launch(K_ATTENTION, attn_mfma_kernel<64, 8>, dim3((max_len + 255) / 256, H, B),
-                    dim3(512), 0, s, qp, kp, vp, row_stride, kv_group, causal, sl, cu_dev, op,
-                    out_stride, lse, T);
-    if (hd == 128 && max_len > 512)
-      return launch(K_ATTENTION, attn_mfma_kernel<128, 8>, dim3((max_len + 255) / 256, H, B),
-                    dim3(512), 0, s, qp, kp, vp, row_stride, kv_group, causal, sl, cu_dev, op,
-                    out_stride, lse, T);
-    const dim3 grid((max_len + 127) / 128, H, B), block(256);
-    if (hd == 64)
-      return launch(K_ATTENTION, attn_mfma_kernel<64, 4>, grid, block, 0, s, qp, kp, vp, row_stride,
-                    kv_group, causal, sl, cu_dev, op, out_stride, lse, T);
-    return launch(K_ATTENTION, attn_mfma_kernel<128, 4>, grid, block, 0, s, qp, kp, vp, row_stride,
-                  kv_group, causal, sl, cu_dev, op, out_stride, lse, T);
+    const int pairs = H * B, p8 = (pairs + 7) / 8;  // pairs per XCD
+    const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
+    const int chunk = alike ? std::min(p8, std::max(1, H / 8)) : p8;
+    auto go = [&](auto kernel, int bq, int threads) {
+      return launch(K_ATTENTION, kernel,
+                    dim3(8u * chunk, (max_len + bq - 1) / bq, (p8 + chunk - 1) / chunk), dim3(threads), 0,
+                    s, static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
+                    static_cast<const bf16_t*>(v), row_stride, kv_group, causal, sl, cu_dev,
+                    static_cast<bf16_t*>(out), out_stride, lse, T, H, pairs);
+    };
+    // lengths from which the wide kernel pays: its comment
+    if (hd == 64) {
+      if (max_len > 256) return go(attn_wide_kernel<64, 2, 4>, 256, 256);
+      if (max_len > 128) return go(attn_mfma_kernel<64, 8>, 256, 512);
+      return go(attn_mfma_kernel<64, 4>, 128, 256);
+    }
+    if (max_len > 384) return go(attn_wide_kernel<128, 1, 8>, 256, 512);
+    return go(attn_mfma_kernel<128, 4>, 128, 256);
   }
   if (dtype == 1)
     return f32_dispatch<bf16_t>(s, q, k, v, row_stride, H, kv_group, hd, causal, scale, B,
