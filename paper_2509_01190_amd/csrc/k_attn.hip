@@ -20,7 +20,6 @@
 // fp32 matrix instruction, four waves sharing 32 queries' keys.
 #include <math.h>
 
-#include <algorithm>
 #include <type_traits>
 
 #include "zsa_internal.h"
@@ -33,34 +32,6 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-
-// Which (sequence, head, query block) a workgroup takes. Workgroup L runs on XCD L % 8, in order of L within it. The (sequence,
-// head) pairs are dealt to the XCDs in turn (with a multiple of 8 heads each
-// XCD takes neighbouring ones, which share key/value heads and so its L2), and
-// an XCD walks `chunk` of its pairs at a time, last query block first. With
-// the query block in the grid's fastest dimension, as these kernels had it,
-// equal sequences put the same query block on the same XCD throughout: under
-// the causal mask one XCD got every longest block and another every shortest
-// (the same kernel: 4 x 4096 causal rows, 32 heads of 128, 918 -> 596 us; 8 x
-// 2048, 32 heads of 64, 286 -> 182; 12 ragged sequences of up to 4095 rows,
-// 1697 -> 852). Measured with attn_wide_kernel, us, one pair at a time / a
-// sequence's / all: causal, 8 x 2048 of 64 211 / 174 / 162, 16 x 1024, 12
-// heads of 64, 55.9 / 55.1 / 43.1; without a mask, where every block of a
-// sequence is as long and the neighbours' K and V are still in L2, 8 x 2048
-// of 64 267 / 263 / 282, 32 x 512, 12 heads, 36.0 / 35.8 / 37.4. So all of
-// them (the longest blocks first, the shortest at the end) under the mask or
-// with sequences of several lengths, and a sequence's otherwise.
-struct Place { int b, h, i; };
-// grid: x = 8 * chunk (XCD fastest), y = query blocks, z = chunks of pairs
-__device__ __forceinline__ bool place(int H, int pairs, Place* at) {
-  const int e = static_cast<int>((blockIdx.z * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7));
-  if (e >= pairs) return false;
-  at->b = e / H;
-  const int x = e - at->b * H;
-  at->h = H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
-  at->i = static_cast<int>(gridDim.y - 1 - blockIdx.y);
-  return true;
-}
 
 // Shorter sequences: four waves per SIMD at head dim 64 (128 registers), two
 // at 128, walking 64-key tiles staged in LDS (K row-major; V transposed at
@@ -113,7 +84,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   __shared__ __align__(16) unsigned char smem[SBYTES];
 
   Place at;
-  if (!place(H, pairs, &at)) return;
+  if (!place(H, pairs, false, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
@@ -418,7 +389,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   typedef __attribute__((address_space(3))) const char lds_char;
 
   Place at;
-  if (!place(H, pairs, &at)) return;
+  if (!place(H, pairs, false, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
@@ -911,15 +882,11 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
   if (B == 0 || max_len == 0) return hipSuccess;
   if (dtype == 1 && (hd == 64 || hd == 128)) {
     const float sl = scale * kLog2e;
-    const int pairs = H * B, p8 = (pairs + 7) / 8;  // pairs per XCD
-    const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
-    const int chunk = alike ? std::min(p8, std::max(1, H / 8)) : p8;
     auto go = [&](auto kernel, int bq, int threads) {
-      return launch(K_ATTENTION, kernel,
-                    dim3(8u * chunk, (max_len + bq - 1) / bq, (p8 + chunk - 1) / chunk), dim3(threads), 0,
-                    s, static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
+      return launch(K_ATTENTION, kernel, place_grid(H, B, max_len, T, causal, bq), dim3(threads), 0, s,
+                    static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
                     static_cast<const bf16_t*>(v), row_stride, kv_group, causal, sl, cu_dev,
-                    static_cast<bf16_t*>(out), out_stride, lse, T, H, pairs);
+                    static_cast<bf16_t*>(out), out_stride, lse, T, H, H * B);
     };
     // lengths from which the wide kernel pays: its comment
     if (hd == 64) {

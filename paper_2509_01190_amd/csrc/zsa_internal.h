@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <utility>
 
 namespace zsa {
@@ -90,6 +91,47 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 keep16(const uint4& v, bool keep) {
   const uint32_t m = keep ? 0xffffffffu : 0u;
   return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
+}
+
+// ---------------------------------------------------------------------------
+// placement of attention workgroups
+// ---------------------------------------------------------------------------
+// Which (sequence, head, block of queries or keys) an attention or score
+// workgroup takes. Workgroup L runs on XCD L % 8, in order of L within it. The (sequence,
+// head) pairs are dealt to the XCDs in turn (with a multiple of 8 heads each
+// XCD takes neighbouring ones, which share key/value heads and so its L2), and
+// an XCD walks `chunk` of its pairs at a time, last query block first. With
+// the query block in the grid's fastest dimension, as these kernels had it,
+// equal sequences put the same query block on the same XCD throughout: under
+// the causal mask one XCD got every longest block and another every shortest
+// (the same kernel: 4 x 4096 causal rows, 32 heads of 128, 918 -> 596 us; 8 x
+// 2048, 32 heads of 64, 286 -> 182; 12 ragged sequences of up to 4095 rows,
+// 1697 -> 852). Measured with attn_wide_kernel, us, one pair at a time / a
+// sequence's / all: causal, 8 x 2048 of 64 211 / 174 / 162, 16 x 1024, 12
+// heads of 64, 55.9 / 55.1 / 43.1; without a mask, where every block of a
+// sequence is as long and the neighbours' K and V are still in L2, 8 x 2048
+// of 64 267 / 263 / 282, 32 x 512, 12 heads, 36.0 / 35.8 / 37.4. So all of
+// them (the longest blocks first, the shortest at the end) under the mask or
+// with sequences of several lengths, and a sequence's otherwise.
+struct Place { int b, h, i; };
+// grid: x = 8 * chunk (XCD fastest), y = blocks, z = chunks of pairs; i counts
+// the blocks from the last (attention: the queries that see most keys) or,
+// with `first`, from the first (scores: the keys that most queries see)
+__device__ __forceinline__ bool place(int H, int pairs, bool first, Place* at) {
+  const int e = static_cast<int>((blockIdx.z * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7));
+  if (e >= pairs) return false;
+  at->b = e / H;
+  const int x = e - at->b * H;
+  at->h = H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
+  at->i = static_cast<int>(first ? blockIdx.y : gridDim.y - 1 - blockIdx.y);
+  return true;
+}
+
+inline dim3 place_grid(int H, int B, int max_len, int T, int causal, int block) {
+  const int p8 = (H * B + 7) / 8;  // pairs per XCD
+  const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
+  const int chunk = alike ? std::min(p8, std::max(1, H / 8)) : p8;
+  return dim3(8u * chunk, (max_len + block - 1) / block, (p8 + chunk - 1) / chunk);
 }
 
 // ---------------------------------------------------------------------------

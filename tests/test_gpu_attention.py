@@ -48,7 +48,8 @@ def check(lens, H, hkv, hd, causal, seed, sharp=1.5, shape_scores=None):
                                         ([512, 512, 512], 8, 2),            # equal lengths, whole tiles
                                         ([575, 576, 577, 0, 1, 33, 64], 3, 1),  # tile edges, ragged, empty
                                         ([449, 449], 12, 12),               # heads not a multiple of 8
-                                        ([801, 40, 769], 16, 4)])           # two heads per XCD, shared keys
+                                        ([801, 40, 769], 16, 4),            # two heads per XCD, shared keys
+                                        ([(97 * i) % 331 for i in range(40)] + [600], 16, 4)])  # the scores' long grid
 def test_attention_tiles_and_order(hd, causal, lens, H, hkv):
     check(lens, H, hkv, hd, causal, seed=hd + H + causal)
 
