@@ -184,6 +184,16 @@ class Seqs:
         cu = np.asarray(cu, dtype=np.int64)
         return cls(np.diff(cu), device)
 
+    @classmethod
+    def _of(cls, host: np.ndarray, dev: torch.Tensor) -> "Seqs":
+        """Offsets already on both sides (int32): a copy to the device from
+        ordinary host memory would wait for everything queued before it."""
+        self = cls.__new__(cls)
+        self.host, self.dev = host, dev
+        self.batch = len(host) - 1
+        self.total = int(host[-1])
+        return self
+
     @property
     def lengths(self) -> List[int]:
         return [int(v) for v in np.diff(self.host)]
@@ -420,7 +430,7 @@ class Stack:
             _stream(dev), ctypes.byref(self.cfg), ctypes.byref(w), _p(hidden), _p(pos),
             seqs.batch, _hp32(seqs.host), _p(seqs.dev), kr_p, _p(x_out), _p(pos_out),
             _hp32(cu_out), _p(cu_out_dev), _p(scores), _p(kept), _p(ws), wsz))
-        out_seqs = Seqs.from_cu(cu_out, dev)
+        out_seqs = Seqs._of(cu_out, cu_out_dev)
         res = {"x": x_out[:t_out], "pos": pos_out[:t_out], "seqs": out_seqs,
                "cu_dev": cu_out_dev}
         if want_scores:

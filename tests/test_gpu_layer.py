@@ -112,3 +112,26 @@ def test_layer_keep_rate_one_equals_unpruned_bitwise():
     assert torch.equal(a["x"], b["x"])
     assert torch.equal(a["pos"], b["pos"])
     assert np.array_equal(a["kept_rows"].cpu().numpy(), np.arange(sum(lens)))
+
+
+@pytest.mark.parametrize("mark", [False, True])
+def test_layers_chained_without_waiting(mark):
+    """Blocks called one after another on the offsets each returns (which stay
+    on the device; nothing waits in between, on a stream of their own) give
+    the stack's result, pruned or marked."""
+    lens, rates = [5, 64, 0, 257, 1], [0.5, 0.3, 0.9, 1.0, 0.2]
+    p, one, xd, wd, _ = _setup(W.ENCODER, "bf16", 256, 4, 512, lens, seed=33)
+    cfg = zsa.make_cfg(W.ENCODER, 256, 4, 512, False, zsa.BF16, mark_only=mark)
+    stack = zsa.Stack(cfg, [wd, wd])
+    seqs = zsa.Seqs(lens, dev())
+    posd = torch.from_numpy(W.positions(lens)).to(dev())
+    ref = stack.forward(xd, posd, seqs, [1], rates)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        a = stack.layer_forward(0, xd, posd, seqs, keep_rate=rates)
+        b = stack.layer_forward(1, a["x"], a["pos"], a["seqs"])
+    torch.cuda.synchronize()
+    assert a["seqs"].lengths == (lens if mark else [int(c) for c in zsa.keep_schedule(lens, rates, 5, 1)[0]])
+    assert np.array_equal(a["seqs"].dev.cpu().numpy(), a["seqs"].host)
+    assert torch.equal(b["x"], ref["x"]) and torch.equal(b["pos"], ref["pos"])
