@@ -7,7 +7,9 @@
 // bf16 kernels, fp32 accumulation, chosen by shape in launch_gemm:
 //  * gemm_bf16_dma_kernel: 128x128 tiles on 4 waves or 256x256 on 8, K
 //    slices loaded straight into swizzled LDS stages; split K for short
-//    grids, the slices summed in slice order by splitk_reduce_kernel;
+//    grids with long K, the slices summed in slice order by
+//    splitk_reduce_kernel; for short grids also 64x64, 128x64 and 128x128
+//    tiles with three or four slices in flight (short_grid);
 //  * gemm_bf16_persist_kernel: 128x128 tiles, two workgroups per CU walking
 //    their XCD's range of tiles, the epilogue from registers;
 //  * gemm_bf16_w4p_kernel: 256x256 or 256x192 tiles on four waves (one per
@@ -18,8 +20,8 @@
 //  * gemm_bf16_w4_kernel: its slice loop with one tile per workgroup (a
 //    tuning baseline, ZSA_GEMM_TILE);
 //  * gemm_skinny_kernel: products of at most 16 rows, and of up to 1024
-//    rows whose 128x128 tiles would number under 64 (generation and short
-//    pruned layers): no shared tiles, operands loaded in whole cache lines
+//    rows whose 128x128 tiles would number under 64 and 64x64 ones under 150
+//    (generation and short pruned layers): no shared tiles, operands loaded in whole cache lines
 //    and passed through a per-wave LDS buffer into
 //    v_mfma_f32_16x16x32_bf16 fragments;
 //  * gemm_bf16_mfma_kernel: the register-staged 128x128 original, kept as a
@@ -230,7 +232,7 @@ template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_mfma_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, int M, int N, int K,
     EpiParams ep) {
-  static_assert(BM % 128 == 0 && (BN == 128 || BN == 256), "tile shape");
+  static_assert(BM % 64 == 0 && (BN == 64 || BN == 128 || BN == 256), "tile shape");
   constexpr int NT = WM * WN * 64;
   constexpr int kTileLd = BN + 4;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -610,7 +612,7 @@ __attribute__((amdgpu_waves_per_eu(dma_waves_per_simd<BM, BN, WM, WN, KB, NS, ER
 gemm_bf16_dma_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, int M, int N, int K,
     EpiParams ep, int kchunk, float* __restrict__ part) {
-  static_assert(BM % 128 == 0 && (BN == 128 || BN == 256), "tile shape");
+  static_assert(BM % 64 == 0 && (BN == 64 || BN == 128 || BN == 256), "tile shape");
   static_assert((KB == 32 || KB == 64) && NS >= 2 && ER % 32 == 0 && BM % ER == 0, "pipeline");
   using SL = Slice<KB>;
   constexpr int NW = WM * WN;
@@ -2563,7 +2565,10 @@ bool w4p_ok(int M, int N, int K, const EpiParams& ep, int bn = 256) {
 // 16384 x 2304 x 768 (three whole rounds: 57.9 us) and 16384 x 768 x K (one:
 // 25.8 and 65.2 us for K = 768 and 3072), 256 for 16384 x 3072 x 768 (85.9
 // us; persistent 128x128 95.2). For K > 3072 (the 4096-wide decoder) a
-// width pays from one whole round of tiles on.
+// width pays from 0.68 of a round on, however the last one is filled (3276 x
+// 4096 x 14336, 256 wide, 208 tiles: 320 us against 451 persistent 128x128;
+// x 4096 x 4096 99.6 against 135; 6000 x 4096 x 14336, 1.5 rounds: 639
+// against 770).
 int w4p_width(int M, int N, int K, const EpiParams& ep) {
   const long cus = device_cus();
   int best = 0;
@@ -2573,7 +2578,7 @@ int w4p_width(int M, int N, int K, const EpiParams& ep) {
     const long tiles = static_cast<long>((M + 255) / 256) * (N / bn);
     const long rem = tiles % cus;
     bool pays;
-    if (K > 3072) pays = tiles >= cus;
+    if (K > 3072) pays = 100 * tiles >= 68 * cus;
     else if (tiles >= cus) pays = rem == 0 || (ep.epi == EPI_GELU ? 4 * rem >= 3 * cus : 2 * rem >= cus);
     else pays = 100 * tiles >= 68 * cus;
     if (!pays) continue;
@@ -2694,6 +2699,7 @@ int gemm_tile_override() {
 
 }  // namespace
 
+// (Up to K = 4096 launch_gemm takes short_grid's tiles instead.)
 // Split K when the 128 x 128 output tiles fill under 0.7 of the CUs once
 // and K is long (at least kMinSplitK): S slices of at least
 // kMinSplitSteps K steps, S x tiles <= 512 workgroups (one round, no tail).
@@ -2755,11 +2761,56 @@ bool skinny_ok(int dtype, int M, int N, int K, const EpiParams& ep) {
 //   1024 x 768 x 768               /   8.5     10.3
 //   1024 x 768 x 3072              /  20.2     22.8
 // so it takes M <= 16, and up to 1024 rows while the 128 x 128 output
-// tiles are fewer than 64 (past 512 rows: 768-column outputs).
+// tiles are fewer than 64 (past 512 rows: 768-column outputs) and the 64 x
+// 64 ones fewer than 150, from where those (short_grid) are faster: few-row /
+// 64 x 64, us, 640 x 768 x 3072 (120 tiles) 15.0 / 16.6, 160 x 3072 x 768
+// with GELU (144) 7.1 / 7.5, 800 x 768 x 3072 (156) 19.7 / 16.3, 800 x 768 x
+// 768 9.7 / 7.4, 300 x 2304 x 768 (180) 9.1 / 7.1.
 bool skinny_pays(int M, int N, int K) {
   (void)K;
   const long tiles128 = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
-  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64);
+  const long tiles64 = static_cast<long>((M + 63) / 64) * ((N + 63) / 64);
+  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64 && tiles64 < 150);
+}
+
+// Tile shape of a product whose 128 x 128 tiles are at most one per CU (none
+// where the general choice below is better). A workgroup alone on its CU
+// waits for every K slice with two stages (0.72 us a slice of 128 x 128 tiles
+// against 0.27 of matrix work): here three or four are in flight, and the
+// tiles are the smallest that still number at most two per CU. Measured, us
+// (before: few-row, split K or persistent 128 x 128 / 64 x 64 on 4 waves, 3
+// stages / 128 x 64 on 8 waves, 3 stages / 128 x 128 on 8 waves, 4 stages):
+//   800 x 768 x 768           9.7 /  7.4 /  8.5 / 12.3   (156 tiles of 64 x 64)
+//   1200 x 768 x 768         11.7 /  7.5 /  8.8 / 12.4   (228)
+//   2500 x 768 x 768         12.4 /  9.8 / 10.0 / 13.7   (480)
+//   4000 x 768 x 768         12.9 / 13.4 / 13.8 / 14.1   (756: left)
+//   512 x 3072 x 768 (GELU)  12.5 /  9.5 /  9.8 / 13.9   (384)
+//   1000 x 2304 x 768        11.4 / 11.7 / 12.5 / 12.6   (576: left)
+//   1030 x 768 x 3072        24.9 / 17.5 / 21.2 / 31.8   (204)
+//   2048 x 768 x 3072        29.1 / 23.1 / 22.3 / 32.0   (384)
+//   3500 x 768 x 3072        36.4 / 33.6 / 34.0 / 33.4   (660)
+//   4500 x 768 x 3072        36.8 / 42.9 / 35.9 / 34.3   (852)
+//   500 x 2048 x 2048        21.9 / 12.1 / 15.0 / 21.5   (256)
+//   600 x 3072 x 2048        22.2 / 16.2 / 15.4 / 21.9   (480)
+//   60 x 16384 x 2048 (SwiGLU) 24.2 / 14.1 / 15.1 / 21.0 (256)
+//   250 x 16384 x 2048       26.5 / 29.7 / 26.6 / 24.8   (1024)
+//   500 x 2048 x 8192        35.2 / 34.5 / 44.5 / 68.7   (split K: left)
+//   1000 x 2048 x 8192       52.0 / 51.9 / 49.6 / 71.3   (left)
+//   1300 x 2048 x 8192       76.5 / 74.6 / 77.7 / 72.8   (176 of 128 x 128)
+//   900 x 4096 x 14336       144 / 176 / 148 / 133       (256 of 128 x 128)
+// `split`: the caller's workspace lets the product split K, which keeps
+// longer K on under 0.7 of a 128 x 128 tile per CU.
+enum ShortGrid { kNoShort, kShort64, kShort128x64, kShort128 };
+ShortGrid short_grid(int M, int N, int K, const EpiParams& ep, bool split) {
+  if (K % kBK != 0) return kNoShort;
+  auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long cus = device_cus(), t64 = tiles(64, 64);
+  if (tiles(128, 128) > cus || (split && K > 4096)) return kNoShort;
+  // a rotary head must lie within a tile's columns
+  const bool narrow = ep.epi != EPI_ROPE || ep.head_dim <= 64;
+  if (narrow && t64 <= 2 * cus)
+    return K >= 2048 && t64 > cus && tiles(128, 64) <= cus ? kShort128x64 : kShort64;
+  return K >= 2048 ? kShort128 : kNoShort;
 }
 
 // The folded pre-norm: every workgroup normalises the x fragments it
@@ -2919,6 +2970,14 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* x, int M, int K, co
   if (dtype == 1 && K % kBK == 0) {
     int S = 1, kchunk = K;
     splitk_plan(M, N, K, &S, &kchunk);
+    if (gemm_tile_override() == 0) {
+      switch (short_grid(M, N, K, ep, S > 1 && ws != nullptr && ws_bytes >= splitk_bytes(S, M, N))) {
+        case kShort64: return launch_dma<64, 64, 2, 2, 64, 3, 64>(s, x, M, K, w, N, ep);
+        case kShort128x64: return launch_dma<128, 64, 4, 2, 64, 3, 64>(s, x, M, K, w, N, ep);
+        case kShort128: return launch_dma<128, 128, 4, 2, 64, 4, 64>(s, x, M, K, w, N, ep);
+        case kNoShort: break;
+      }
+    }
     // (K <= 2048: the persistent 128x128 kernel beats the split where it
     // takes the epilogue; see splitk_plan)
     if (S > 1 && ws != nullptr && ws_bytes >= splitk_bytes(S, M, N) &&
