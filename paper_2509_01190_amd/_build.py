@@ -30,6 +30,7 @@ SOURCES = [
     "k_gather.hip",
     "k_decode.hip",
     "k_backward.hip",
+    "k_wgrad.hip",
 ]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -59,6 +60,7 @@ EXTRA_FLAGS = {
     "k_score.hip": VGPR_MFMA,
     "k_backward.hip": VGPR_MFMA,
     "k_decode.hip": VGPR_MFMA,
+    "k_wgrad.hip": VGPR_MFMA,
 }
 
 

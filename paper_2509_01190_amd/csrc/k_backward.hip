@@ -1,11 +1,12 @@
 // Backward pass through the pruned block (the fine-tuning step of Eq. 3
 // trains through the pruned forward; the kept rows are constants).
 //
-// Row-wise pieces: transposes (so both products of a projection's backward
-// run on the forward's NT GEMM), column sums (bias / gain gradients, in a
-// fixed order), LayerNorm / RMSNorm backward, GELU / SwiGLU backward, the
-// scatter that undoes compaction (dropped rows get zero gradient), the
-// per-row dot D_i = dO_i . O_i, and the inverse rotary rotation.
+// Row-wise pieces: transposes of the weights (so a projection's input
+// gradient runs on the forward's NT GEMM; its weight gradient is k_wgrad.hip),
+// LayerNorm / RMSNorm backward with the gain and shift gradients, GELU /
+// SwiGLU backward with the recomputed activation, the scatter that undoes
+// compaction (dropped rows get zero gradient), the per-row dot
+// D_i = dO_i . O_i, and the inverse rotary rotation.
 //
 // Attention backward (bf16, head_dim 64 / 128, MFMA), with P recomputed
 // from the forward's log-sum-exp:
@@ -57,212 +58,218 @@ __device__ __forceinline__ void store8<float>(float* p, const float* v) {
 }
 
 // ---------------------------------------------------------------------------
-// transpose: out[c][r] = in[r][c] for r < R, 0 for R <= r < Rpad
+// out = in^T of the layer's weights, one launch for all of them: four
+// launches of 4 to 5 us of which the launch itself is most (2.4 M weights of
+// a 768-wide block)
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, int R, int C,
-                                                        int64_t ldi, T* __restrict__ out,
-                                                        int Rpad) {
-  __shared__ T tile[32][33];
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows per pass
-  for (int k = ty; k < 32; k += 8) {
-    const int r = r0 + k, c = c0 + tx;
-    tile[k][tx] = (r < R && c < C) ? in[static_cast<int64_t>(r) * ldi + c] : T(0.f);
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int c = c0 + k, r = r0 + tx;
-    if (c < C && r < Rpad) out[static_cast<int64_t>(c) * Rpad + r] = tile[tx][k];
-  }
-}
+struct TransposeArgs {
+  TransposeArg m[4];
+  int first[5];  // first tile of each matrix
+};
 
-// bf16, 64 x 64 tiles with 16-byte loads and stores (C, R multiples of 8 for
-// the vector paths; edges fall back to element accesses)
-__global__ __launch_bounds__(256) void transpose64_kernel(const bf16_t* __restrict__ in, int R,
-                                                          int C, int64_t ldi,
-                                                          bf16_t* __restrict__ out, int Rpad) {
+// bf16, 64 x 64 tiles with 16-byte loads and stores (r and c multiples of 8)
+__global__ __launch_bounds__(256) void transpose64_kernel(const TransposeArgs p) {
   __shared__ bf16_t tile[64][64 + 2];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+  int i = 0;
+  while (static_cast<int>(blockIdx.x) >= p.first[i + 1]) ++i;
+  const bf16_t* __restrict__ in = static_cast<const bf16_t*>(p.m[i].in);
+  bf16_t* __restrict__ out = static_cast<bf16_t*>(p.m[i].out);
+  const int R = p.m[i].r, C = p.m[i].c, tc = (C + 63) / 64;
+  const int id = static_cast<int>(blockIdx.x) - p.first[i];
+  const int r0 = id / tc * 64, c0 = id % tc * 64;
   const int t = threadIdx.x;
   for (int k = t; k < 64 * 8; k += 256) {
     const int r = k / 8, ch = (k % 8) * 8;
     const int gr = r0 + r, gc = c0 + ch;
-    if (gr < R && gc + 8 <= C) {
-      const uint4 v = *reinterpret_cast<const uint4*>(in + static_cast<int64_t>(gr) * ldi + gc);
+    if (gr < R && gc < C) {
+      const uint4 v = *reinterpret_cast<const uint4*>(in + static_cast<int64_t>(gr) * C + gc);
       const bf16_t* e = reinterpret_cast<const bf16_t*>(&v);
 #pragma unroll
       for (int j = 0; j < 8; ++j) tile[r][ch + j] = e[j];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        tile[r][ch + j] = (gr < R && gc + j < C) ? in[static_cast<int64_t>(gr) * ldi + gc + j]
-                                                 : bf16_t(0.f);
     }
   }
   __syncthreads();
   for (int k = t; k < 64 * 8; k += 256) {
     const int c = k / 8, rh = (k % 8) * 8;   // output row c0 + c, columns r0 + rh ..
     const int gc = c0 + c, gr = r0 + rh;
-    if (gc >= C) continue;
-    if (gr + 8 <= Rpad) {
-      uint4 v;
-      bf16_t* e = reinterpret_cast<bf16_t*>(&v);
+    if (gc >= C || gr >= R) continue;
+    uint4 v;
+    bf16_t* e = reinterpret_cast<bf16_t*>(&v);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) e[j] = tile[rh + j][c];
-      *reinterpret_cast<uint4*>(out + static_cast<int64_t>(gc) * Rpad + gr) = v;
-    } else {
-      for (int j = 0; j < 8 && gr + j < Rpad; ++j)
-        out[static_cast<int64_t>(gc) * Rpad + gr + j] = tile[rh + j][c];
-    }
+    for (int j = 0; j < 8; ++j) e[j] = tile[rh + j][c];
+    *reinterpret_cast<uint4*>(out + static_cast<int64_t>(gc) * R + gr) = v;
   }
-}
-
-// ---------------------------------------------------------------------------
-// column sums in a fixed order: stage 1 sums chunks of kColRows rows (each
-// thread 8 consecutive columns with 16-byte loads, 8 row lanes per block
-// added in lane order), stage 2 adds the chunks in chunk order
-// ---------------------------------------------------------------------------
-constexpr int kColRows = 64;   // rows per stage-1 chunk
-constexpr int kColLanes = 8;   // row lanes per block
-
-// sum over rows of a[r][c] (or of a[r][c] * xhat[r][c] when x is given, with
-// xhat = (x - mean_r) * rstd_r from stats [R][2]); C a multiple of 8
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_stage1(const T* __restrict__ a, int64_t lda,
-                                                     const T* __restrict__ x, int64_t ldx,
-                                                     const float* __restrict__ stats, int R,
-                                                     int C, float* __restrict__ part) {
-  __shared__ float red[kColLanes][32 * 8 + 4];
-  const int cg = threadIdx.x & 31, lane_r = threadIdx.x >> 5;
-  const int c0 = (blockIdx.x * 32 + cg) * 8;
-  const int r0 = blockIdx.y * kColRows;
-  float s[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) s[e] = 0.f;
-  if (c0 < C) {
-    const int r1 = min(R, r0 + kColRows);
-    for (int r = r0 + lane_r; r < r1; r += kColLanes) {
-      float v[8];
-      load8<T>(a + static_cast<int64_t>(r) * lda + c0, v);
-      if (x != nullptr) {
-        float xv[8];
-        load8<T>(x + static_cast<int64_t>(r) * ldx + c0, xv);
-        const float mu = stats[2 * r], rs = stats[2 * r + 1];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] *= (xv[e] - mu) * rs;
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s[e] += v[e];
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[lane_r][cg * 8 + e] = s[e];
-  __syncthreads();
-  if (lane_r == 0 && c0 < C) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = red[0][cg * 8 + e];
-#pragma unroll
-      for (int k = 1; k < kColLanes; ++k) v += red[k][cg * 8 + e];
-      part[static_cast<int64_t>(blockIdx.y) * C + c0 + e] = v;
-    }
-  }
-}
-
-__global__ void zero_f32_kernel(float* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.f;
 }
 
 // ---------------------------------------------------------------------------
 // norm backward: one wave per row.
 //   LN:  dx = rstd (g dh - mean(g dh) - xhat mean(g dh xhat))
 //   RMS: dx = rstd (g dh - xhat mean(g dh xhat))
-// out = res + dx (res may alias out, or be NULL); stats[r] = (mean, rstd)
-// (mean 0 for RMS) for the gain / shift gradients.
+// out = res + dx (res may alias out, or be NULL). The gain and shift
+// gradients, the column sums of dh xhat and dh, are summed on the way: each
+// wave over its rows, a workgroup's waves in order into a row of `part`
+// [blocks][(1 or 2) d], and col_total_kernel over the blocks. (As passes of
+// their own they read dh twice and x once more: 40 us of five launches for
+// 8192 rows of 768 where this takes two.)
 // ---------------------------------------------------------------------------
-template <typename T, int RMS, int NC>
-__global__ __launch_bounds__(256) void norm_bwd_kernel(const T* __restrict__ x,
-                                                       const T* __restrict__ g,
-                                                       const T* __restrict__ dh, const T* res,
-                                                       T* out, int R, int d, float eps,
-                                                       float* __restrict__ stats) {
-  // one wave per row; lane owns the 8-column chunks lane, lane + 64, ...
-  // (NC of them, d <= NC * 512), held in registers across the passes
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= R) return;
-  const int64_t base = static_cast<int64_t>(row) * d;
-  float xv[NC][8], gd[NC][8];
-  float s = 0.f;
+constexpr int kNormBwdBlocks = 512;
+
+template <int RMS, int NC>
+__global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict__ x,
+                                                       const bf16_t* __restrict__ g,
+                                                       const bf16_t* __restrict__ dh, const bf16_t* res,
+                                                       bf16_t* out, int R, int d, float eps,
+                                                       float* __restrict__ part) {
+  // lane owns the 8-column chunks lane, lane + 64, ... (NC of them, d <= NC *
+  // 512); rows stay packed in registers across the passes, chunks past d zero
+  constexpr int NS = RMS ? 1 : 2;
+  __shared__ float red[4][NS][512];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const u32x4 none = {0u, 0u, 0u, 0u};
+  auto unpack = [](const u32x4& v, int e) {
+    const uint32_t w = v[e >> 1];
+    return __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
+  };
+  u32x4 gv[NC];
+  float gs[NC][8], bs[NC][8];
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     const int c = (k * 64 + lane) * 8;
-    if (c < d) {
-      float gv[8];
-      load8<T>(x + base + c, xv[k]);
-      load8<T>(g + c, gv);
-      load8<T>(dh + base + c, gd[k]);
+    gv[k] = c < d ? *reinterpret_cast<const u32x4*>(g + c) : none;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        gd[k][e] *= gv[e];
-        s += xv[k][e];
+    for (int e = 0; e < 8; ++e) gs[k][e] = bs[k][e] = 0.f;
+  }
+  // the next row's loads are in flight while this one is worked on
+  constexpr bool ahead = NC <= 8;
+  constexpr int NN = ahead ? NC : 1;
+  u32x4 xn[NN], dn[NN];
+  const int step = 4 * static_cast<int>(gridDim.x);
+  auto fetch = [&](int row, u32x4* xr, u32x4* dr) {
+    const int64_t base = static_cast<int64_t>(row) * d;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const int c = (k * 64 + lane) * 8;
+      xr[k] = c < d && row < R ? *reinterpret_cast<const u32x4*>(x + base + c) : none;
+      dr[k] = c < d && row < R ? *reinterpret_cast<const u32x4*>(dh + base + c) : none;
+    }
+  };
+  int row = static_cast<int>(blockIdx.x) * 4 + wave;
+  if constexpr (ahead) fetch(row, xn, dn);
+  for (; row < R; row += step) {
+    const int64_t base = static_cast<int64_t>(row) * d;
+    u32x4 xv[NC], dv[NC];
+    float s = 0.f;
+    if constexpr (ahead) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        xv[k] = xn[k];
+        dv[k] = dn[k];
       }
+      fetch(row < R - step ? row + step : R, xn, dn);
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xv[k][e] = gd[k][e] = 0.f;
+      fetch(row, xv, dv);
     }
-  }
-  float mean = 0.f;
-  if (!RMS) {
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    mean = s / d;
-  }
-  float ss = 0.f;
+    float mean = 0.f;
+    if (!RMS) {
 #pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    if ((k * 64 + lane) * 8 < d) {
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += unpack(xv[k], e);
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      mean = s / d;
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      if ((k * 64 + lane) * 8 < d) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = unpack(xv[k], e) - mean;
+          ss += v * v;
+        }
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    const float rstd = 1.0f / sqrtf(ss / d + eps);
+    float s1 = 0.f, s2 = 0.f;  // sum(g dh), sum(g dh xhat)
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float v = xv[k][e] - mean;
-        ss += v * v;
+        const float h = unpack(dv[k], e), gd = h * unpack(gv[k], e), xh = (unpack(xv[k], e) - mean) * rstd;
+        s1 += gd;
+        s2 += gd * xh;  // zero on chunks past d
+        gs[k][e] += h * xh;
+        if (!RMS) bs[k][e] += h;
+      }
+    for (int o = 32; o > 0; o >>= 1) {
+      s1 += __shfl_xor(s1, o, 64);
+      s2 += __shfl_xor(s2, o, 64);
+    }
+    const float m1 = RMS ? 0.f : s1 / d, m2 = s2 / d;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const int c = (k * 64 + lane) * 8;
+      if (c < d) {
+        float o[8], rv[8];
+        if (res != nullptr) load8<bf16_t>(res + base + c, rv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float xh = (unpack(xv[k], e) - mean) * rstd;
+          o[e] = rstd * (unpack(dv[k], e) * unpack(gv[k], e) - m1 - xh * m2) + (res != nullptr ? rv[e] : 0.f);
+        }
+        store8<bf16_t>(out + base + c, o);
       }
     }
   }
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  const float rstd = 1.0f / sqrtf(ss / d + eps);
-  float s1 = 0.f, s2 = 0.f;  // sum(g dh), sum(g dh xhat)
+  float* prow = part + static_cast<int64_t>(blockIdx.x) * NS * d;
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
+    if (k > 0) __syncthreads();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      s1 += gd[k][e];
-      s2 += gd[k][e] * (xv[k][e] - mean) * rstd;  // zero on chunks past d
+      red[wave][0][lane * 8 + e] = gs[k][e];
+      if (!RMS) red[wave][NS - 1][lane * 8 + e] = bs[k][e];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < NS * 512; i += 256) {
+      const int which = i >> 9, j = i & 511, c = k * 512 + j;
+      if (c < d) prow[which * d + c] = red[0][which][j] + red[1][which][j] + red[2][which][j] + red[3][which][j];
     }
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    s1 += __shfl_xor(s1, o, 64);
-    s2 += __shfl_xor(s2, o, 64);
-  }
-  const float m1 = RMS ? 0.f : s1 / d, m2 = s2 / d;
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = (k * 64 + lane) * 8;
-    if (c < d) {
-      float o[8], rv[8];
-      if (res != nullptr) load8<T>(res + base + c, rv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float xh = (xv[k][e] - mean) * rstd;
-        o[e] = rstd * (gd[k][e] - m1 - xh * m2) + (res != nullptr ? rv[e] : 0.f);
-      }
-      store8<T>(out + base + c, o);
+}
+
+// out0[c] (c < d) and out1[c - d] = the sum of column c of part [rows][cols]:
+// 32 columns and 32 row lanes a workgroup, added in a fixed order
+__global__ __launch_bounds__(256) void col_total_kernel(const float* __restrict__ part, int rows, int cols,
+                                                        int d, float* __restrict__ out0,
+                                                        float* __restrict__ out1) {
+  __shared__ float red[32][33];
+  const int q = threadIdx.x & 7, rl = threadIdx.x >> 3;
+  const int c0 = blockIdx.x * 32, c = c0 + 4 * q;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c < cols) {  // a multiple of 8
+#pragma unroll 8
+    for (int r = rl; r < rows; r += 32) {
+      const float4 t = *reinterpret_cast<const float4*>(part + static_cast<int64_t>(r) * cols + c);
+      v.x += t.x;
+      v.y += t.y;
+      v.z += t.z;
+      v.w += t.w;
     }
   }
-  if (lane == 0) {
-    stats[2 * row] = mean;
-    stats[2 * row + 1] = rstd;
+  red[rl][4 * q] = v.x;
+  red[rl][4 * q + 1] = v.y;
+  red[rl][4 * q + 2] = v.z;
+  red[rl][4 * q + 3] = v.w;
+  __syncthreads();
+  const int oc = c0 + static_cast<int>(threadIdx.x);
+  if (threadIdx.x < 32 && oc < cols) {
+    float s = red[0][threadIdx.x];
+#pragma unroll
+    for (int k = 1; k < 32; ++k) s += red[k][threadIdx.x];
+    if (oc < d) out0[oc] = s;
+    else if (out1 != nullptr) out1[oc - d] = s;
   }
 }
 
@@ -271,100 +278,82 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const T* __restrict__ x,
 // interleaved columns (2f gate, 2f+1 up): dgate = dF up silu'(gate),
 // dup = dF silu(gate), silu'(z) = s (1 + z (1 - s)), s = sigmoid(z).
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void act_bwd_kernel(const T* __restrict__ dF,
-                                                      const T* __restrict__ u, T* __restrict__ du,
-                                                      int64_t rows, int F, int swiglu) {
+// The activation f itself (recomputed for the down projection's weight
+// gradient) comes from the same read of u: a pass of its own took 11.4 us for
+// 4096 rows of 3072 beside this one's 15.2.
+__global__ __launch_bounds__(256) void act_bwd_kernel(const bf16_t* __restrict__ dF,
+                                                      const bf16_t* __restrict__ u, bf16_t* __restrict__ du,
+                                                      bf16_t* __restrict__ fo, int64_t rows, int F,
+                                                      int swiglu) {
   // 8 consecutive outputs f..f+7 of one row per thread
   const int64_t i = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 8;
   if (i >= rows * F) return;
   const int64_t r = i / F;
   const int f = static_cast<int>(i - r * F);
-  float g[8];
-  load8<T>(dF + i, g);
+  float g[8], a[8];
+  load8<bf16_t>(dF + i, g);
   if (swiglu) {
     float u0[8], u1[8], o0[8], o1[8];
-    load8<T>(u + r * 2 * F + 2 * f, u0);       // gate, up of outputs f .. f+3
-    load8<T>(u + r * 2 * F + 2 * f + 8, u1);   // ... of f+4 .. f+7
+    load8<bf16_t>(u + r * 2 * F + 2 * f, u0);       // gate, up of outputs f .. f+3
+    load8<bf16_t>(u + r * 2 * F + 2 * f + 8, u1);   // ... of f+4 .. f+7
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float z0 = u0[2 * e], up0 = u0[2 * e + 1], s0 = 1.0f / (1.0f + expf(-z0));
-      const float z1 = u1[2 * e], up1 = u1[2 * e + 1], s1 = 1.0f / (1.0f + expf(-z1));
+      const float z0 = u0[2 * e], up0 = u0[2 * e + 1], e0 = 1.0f + expf(-z0), s0 = 1.0f / e0;
+      const float z1 = u1[2 * e], up1 = u1[2 * e + 1], e1 = 1.0f + expf(-z1), s1 = 1.0f / e1;
       o0[2 * e] = g[e] * up0 * s0 * (1.0f + z0 * (1.0f - s0));
       o0[2 * e + 1] = g[e] * z0 * s0;
       o1[2 * e] = g[4 + e] * up1 * s1 * (1.0f + z1 * (1.0f - s1));
       o1[2 * e + 1] = g[4 + e] * z1 * s1;
+      a[e] = z0 / e0 * up0;
+      a[4 + e] = z1 / e1 * up1;
     }
-    store8<T>(du + r * 2 * F + 2 * f, o0);
-    store8<T>(du + r * 2 * F + 2 * f + 8, o1);
+    store8<bf16_t>(du + r * 2 * F + 2 * f, o0);
+    store8<bf16_t>(du + r * 2 * F + 2 * f + 8, o1);
   } else {
     float z[8], o[8];
-    load8<T>(u + i, z);
+    load8<bf16_t>(u + i, z);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float cdf = 0.5f * (1.0f + erff(z[e] * 0.70710678118654752f));
       const float pdf = 0.39894228040143268f * __expf(-0.5f * z[e] * z[e]);
       o[e] = g[e] * (cdf + z[e] * pdf);
+      a[e] = z[e] * cdf;
     }
-    store8<T>(du + i, o);
+    store8<bf16_t>(du + i, o);
   }
-}
-
-// the activation itself from the pre-activation u (GELU, or SwiGLU on
-// interleaved gate / up columns): the backward's recomputed forward
-template <typename T>
-__global__ __launch_bounds__(256) void act_fwd_kernel(const T* __restrict__ u, T* __restrict__ f,
-                                                      int64_t rows, int F, int swiglu) {
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 8;
-  if (i >= rows * F) return;
-  const int64_t r = i / F;
-  const int c = static_cast<int>(i - r * F);
-  float o[8];
-  if (swiglu) {
-    float u0[8], u1[8];
-    load8<T>(u + r * 2 * F + 2 * c, u0);
-    load8<T>(u + r * 2 * F + 2 * c + 8, u1);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[e] = u0[2 * e] / (1.0f + expf(-u0[2 * e])) * u0[2 * e + 1];
-      o[4 + e] = u1[2 * e] / (1.0f + expf(-u1[2 * e])) * u1[2 * e + 1];
-    }
-  } else {
-    float z[8];
-    load8<T>(u + i, z);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = 0.5f * z[e] * (1.0f + erff(z[e] * 0.70710678118654752f));
-  }
-  store8<T>(f + i, o);
+  store8<bf16_t>(fo + i, a);
 }
 
 // ---------------------------------------------------------------------------
-// undo compaction: dst[r] = src[inv[r]] for kept rows, 0 for dropped ones
+// undo compaction of two arrays: dst[kept[i]] = src[i], zeros elsewhere. kept
+// ascends, so wave i clears the rows between kept[i - 1] and kept[i] and
+// copies row i; the last one (i = t_out) clears the rest. An inverse index
+// (filled, then written, then read by one scatter per array) took six
+// launches, 21 us for 8192 rows of 768; this one 17.
 // ---------------------------------------------------------------------------
-__global__ void inverse_index_kernel(const int32_t* __restrict__ kept, int t_out, int t_in,
-                                     int32_t* __restrict__ inv) {
-  // one pass per row of the input: rows not found stay -1 (filled first)
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < t_out) {
-    const int r = kept[i];
-    if (r >= 0 && r < t_in) inv[r] = i;
+__global__ __launch_bounds__(256) void scatter_rows_kernel(const u32x4* __restrict__ src0, u32x4* __restrict__ dst0,
+                                                           const u32x4* __restrict__ src1, u32x4* __restrict__ dst1,
+                                                           const int32_t* __restrict__ kept, int t_out, int t_in,
+                                                           int cpr) {
+  const int lane = threadIdx.x & 63;
+  const int i = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
+  if (i > t_out) return;
+  const int prev = i == 0 ? -1 : kept[i - 1], here = i == t_out ? t_in : kept[i];
+  const int64_t from = static_cast<int64_t>(max(prev, -1) + 1) * cpr, to = static_cast<int64_t>(min(here, t_in)) * cpr;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  if (here >= 0 && here < t_in) {
+    const int64_t at = static_cast<int64_t>(i) * cpr;
+#pragma unroll 2
+    for (int c = lane; c < cpr; c += 64) {
+      const u32x4 v0 = src0[at + c], v1 = src1[at + c];
+      dst0[to + c] = v0;
+      dst1[to + c] = v1;
+    }
   }
-}
-
-__global__ void fill_i32_kernel(int32_t* __restrict__ p, int n, int v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const uint4* __restrict__ src,
-                                                           const int32_t* __restrict__ inv,
-                                                           int t_in, int cpr,
-                                                           uint4* __restrict__ dst) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(t_in) * cpr) return;
-  const int r = static_cast<int>(i / cpr), c = static_cast<int>(i % cpr);
-  const int s = inv[r];
-  dst[i] = s >= 0 ? src[static_cast<int64_t>(s) * cpr + c] : make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t c = from + lane; c < to; c += 64) {
+    dst0[c] = zero;
+    dst1[c] = zero;
+  }
 }
 
 // D[h][r] = sum_c dO[r][h hd + c] O[r][h hd + c]: each thread takes 8
@@ -770,147 +759,68 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(
   }
 }
 
-template <typename T>
-hipError_t transpose_t(hipStream_t s, const void* in, int R, int C, int64_t ldi, void* out,
-                       int Rpad) {
-  const dim3 grid((C + 31) / 32, (Rpad + 31) / 32);
-  return launch(K_MISC, transpose_kernel<T>, grid, dim3(256), 0, s, static_cast<const T*>(in), R,
-                C, ldi, static_cast<T*>(out), Rpad);
-}
-
 }  // namespace
 
 bool backward_supported(int dtype, int hd) { return dtype == 1 && (hd == 64 || hd == 128); }
 
-hipError_t launch_transpose(hipStream_t s, int dtype, const void* in, int R, int C, int64_t ldi,
-                            void* out, int Rpad) {
-  if (C == 0 || Rpad == 0) return hipSuccess;
-  if (dtype == 1 && ldi % 8 == 0 && Rpad % 8 == 0)
-    return launch(K_MISC, transpose64_kernel, dim3((C + 63) / 64, (Rpad + 63) / 64), dim3(256), 0,
-                  s, static_cast<const bf16_t*>(in), R, C, ldi, static_cast<bf16_t*>(out), Rpad);
-  return dtype == 1 ? transpose_t<bf16_t>(s, in, R, C, ldi, out, Rpad)
-                    : transpose_t<float>(s, in, R, C, ldi, out, Rpad);
-}
-
-size_t colsum_scratch_floats(int R, int C) {
-  size_t f = 0;
-  for (int rows = R; rows > kColRows;) {
-    rows = (rows + kColRows - 1) / kColRows;
-    f += static_cast<size_t>(rows) * C;
+hipError_t launch_transposes(hipStream_t s, const TransposeArg* m, int count) {
+  if (count < 1 || count > 4) return hipErrorInvalidValue;
+  TransposeArgs p;
+  int total = 0;
+  for (int i = 0; i < 4; ++i) {
+    p.m[i] = m[std::min(i, count - 1)];
+    p.first[i] = total;
+    if (i >= count) continue;
+    if (m[i].r % 8 != 0 || m[i].c % 8 != 0) return hipErrorInvalidValue;
+    total += ((m[i].r + 63) / 64) * ((m[i].c + 63) / 64);
   }
-  return f + C;
+  p.first[4] = total;
+  if (total == 0) return hipSuccess;
+  return launch(K_MISC, transpose64_kernel, dim3(total), dim3(256), 0, s, p);
 }
 
-// passes of 64x row reduction (fixed order) until one row is left; the
-// first pass reads the input (times xhat when x is given), the others the
-// fp32 partial rows of the previous pass
-hipError_t launch_colsum(hipStream_t s, int dtype, const void* a, int64_t lda, const void* x,
-                         int64_t ldx, const float* stats, int R, int C, float* scratch,
-                         float* out) {
-  if (C == 0) return hipSuccess;
-  if (R == 0)
-    return launch(K_MISC, zero_f32_kernel, dim3((C + 255) / 256), dim3(256), 0, s, out, C);
-  const dim3 block(256);
-  int rows = R;
-  bool first = true;
-  const float* src = nullptr;
-  float* dst = scratch;
-  while (true) {
-    const int chunks = (rows + kColRows - 1) / kColRows;
-    float* target = chunks == 1 ? out : dst;
-    const dim3 grid((C + 255) / 256, chunks);  // 32 column groups of 8 per block
-    hipError_t e;
-    if (first && dtype == 1)
-      e = launch(K_MISC, colsum_stage1<bf16_t>, grid, block, 0, s, static_cast<const bf16_t*>(a),
-                 lda, static_cast<const bf16_t*>(x), ldx, stats, rows, C, target);
-    else if (first)
-      e = launch(K_MISC, colsum_stage1<float>, grid, block, 0, s, static_cast<const float*>(a),
-                 lda, static_cast<const float*>(x), ldx, stats, rows, C, target);
-    else
-      e = launch(K_MISC, colsum_stage1<float>, grid, block, 0, s, src, static_cast<int64_t>(C),
-                 static_cast<const float*>(nullptr), static_cast<int64_t>(0), nullptr, rows, C,
-                 target);
-    if (e != hipSuccess || chunks == 1) return e;
-    first = false;
-    src = dst;
-    dst += static_cast<size_t>(chunks) * C;
-    rows = chunks;
-  }
-}
+static int norm_bwd_blocks(int R) { return std::max(1, std::min((R + 7) / 8, kNormBwdBlocks)); }
 
-template <typename T, int RMS>
-static hipError_t norm_bwd_nc(hipStream_t s, const void* x, const void* g, const void* dh,
-                              const void* res, void* out, int R, int d, float eps, float* stats) {
-  const dim3 grid((R + 3) / 4), block(256);
-  auto* xp = static_cast<const T*>(x);
-  auto* gp = static_cast<const T*>(g);
-  auto* dp = static_cast<const T*>(dh);
-  auto* rp = static_cast<const T*>(res);
-  auto* op = static_cast<T*>(out);
-  const int nc = (d + 511) / 512;
-  if (nc <= 1) return launch(K_NORM, norm_bwd_kernel<T, RMS, 1>, grid, block, 0, s, xp, gp, dp, rp, op, R, d, eps, stats);
-  if (nc <= 2) return launch(K_NORM, norm_bwd_kernel<T, RMS, 2>, grid, block, 0, s, xp, gp, dp, rp, op, R, d, eps, stats);
-  if (nc <= 4) return launch(K_NORM, norm_bwd_kernel<T, RMS, 4>, grid, block, 0, s, xp, gp, dp, rp, op, R, d, eps, stats);
-  if (nc <= 8) return launch(K_NORM, norm_bwd_kernel<T, RMS, 8>, grid, block, 0, s, xp, gp, dp, rp, op, R, d, eps, stats);
-  return launch(K_NORM, norm_bwd_kernel<T, RMS, 16>, grid, block, 0, s, xp, gp, dp, rp, op, R, d, eps, stats);
-}
+size_t norm_bwd_scratch_floats(int R, int d) { return static_cast<size_t>(norm_bwd_blocks(R)) * 2 * d; }
 
-hipError_t launch_norm_bwd(hipStream_t s, int dtype, int kind, const void* x, const void* g,
-                           const void* dh, const void* res, void* out, int R, int d, float eps,
-                           float* stats) {
-  if (R == 0) return hipSuccess;
+hipError_t launch_norm_bwd(hipStream_t s, int kind, const void* x, const void* g, const void* dh,
+                           const void* res, void* out, int R, int d, float eps, float* scratch,
+                           float* dg, float* db) {
   if (d % 8 != 0 || d > 16 * 512) return hipErrorInvalidValue;
-  if (dtype == 1)
-    return kind == 1 ? norm_bwd_nc<bf16_t, 1>(s, x, g, dh, res, out, R, d, eps, stats)
-                     : norm_bwd_nc<bf16_t, 0>(s, x, g, dh, res, out, R, d, eps, stats);
-  return kind == 1 ? norm_bwd_nc<float, 1>(s, x, g, dh, res, out, R, d, eps, stats)
-                   : norm_bwd_nc<float, 0>(s, x, g, dh, res, out, R, d, eps, stats);
-}
-
-hipError_t launch_act_bwd(hipStream_t s, int dtype, const void* dF, const void* u, void* du,
-                          int rows, int F, int swiglu) {
-  const int64_t total = static_cast<int64_t>(rows) * F;
-  if (total == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((total / 8 + 255) / 256));  // F % 8 == 0
-  if (dtype == 1)
-    return launch(K_MISC, act_bwd_kernel<bf16_t>, grid, dim3(256), 0, s,
-                  static_cast<const bf16_t*>(dF), static_cast<const bf16_t*>(u),
-                  static_cast<bf16_t*>(du), static_cast<int64_t>(rows), F, swiglu);
-  return launch(K_MISC, act_bwd_kernel<float>, grid, dim3(256), 0, s,
-                static_cast<const float*>(dF), static_cast<const float*>(u),
-                static_cast<float*>(du), static_cast<int64_t>(rows), F, swiglu);
-}
-
-hipError_t launch_act_fwd(hipStream_t s, int dtype, const void* u, void* f, int rows, int F,
-                          int swiglu) {
-  const int64_t total = static_cast<int64_t>(rows) * F;
-  if (total == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((total / 8 + 255) / 256));  // F % 8 == 0
-  if (dtype == 1)
-    return launch(K_MISC, act_fwd_kernel<bf16_t>, grid, dim3(256), 0, s,
-                  static_cast<const bf16_t*>(u), static_cast<bf16_t*>(f),
-                  static_cast<int64_t>(rows), F, swiglu);
-  return launch(K_MISC, act_fwd_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(u),
-                static_cast<float*>(f), static_cast<int64_t>(rows), F, swiglu);
-}
-
-hipError_t launch_scatter_rows(hipStream_t s, int dtype, int d, const void* src,
-                               const int32_t* kept, int t_out, int t_in, int32_t* inv,
-                               void* dst) {
-  if (t_in == 0) return hipSuccess;
-  hipError_t e = launch(K_MISC, fill_i32_kernel, dim3((t_in + 255) / 256), dim3(256), 0, s, inv,
-                        t_in, -1);
+  const int blocks = norm_bwd_blocks(R), cols = kind == 1 ? d : 2 * d, nc = (d + 511) / 512;
+  auto go = [&](auto rms, auto layer) {
+    return launch(K_NORM, kind == 1 ? rms : layer, dim3(blocks), dim3(256), 0, s,
+                  static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(g),
+                  static_cast<const bf16_t*>(dh), static_cast<const bf16_t*>(res),
+                  static_cast<bf16_t*>(out), R, d, eps, scratch);
+  };
+  const hipError_t e = nc <= 1   ? go(norm_bwd_kernel<1, 1>, norm_bwd_kernel<0, 1>)
+                       : nc <= 2 ? go(norm_bwd_kernel<1, 2>, norm_bwd_kernel<0, 2>)
+                       : nc <= 4 ? go(norm_bwd_kernel<1, 4>, norm_bwd_kernel<0, 4>)
+                       : nc <= 8 ? go(norm_bwd_kernel<1, 8>, norm_bwd_kernel<0, 8>)
+                                 : go(norm_bwd_kernel<1, 16>, norm_bwd_kernel<0, 16>);
   if (e != hipSuccess) return e;
-  if (t_out > 0) {
-    e = launch(K_MISC, inverse_index_kernel, dim3((t_out + 255) / 256), dim3(256), 0, s, kept,
-               t_out, t_in, inv);
-    if (e != hipSuccess) return e;
-  }
-  const int cpr = d * (dtype == 1 ? 2 : 4) / 16;
-  const int64_t total = static_cast<int64_t>(t_in) * cpr;
-  return launch(K_MISC, scatter_rows_kernel, dim3(static_cast<unsigned>((total + 255) / 256)),
-                dim3(256), 0, s, static_cast<const uint4*>(src), inv, t_in, cpr,
-                static_cast<uint4*>(dst));
+  return launch(K_NORM, col_total_kernel, dim3((cols + 31) / 32), dim3(256), 0, s,
+                static_cast<const float*>(scratch), blocks, cols, d, dg, db);
+}
+
+hipError_t launch_act_bwd(hipStream_t s, const void* dF, const void* u, void* du, void* f, int rows,
+                          int F, int swiglu) {
+  const int64_t total = static_cast<int64_t>(rows) * F;
+  if (total == 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>((total / 8 + 255) / 256));  // F % 8 == 0
+  return launch(K_MISC, act_bwd_kernel, grid, dim3(256), 0, s, static_cast<const bf16_t*>(dF),
+                static_cast<const bf16_t*>(u), static_cast<bf16_t*>(du), static_cast<bf16_t*>(f),
+                static_cast<int64_t>(rows), F, swiglu);
+}
+
+hipError_t launch_scatter_rows(hipStream_t s, int d, const void* src0, void* dst0, const void* src1,
+                               void* dst1, const int32_t* kept, int t_out, int t_in) {
+  if (t_in == 0) return hipSuccess;
+  return launch(K_MISC, scatter_rows_kernel, dim3(t_out / 4 + 1), dim3(256), 0, s,
+                static_cast<const u32x4*>(src0), static_cast<u32x4*>(dst0),
+                static_cast<const u32x4*>(src1), static_cast<u32x4*>(dst1), kept, t_out, t_in,
+                d * 2 / 16);
 }
 
 hipError_t launch_rowdot(hipStream_t s, int dtype, const void* dO, const void* O, int64_t ld,

@@ -1,0 +1,304 @@
+// Weight and bias gradients of a projection y = x W^T + b (bf16 rows, fp32
+// gradients): dW = dY^T X, the contraction running over the rows, and db the
+// column sums of dY.
+//
+// Both operands are read as they lie, [rows, columns]: slices of rows go
+// straight to LDS (buffer loads with the LDS destination) and the matrix
+// fragments, which want eight consecutive rows of a column per lane, come
+// from the transposing LDS reads. The two operands are read with the same
+// row order within a fragment, which leaves the contraction unchanged. The
+// kernel this replaces wanted the rows consecutive in memory, so each
+// product first transposed both operands.
+//
+// db is summed on the same fragments: a product of dY^T with ones, each
+// (column tile of X, wave column) taking the slices that are its turn, so the
+// extra products are spread over the workgroups of a row of tiles.
+//
+// The rows are split over S workgroups per tile where the tiles alone would
+// not fill the chip; wgrad_sum_kernel adds the S partial results in order.
+// us with all their launches, before (two transposes, product, sum, two
+// column-sum passes) / now: 4096 rows, 3072 x 768 63.4 / 39.5, 768 x 768 45.5 /
+// 19.6, 2304 x 768 54.3 / 32.9; 8192 rows, 2304 x 768 85.6 / 50.2. What bounds the
+// product: the partial results it writes (28 MB at 3072 x 768) and the LDS, whose
+// reads and writes take 1.5 times the matrix instructions' time.
+#include "zsa_internal.h"
+
+namespace zsa {
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+constexpr int kBiasTiles = 4;  // column tiles that share the bias sums
+
+struct WgradArgs {
+  const bf16_t *a, *b;   // dY [rows, m], X [rows, n]
+  int rows, m, n;
+  int tm, tn, splits;    // tiles of m and n, row splits
+  int chunk;             // rows per split, a multiple of the slice
+  float* out;            // splits == 1: [m, n]; else [splits][m, n]
+  float* bias;           // [splits * 2 * min(tn, kBiasTiles)][m], or null
+};
+
+// TILE x TILE outputs on four waves (2 x 2), BK rows per slice, NB slices in
+// LDS, NB - 1 of them in flight; one barrier per slice.
+template <int TILE, int BK, int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(const WgradArgs p) {
+  constexpr int RB = TILE * 2, CPR = TILE / 8;   // bytes and 16-byte chunks of a slice row
+  constexpr int HALF = BK * RB, BUF = 2 * HALF;
+  constexpr int RPL = 1024 / RB, LPW = HALF / 1024 / 4;  // rows per load, loads per wave and operand
+  constexpr int FR = TILE / 64;                  // 32-wide fragments per wave and operand
+  static_assert(LPW * 4096 == HALF, "slice split");
+  __shared__ __align__(1024) unsigned char smem[NB * BUF];
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef __attribute__((address_space(3))) const char lds_char;
+
+  // an XCD (workgroup number mod 8) takes neighbouring tiles of one split,
+  // whose rows its L2 then holds
+  const int total = p.tm * p.tn * p.splits, per = (total + 7) / 8;
+  const int id = static_cast<int>(blockIdx.x & 7) * per + static_cast<int>(blockIdx.x >> 3);
+  if (static_cast<int>(blockIdx.x >> 3) >= per || id >= total) return;
+  const int split = id / (p.tm * p.tn), tile = id - split * (p.tm * p.tn);
+  const int im = tile / p.tn, in = tile - im * p.tn;
+  const int m0 = im * TILE, n0 = in * TILE;
+  const int r_begin = split * p.chunk, r_end = min(p.rows, r_begin + p.chunk);
+  const int slices = r_end > r_begin ? (r_end - r_begin + BK - 1) / BK : 0;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int wm = wave >> 1, wn = wave & 1;
+  // slice row r keeps its 16-byte chunk c at c ^ sw(r): the four rows a
+  // transposing read takes fall on all banks
+  auto sw = [](int r) { return TILE == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
+  const int lrow = wave * RPL + lane / CPR;  // slice row of the wave's first load
+  const uint32_t a_row = static_cast<uint32_t>(p.m) * 2, b_row = static_cast<uint32_t>(p.n) * 2;
+  const uint32_t lchunk = ((lane % CPR) ^ sw(lrow)) << 4;
+  const uint32_t aoff = lrow * a_row + lchunk, boff = lrow * b_row + lchunk;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
+  // the resource covers this slice's rows from the tile's first column on:
+  // rows past the split (or the whole slice, past the last) read as zeros;
+  // columns past the matrix read its next row and feed outputs that are not
+  // stored
+  auto resource = [&](const bf16_t* base, int width, int col, int r0) {
+    const uint64_t at = reinterpret_cast<uint64_t>(base + static_cast<int64_t>(r0) * width + col);
+    const int live = max(0, min(BK, r_end - r0));
+    const uint32_t bytes = live > 0 ? static_cast<uint32_t>(live) * width * 2 - col * 2 : 0;
+    const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(at))),
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(at >> 32))) & 0xffffu,
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
+    return r;
+  };
+  auto load_slice = [&](int t, int buf) {
+    const int r0 = t < slices ? r_begin + t * BK : r_end;
+    const u32x4 ar = resource(p.a, p.m, m0, r0), br = resource(p.b, p.n, n0, r0);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t d = lds0 + buf * BUF + i * 4096;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(aoff + i * (4 * RPL) * a_row), "s"(ar) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(boff + i * (4 * RPL) * b_row), "s"(br) : "memory");
+    }
+  };
+
+  // a fragment: columns 32 c + l32 of slice rows 16 g + 4 half + 0 .. 3 and
+  // + 8 of these. A transposing read gives each lane of a 16-lane group
+  // element (its number in the group) of four 16-element rows, row r pieced
+  // together from the runs at the addresses of the group's lanes 4r .. 4r + 3.
+  const int vrow = 4 * half + ((lane & 15) >> 2);
+  const int vch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+  const uint32_t f0 = vrow * RB + (lane & 1) * 8;
+  uint32_t fa[FR], fb[FR];
+#pragma unroll
+  for (int i = 0; i < FR; ++i) {
+    fa[i] = f0 + (((4 * (wm * FR + i) + vch) ^ sw(vrow)) << 4);
+    fb[i] = HALF + f0 + (((4 * (wn * FR + i) + vch) ^ sw(vrow)) << 4);
+  }
+  auto frag = [&](const unsigned char* at) {
+    const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)at));
+    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(at + 8 * RB)));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo4), h2 = __builtin_bit_cast(uint2, hi4);
+    const u32x4 v = {l2.x, l2.y, h2.x, h2.y};
+    return __builtin_bit_cast(bf16x8_t, v);
+  };
+
+  f32x16_t acc[FR][FR] = {}, sum[FR] = {};
+  const u32x4 one4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, one4);
+  const int nsum = 2 * min(p.tn, kBiasTiles);
+  int turn = p.bias != nullptr && in < kBiasTiles ? 2 * in + wn : -1;  // next slice this wave sums
+
+#pragma unroll
+  for (int t = 0; t < NB - 1; ++t) load_slice(t, t);
+  for (int t = 0; t < slices; ++t) {
+    __builtin_amdgcn_sched_barrier(0);
+    // slice t has landed (NB - 2 later ones may be in flight), and every wave
+    // is done with slice t - 1, whose buffer the next load takes
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * 2 * LPW) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    load_slice(t + NB - 1, (t + NB - 1) % NB);
+    const unsigned char* base = smem + (t % NB) * BUF;
+    const bool mine = t == turn;
+    if (mine) turn += nsum;
+#pragma unroll
+    for (int g = 0; g < BK / 16; ++g) {
+      bf16x8_t av[FR], bv[FR];
+#pragma unroll
+      for (int i = 0; i < FR; ++i) av[i] = frag(base + fa[i] + g * (16 * RB));
+#pragma unroll
+      for (int i = 0; i < FR; ++i) bv[i] = frag(base + fb[i] + g * (16 * RB));
+#pragma unroll
+      for (int i = 0; i < FR; ++i)
+#pragma unroll
+        for (int j = 0; j < FR; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+      if (mine) {
+#pragma unroll
+        for (int i = 0; i < FR; ++i)
+          sum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], ones, sum[i], 0, 0, 0);
+      }
+    }
+  }
+  // no load may still be writing LDS when the workgroup ends
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  // acc[i][j][r]: row m0 + 32 (wm FR + i) + 8 (r/4) + 4 half + r%4, column n0 + 32 (wn FR + j) + l32
+  float* out = p.out + static_cast<int64_t>(split) * p.m * p.n;
+#pragma unroll
+  for (int i = 0; i < FR; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 32 * (wm * FR + i) + 8 * (r >> 2) + 4 * half + (r & 3);
+#pragma unroll
+      for (int j = 0; j < FR; ++j) {
+        const int n = n0 + 32 * (wn * FR + j) + l32;
+        if (m < p.m && n < p.n) out[static_cast<int64_t>(m) * p.n + n] = acc[i][j][r];
+      }
+    }
+  if (p.bias != nullptr && in < kBiasTiles && l32 == 0) {
+    float* row = p.bias + (static_cast<int64_t>(split) * nsum + 2 * in + wn) * p.m;
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + 32 * (wm * FR + i) + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (m < p.m) row[m] = sum[i][r];
+      }
+  }
+}
+
+// The sums of the split rows' partial products (total4 float4, `splits` of
+// them; none when total4 is 0) and, in the workgroups past those, of the
+// bias rows [brows][m] -- 32 columns a workgroup, 32 row lanes -- in order.
+__global__ __launch_bounds__(256) void wgrad_sum_kernel(const float4* __restrict__ part, int splits,
+                                                        int64_t total4, int blocks4,
+                                                        float4* __restrict__ out,
+                                                        const float* __restrict__ bias, int brows, int m,
+                                                        float* __restrict__ db) {
+  if (static_cast<int>(blockIdx.x) < blocks4) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= total4) return;
+    float4 v = part[i];
+#pragma unroll 4
+    for (int y = 1; y < splits; ++y) {
+      const float4 t = part[y * total4 + i];
+      v.x += t.x;
+      v.y += t.y;
+      v.z += t.z;
+      v.w += t.w;
+    }
+    out[i] = v;
+    return;
+  }
+  __shared__ float red[32][33];
+  const int q = threadIdx.x & 7, rl = threadIdx.x >> 3;
+  const int c0 = (blockIdx.x - blocks4) * 32, c = c0 + 4 * q;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c < m) {  // m is a multiple of 8
+#pragma unroll 4
+    for (int r = rl; r < brows; r += 32) {
+      const float4 t = *reinterpret_cast<const float4*>(bias + static_cast<int64_t>(r) * m + c);
+      v.x += t.x;
+      v.y += t.y;
+      v.z += t.z;
+      v.w += t.w;
+    }
+  }
+  red[rl][4 * q] = v.x;
+  red[rl][4 * q + 1] = v.y;
+  red[rl][4 * q + 2] = v.z;
+  red[rl][4 * q + 3] = v.w;
+  __syncthreads();
+  if (threadIdx.x < 32 && c0 + static_cast<int>(threadIdx.x) < m) {
+    float s = red[0][threadIdx.x];
+    for (int k = 1; k < min(32, brows); ++k) s += red[k][threadIdx.x];
+    db[c0 + threadIdx.x] = s;
+  }
+}
+
+// 128-wide tiles read each operand half as often, 64-wide ones need fewer
+// splits to fill the two workgroups a CU holds (512 in all) and so write fewer
+// partial results: 768 x 768 over 4096 rows, 19.7 us in 36 tiles of 128 and 13
+// splits (30 MB) with the kernel of before, 14.6 in 144 tiles of 64 and 3.
+// Splits keep at least 128 rows.
+struct WgradPlan { int tile, tm, tn, splits, chunk; };
+
+WgradPlan wgrad_plan(int rows, int m, int n) {
+  WgradPlan p;
+  const int64_t t128 = static_cast<int64_t>((m + 127) / 128) * ((n + 127) / 128);
+  p.tile = t128 >= 64 ? 128 : 64;
+  p.tm = (m + p.tile - 1) / p.tile;
+  p.tn = (n + p.tile - 1) / p.tile;
+  const int64_t tiles = static_cast<int64_t>(p.tm) * p.tn;
+  const int64_t want = std::max<int64_t>(1, 512 / tiles), room = std::max(1, rows / 128);
+  const int s = static_cast<int>(std::min(want, room));
+  p.chunk = std::max(64, ((rows + s - 1) / s + 63) / 64 * 64);
+  p.splits = std::max(1, (rows + p.chunk - 1) / p.chunk);
+  return p;
+}
+
+size_t bias_rows(const WgradPlan& p) { return static_cast<size_t>(p.splits) * 2 * std::min(p.tn, kBiasTiles); }
+
+}  // namespace
+
+size_t wgrad_workspace_bytes(int max_rows, int m, int n) {
+  // the splits never fall as the rows grow past a multiple of 128, so the
+  // most any number of rows needs is bounded by the wanted splits
+  const WgradPlan p = wgrad_plan(max_rows, m, n);
+  const int64_t tiles = static_cast<int64_t>(p.tm) * p.tn;
+  const size_t s = static_cast<size_t>(std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max(1, max_rows / 128)));
+  const size_t part = s > 1 ? s * m * n : 0;
+  return (part + s * 2 * std::min(p.tn, kBiasTiles) * m) * sizeof(float);
+}
+
+hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int n, int rows,
+                        float* dw, float* db, void* ws, size_t ws_bytes) {
+  if (m == 0 || n == 0) return hipSuccess;
+  const WgradPlan p = wgrad_plan(rows, m, n);
+  const size_t part = p.splits > 1 ? static_cast<size_t>(p.splits) * m * n : 0;
+  const size_t brows = db != nullptr ? bias_rows(p) : 0;
+  if (m % 8 != 0 || n % 8 != 0 || ws_bytes < (part + brows * m) * sizeof(float)) return hipErrorInvalidValue;
+  float* w = static_cast<float*>(ws);
+  WgradArgs a;
+  a.a = static_cast<const bf16_t*>(dy);
+  a.b = static_cast<const bf16_t*>(x);
+  a.rows = rows;
+  a.m = m;
+  a.n = n;
+  a.tm = p.tm;
+  a.tn = p.tn;
+  a.splits = p.splits;
+  a.chunk = p.chunk;
+  a.out = p.splits > 1 ? w : dw;
+  a.bias = db != nullptr ? w + part : nullptr;
+  const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(p.tm) * p.tn * p.splits + 7) / 8 * 8);
+  const hipError_t e = p.tile == 128 ? launch(K_GEMM, wgrad_kernel<128, 32, 4>, dim3(grid), dim3(256), 0, s, a)
+                                     : launch(K_GEMM, wgrad_kernel<64, 64, 4>, dim3(grid), dim3(256), 0, s, a);
+  if (e != hipSuccess || (part == 0 && db == nullptr)) return e;
+  const int64_t total4 = part ? static_cast<int64_t>(m) * n / 4 : 0;
+  const int blocks4 = static_cast<int>((total4 + 255) / 256);
+  return launch(K_GEMM, wgrad_sum_kernel, dim3(blocks4 + (db != nullptr ? (m + 31) / 32 : 0)), dim3(256), 0, s,
+                reinterpret_cast<const float4*>(w), p.splits, total4, blocks4, reinterpret_cast<float4*>(dw),
+                static_cast<const float*>(a.bias), static_cast<int>(brows), m, db);
+}
+
+}  // namespace zsa

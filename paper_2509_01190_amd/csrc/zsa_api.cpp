@@ -913,11 +913,9 @@ int zsa_stack_forward(void* stream, const zsa_layer_cfg* cfg, const zsa_layer_we
 // ---------------------------------------------------------------------------
 namespace {
 
-int64_t round64(int64_t v) { return (v + 63) / 64 * 64; }
-
 // buffers of one layer's backward, for up to T rows
 struct BwdLayout {
-  size_t h1, x1, h2, u, dF, du, dh2, dx1, dog, dofull, dxr, dqkv, dh1, D, stats, inv, wT, aT, bT,
+  size_t h1, x1, h2, u, dF, du, dh2, dx1, dog, dofull, dxr, dqkv, dh1, D, wqkvT, woT, wupT, wdownT,
       col, splitk, splitk_bytes, end;
 };
 
@@ -925,7 +923,6 @@ BwdLayout bwd_layout(const zsa_layer_cfg* c, int64_t T, Carver& cv) {
   const size_t e = esize(c->dtype);
   const int64_t d = c->d_model, F = c->d_ff, qw = qkv_width(*c);
   const int64_t up_n = c->kind == ZSA_DECODER ? 2 * F : F;
-  const int64_t maxc = std::max({d, qw, up_n, F});
   BwdLayout B;
   B.h1 = cv.take(T * d * e);
   B.x1 = cv.take(T * d * e);
@@ -941,25 +938,23 @@ BwdLayout bwd_layout(const zsa_layer_cfg* c, int64_t T, Carver& cv) {
   B.dqkv = cv.take(T * qw * e);
   B.dh1 = cv.take(T * d * e);
   B.D = cv.take(static_cast<size_t>(c->n_heads) * T * 4);
-  B.stats = cv.take(static_cast<size_t>(T) * 2 * 4);
-  B.inv = cv.take(static_cast<size_t>(T) * 4);
-  B.wT = cv.take(static_cast<size_t>(d) * maxc * e);
-  B.aT = cv.take(static_cast<size_t>(round64(T)) * maxc * e);
-  B.bT = cv.take(static_cast<size_t>(round64(T)) * maxc * e);
-  B.col = cv.take(zsa::colsum_scratch_floats(static_cast<int>(T), static_cast<int>(maxc)) * 4);
+  B.wqkvT = cv.take(static_cast<size_t>(d) * qw * e);
+  B.woT = cv.take(static_cast<size_t>(d) * d * e);
+  B.wupT = cv.take(static_cast<size_t>(d) * up_n * e);
+  B.wdownT = cv.take(static_cast<size_t>(d) * F * e);
+  B.col = cv.take(zsa::norm_bwd_scratch_floats(static_cast<int>(T), static_cast<int>(d)) * 4);
   // split-K room for the backward's input-gradient products at any row count
   const int dt = c->dtype, rows = static_cast<int>(T);
   B.splitk_bytes = std::max({zsa::gemm_workspace_bound(dt, rows, static_cast<int>(F), static_cast<int>(d)),
                              zsa::gemm_workspace_bound(dt, rows, static_cast<int>(d), static_cast<int>(up_n)),
                              zsa::gemm_workspace_bound(dt, rows, static_cast<int>(d), static_cast<int>(d)),
                              zsa::gemm_workspace_bound(dt, rows, static_cast<int>(d), static_cast<int>(qw))});
-  // ... and for the weight-gradient products (K = the rows, padded to 64)
-  const int kp = static_cast<int>(round64(T));
+  // ... and for the weight-gradient products
   B.splitk_bytes = std::max({B.splitk_bytes,
-                             zsa::gemm_f32_workspace_bound(static_cast<int>(d), static_cast<int>(F), kp),
-                             zsa::gemm_f32_workspace_bound(static_cast<int>(up_n), static_cast<int>(d), kp),
-                             zsa::gemm_f32_workspace_bound(static_cast<int>(d), static_cast<int>(d), kp),
-                             zsa::gemm_f32_workspace_bound(static_cast<int>(qw), static_cast<int>(d), kp)});
+                             zsa::wgrad_workspace_bytes(rows, static_cast<int>(d), static_cast<int>(F)),
+                             zsa::wgrad_workspace_bytes(rows, static_cast<int>(up_n), static_cast<int>(d)),
+                             zsa::wgrad_workspace_bytes(rows, static_cast<int>(d), static_cast<int>(d)),
+                             zsa::wgrad_workspace_bytes(rows, static_cast<int>(qw), static_cast<int>(d))});
   B.splitk = cv.take(B.splitk_bytes);
   B.end = cv.off;
   return B;
@@ -980,9 +975,7 @@ int layer_backward(hipStream_t s, const zsa_layer_cfg& c, const zsa_layer_weight
   const int up_n = dec ? 2 * F : F;
   const float scale = 1.0f / sqrtf(static_cast<float>(hd));
   const int T = in.T, To = prune ? out.T : in.T;
-  const int Tp = static_cast<int>(round64(T)), Top = static_cast<int>(round64(To));
   auto P = [&](size_t off) { return static_cast<void*>(base + off); };
-  float* stats = reinterpret_cast<float*>(base + B.stats);
   float* col = reinterpret_cast<float*>(base + B.col);
   void* sk = B.splitk_bytes ? P(B.splitk) : nullptr;
   auto gemm = [&](const void* x, int M, int K, const void* wt, int N, void* y) {
@@ -992,25 +985,10 @@ int layer_backward(hipStream_t s, const zsa_layer_cfg& c, const zsa_layer_weight
     ep.ldy = N;
     return launch_gemm(s, dt, x, M, K, wt, N, ep, sk, B.splitk_bytes);
   };
-  // dW = a^T b over `rows` rows: a [rows, na], b [rows, nb] -> out [na, nb]
-  auto wgrad = [&](const void* a, int na, const void* b, int nb, int rows, int rows_p,
-                   float* out) -> hipError_t {
-    hipError_t er = launch_transpose(s, dt, a, rows, na, na, P(B.aT), rows_p);
-    if (er != hipSuccess) return er;
-    er = launch_transpose(s, dt, b, rows, nb, nb, P(B.bT), rows_p);
-    if (er != hipSuccess) return er;
-    return launch_gemm_f32(s, P(B.aT), na, rows_p, P(B.bT), nb, out, sk, B.splitk_bytes);
-  };
-  // y = x W for W [n_out_w, n_in_w] stored as a Linear weight: x [rows, n_out_w]
-  auto xgrad = [&](const void* x, int rows, const void* W, int wn, int wk, void* y) -> hipError_t {
-    hipError_t er = launch_transpose(s, dt, W, wn, wk, wk, P(B.wT), wn);  // W^T [wk, wn]
-    if (er != hipSuccess) return er;
-    return gemm(x, rows, wn, P(B.wT), wk, y);
-  };
-  auto colsum = [&](const void* a, int rows, int cols, const void* x, float* outp) -> hipError_t {
-    if (outp == nullptr) return hipSuccess;
-    return launch_colsum(s, dt, a, cols, x, cols, x != nullptr ? stats : nullptr, rows, cols, col,
-                         outp);
+  // dW = a^T b over `rows` rows and db the column sums of a: a [rows, na],
+  // b [rows, nb] -> dw [na, nb], db [na] (may be NULL)
+  auto wgrad = [&](const void* a, int na, const void* b, int nb, int rows, float* dw, float* db) {
+    return launch_wgrad(s, a, na, b, nb, rows, dw, db, sk, B.splitk_bytes);
   };
 
   // ---- the layer's forward again (deterministic: the same values)
@@ -1068,32 +1046,28 @@ int layer_backward(hipStream_t s, const zsa_layer_cfg& c, const zsa_layer_weight
     HIP_TRY(launch_gemm(s, dt, P(B.h2), To, d, w.w_up, up_n, ep, wb.splitk, wb.splitk_bytes),
             "up projection");
   }
-  HIP_TRY(launch_act_fwd(s, dt, P(B.u), wb.f, To, F, dec), "activation");
+  // the weights transposed: W^T [in, out], for the input gradients x W
+  const TransposeArg wt[4] = {{w.w_qkv, P(B.wqkvT), qw, d}, {w.w_o, P(B.woT), d, d},
+                              {w.w_up, P(B.wupT), up_n, d}, {w.w_down, P(B.wdownT), d, F}};
+  HIP_TRY(launch_transposes(s, wt, 4), "weight transposes");
 
   // ---- backward: MLP
-  HIP_TRY(wgrad(dy, d, wb.f, F, To, Top, gr.w_down), "down weight gradient");
-  HIP_TRY(colsum(dy, To, d, nullptr, gr.b_down), "down bias gradient");
-  HIP_TRY(xgrad(dy, To, w.w_down, d, F, P(B.dF)), "down input gradient");
-  HIP_TRY(launch_act_bwd(s, dt, P(B.dF), P(B.u), P(B.du), To, F, dec), "activation gradient");
-  HIP_TRY(wgrad(P(B.du), up_n, P(B.h2), d, To, Top, gr.w_up), "up weight gradient");
-  HIP_TRY(colsum(P(B.du), To, up_n, nullptr, gr.b_up), "up bias gradient");
-  HIP_TRY(xgrad(P(B.du), To, w.w_up, up_n, d, P(B.dh2)), "up input gradient");
-  HIP_TRY(launch_norm_bwd(s, dt, norm_kind, P(B.x1), w.norm2_w, P(B.dh2), dy, P(B.dx1), To, d,
-                          c.norm_eps, stats),
+  HIP_TRY(gemm(dy, To, d, P(B.wdownT), F, P(B.dF)), "down input gradient");
+  HIP_TRY(launch_act_bwd(s, P(B.dF), P(B.u), P(B.du), wb.f, To, F, dec), "activation gradient");
+  HIP_TRY(wgrad(dy, d, wb.f, F, To, gr.w_down, gr.b_down), "down weight gradient");
+  HIP_TRY(wgrad(P(B.du), up_n, P(B.h2), d, To, gr.w_up, gr.b_up), "up weight gradient");
+  HIP_TRY(gemm(P(B.du), To, up_n, P(B.wupT), d, P(B.dh2)), "up input gradient");
+  HIP_TRY(launch_norm_bwd(s, norm_kind, P(B.x1), w.norm2_w, P(B.dh2), dy, P(B.dx1), To, d, c.norm_eps,
+                          col, gr.norm2_w, dec ? nullptr : gr.norm2_b),
           "norm2 gradient");
-  HIP_TRY(colsum(P(B.dh2), To, d, P(B.x1), gr.norm2_w), "norm2 gain gradient");
-  if (!dec) HIP_TRY(colsum(P(B.dh2), To, d, nullptr, gr.norm2_b), "norm2 shift gradient");
   // ---- output projection
-  HIP_TRY(wgrad(P(B.dx1), d, og, d, To, Top, gr.w_o), "output weight gradient");
-  HIP_TRY(colsum(P(B.dx1), To, d, nullptr, gr.b_o), "output bias gradient");
-  HIP_TRY(xgrad(P(B.dx1), To, w.w_o, d, d, P(B.dog)), "output input gradient");
+  HIP_TRY(wgrad(P(B.dx1), d, og, d, To, gr.w_o, gr.b_o), "output weight gradient");
+  HIP_TRY(gemm(P(B.dx1), To, d, P(B.woT), d, P(B.dog)), "output input gradient");
   // ---- undo compaction: dropped rows get no gradient from the rows after them
   const void* dof = P(B.dog);
   const void* dxr = P(B.dx1);
   if (prune) {
-    int32_t* inv = reinterpret_cast<int32_t*>(base + B.inv);
-    HIP_TRY(launch_scatter_rows(s, dt, d, P(B.dog), kept, To, T, inv, P(B.dofull)), "scatter");
-    HIP_TRY(launch_scatter_rows(s, dt, d, P(B.dx1), kept, To, T, inv, P(B.dxr)), "scatter");
+    HIP_TRY(launch_scatter_rows(s, d, P(B.dog), P(B.dofull), P(B.dx1), P(B.dxr), kept, To, T), "scatter");
     dof = P(B.dofull);
     dxr = P(B.dxr);
   }
@@ -1107,14 +1081,11 @@ int layer_backward(hipStream_t s, const zsa_layer_cfg& c, const zsa_layer_weight
           "attention gradient");
   if (dec) HIP_TRY(launch_rope_bwd(s, dt, dqkv, qw, T, d + kvd, hd, pos_in, rope), "rope gradient");
   // ---- qkv projection and norm1
-  HIP_TRY(wgrad(dqkv, qw, P(B.h1), d, T, Tp, gr.w_qkv), "qkv weight gradient");
-  HIP_TRY(colsum(dqkv, T, qw, nullptr, gr.b_qkv), "qkv bias gradient");
-  HIP_TRY(xgrad(dqkv, T, w.w_qkv, qw, d, P(B.dh1)), "qkv input gradient");
-  HIP_TRY(launch_norm_bwd(s, dt, norm_kind, x_in, w.norm1_w, P(B.dh1), dxr, dx, T, d, c.norm_eps,
-                          stats),
+  HIP_TRY(wgrad(dqkv, qw, P(B.h1), d, T, gr.w_qkv, gr.b_qkv), "qkv weight gradient");
+  HIP_TRY(gemm(dqkv, T, qw, P(B.wqkvT), d, P(B.dh1)), "qkv input gradient");
+  HIP_TRY(launch_norm_bwd(s, norm_kind, x_in, w.norm1_w, P(B.dh1), dxr, dx, T, d, c.norm_eps, col,
+                          gr.norm1_w, dec ? nullptr : gr.norm1_b),
           "norm1 gradient");
-  HIP_TRY(colsum(P(B.dh1), T, d, x_in, gr.norm1_w), "norm1 gain gradient");
-  if (!dec) HIP_TRY(colsum(P(B.dh1), T, d, nullptr, gr.norm1_b), "norm1 shift gradient");
   return ZSA_OK;
 }
 

@@ -282,25 +282,29 @@ bool decode_supported(int dtype, int hd, int group);
 
 // backward pass (bf16, head_dim 64 / 128 for the attention part)
 bool backward_supported(int dtype, int hd);
-hipError_t launch_gemm_f32(hipStream_t s, const void* x, int M, int K, const void* w, int N,
-                           float* out, void* ws, size_t ws_bytes);
-size_t gemm_f32_workspace_bound(int M, int N, int K);
-hipError_t launch_transpose(hipStream_t s, int dtype, const void* in, int R, int C, int64_t ldi,
-                            void* out, int Rpad);
-size_t colsum_scratch_floats(int R, int C);
-hipError_t launch_colsum(hipStream_t s, int dtype, const void* a, int64_t lda, const void* x,
-                         int64_t ldx, const float* stats, int R, int C, float* scratch,
-                         float* out);
-hipError_t launch_norm_bwd(hipStream_t s, int dtype, int kind, const void* x, const void* g,
-                           const void* dh, const void* res, void* out, int R, int d, float eps,
-                           float* stats);
-hipError_t launch_act_fwd(hipStream_t s, int dtype, const void* u, void* f, int rows, int F,
-                          int swiglu);
-hipError_t launch_act_bwd(hipStream_t s, int dtype, const void* dF, const void* u, void* du,
-                          int rows, int F, int swiglu);
-hipError_t launch_scatter_rows(hipStream_t s, int dtype, int d, const void* src,
-                               const int32_t* kept, int t_out, int t_in, int32_t* inv,
-                               void* dst);
+// dW [m, n] = dY^T X over `rows` rows and db [m] = the column sums of dY (db
+// may be NULL), both fp32
+hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int n, int rows,
+                        float* dw, float* db, void* ws, size_t ws_bytes);
+// the most any number of rows up to max_rows needs
+size_t wgrad_workspace_bytes(int max_rows, int m, int n);
+// out = in^T for up to four bf16 matrices [r, c] in one launch
+struct TransposeArg { const void* in; void* out; int r, c; };
+hipError_t launch_transposes(hipStream_t s, const TransposeArg* t, int count);
+// out = res + dL/dx of a norm whose output has gradient dh, dg and db [d] the
+// gradients of its gain and shift (db may be NULL; unused by RMSNorm).
+// scratch: norm_bwd_scratch_floats of the largest R
+size_t norm_bwd_scratch_floats(int R, int d);
+hipError_t launch_norm_bwd(hipStream_t s, int kind, const void* x, const void* g, const void* dh,
+                           const void* res, void* out, int R, int d, float eps, float* scratch,
+                           float* dg, float* db);
+// f = act(u) and du = dF act'(u)
+hipError_t launch_act_bwd(hipStream_t s, const void* dF, const void* u, void* du, void* f, int rows,
+                          int F, int swiglu);
+// undoes compaction of two arrays of d-wide rows: dst[kept[i]] = src[i],
+// zeros elsewhere (kept ascending)
+hipError_t launch_scatter_rows(hipStream_t s, int d, const void* src0, void* dst0, const void* src1,
+                               void* dst1, const int32_t* kept, int t_out, int t_in);
 hipError_t launch_rowdot(hipStream_t s, int dtype, const void* dO, const void* O, int64_t ld,
                          int T, int H, int hd, float* D);
 hipError_t launch_rope_bwd(hipStream_t s, int dtype, void* g, int64_t ld, int rows, int cols,

@@ -75,31 +75,24 @@ bool decode_supported(int dtype, int hd, int group) {
          (group == 1 || group == 2 || group == 4 || group == 8);
 }
 bool backward_supported(int dtype, int hd) { return dtype == 1 && (hd == 64 || hd == 128); }
-hipError_t launch_gemm_f32(hipStream_t, const void*, int, int, const void*, int, float*, void*,
-                           size_t) {
-  reached("launch_gemm_f32");
+hipError_t launch_wgrad(hipStream_t, const void*, int, const void*, int, int, float*, float*,
+                        void*, size_t) {
+  reached("launch_wgrad");
 }
-size_t gemm_f32_workspace_bound(int, int, int) { return 0; }
-hipError_t launch_transpose(hipStream_t, int, const void*, int, int, int64_t, void*, int) {
-  reached("launch_transpose");
+size_t wgrad_workspace_bytes(int, int, int) { return 0; }
+hipError_t launch_transposes(hipStream_t, const TransposeArg*, int) {
+  reached("launch_transposes");
 }
-size_t colsum_scratch_floats(int, int) { return 0; }
-hipError_t launch_colsum(hipStream_t, int, const void*, int64_t, const void*, int64_t,
-                         const float*, int, int, float*, float*) {
-  reached("launch_colsum");
-}
-hipError_t launch_norm_bwd(hipStream_t, int, int, const void*, const void*, const void*,
-                           const void*, void*, int, int, float, float*) {
+size_t norm_bwd_scratch_floats(int, int) { return 0; }
+hipError_t launch_norm_bwd(hipStream_t, int, const void*, const void*, const void*, const void*,
+                           void*, int, int, float, float*, float*, float*) {
   reached("launch_norm_bwd");
 }
-hipError_t launch_act_fwd(hipStream_t, int, const void*, void*, int, int, int) {
-  reached("launch_act_fwd");
-}
-hipError_t launch_act_bwd(hipStream_t, int, const void*, const void*, void*, int, int, int) {
+hipError_t launch_act_bwd(hipStream_t, const void*, const void*, void*, void*, int, int, int) {
   reached("launch_act_bwd");
 }
-hipError_t launch_scatter_rows(hipStream_t, int, int, const void*, const int32_t*, int, int,
-                               int32_t*, void*) {
+hipError_t launch_scatter_rows(hipStream_t, int, const void*, void*, const void*, void*,
+                               const int32_t*, int, int) {
   reached("launch_scatter_rows");
 }
 hipError_t launch_rowdot(hipStream_t, int, const void*, const void*, int64_t, int, int, int,
