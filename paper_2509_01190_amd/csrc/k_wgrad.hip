@@ -10,9 +10,9 @@
 // kernel this replaces wanted the rows consecutive in memory, so each
 // product first transposed both operands.
 //
-// db is summed on the same fragments: a product of dY^T with ones, each
-// (column tile of X, wave column) taking the slices that are its turn, so the
-// extra products are spread over the workgroups of a row of tiles.
+// db is summed from the same fragments, each (column tile of X, wave column)
+// taking the slices that are its turn, so that the additions are spread over
+// the workgroups of a row of tiles.
 //
 // The rows are split over S workgroups per tile where the tiles alone would
 // not fill the chip; wgrad_sum_kernel adds the S partial results in order.
@@ -37,18 +37,18 @@ struct WgradArgs {
   int tm, tn, splits;    // tiles of m and n, row splits
   int chunk;             // rows per split, a multiple of the slice
   float* out;            // splits == 1: [m, n]; else [splits][m, n]
-  float* bias;           // [splits * 2 * min(tn, kBiasTiles)][m], or null
+  float* bias;           // [splits * wave columns * min(tn, kBiasTiles)][m], or null
 };
 
-// TILE x TILE outputs on four waves (2 x 2), BK rows per slice, NB slices in
-// LDS, NB - 1 of them in flight; one barrier per slice.
-template <int TILE, int BK, int NB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(const WgradArgs p) {
-  constexpr int RB = TILE * 2, CPR = TILE / 8;   // bytes and 16-byte chunks of a slice row
+// TILE x TILE outputs on WM x WN waves, BK rows per slice, NB slices in LDS,
+// NB - 1 of them in flight; one barrier per slice.
+template <int TILE, int WM, int WN, int BK, int NB>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(const WgradArgs p) {
+  constexpr int NW = WM * WN, RB = TILE * 2, CPR = TILE / 8;  // bytes and 16-byte chunks of a slice row
   constexpr int HALF = BK * RB, BUF = 2 * HALF;
-  constexpr int RPL = 1024 / RB, LPW = HALF / 1024 / 4;  // rows per load, loads per wave and operand
-  constexpr int FR = TILE / 64;                  // 32-wide fragments per wave and operand
-  static_assert(LPW * 4096 == HALF, "slice split");
+  constexpr int RPL = 1024 / RB, LPW = HALF / 1024 / NW;  // rows per load, loads per wave and operand
+  constexpr int FM = TILE / 32 / WM, FN = TILE / 32 / WN;  // 32-wide fragments per wave
+  static_assert(LPW * NW * 1024 == HALF, "slice split");
   __shared__ __align__(1024) unsigned char smem[NB * BUF];
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, l32 = lane & 31;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / WN, wn = wave % WN;
   // slice row r keeps its 16-byte chunk c at c ^ sw(r): the four rows a
   // transposing read takes fall on all banks
   auto sw = [](int r) { return TILE == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
@@ -94,9 +94,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const u32x4 ar = resource(p.a, p.m, m0, r0), br = resource(p.b, p.n, n0, r0);
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-      const uint32_t d = lds0 + buf * BUF + i * 4096;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(aoff + i * (4 * RPL) * a_row), "s"(ar) : "memory");
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(boff + i * (4 * RPL) * b_row), "s"(br) : "memory");
+      const uint32_t d = lds0 + buf * BUF + i * (NW * 1024);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(aoff + i * (NW * RPL) * a_row), "s"(ar) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(boff + i * (NW * RPL) * b_row), "s"(br) : "memory");
     }
   };
 
@@ -107,12 +107,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int vrow = 4 * half + ((lane & 15) >> 2);
   const int vch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
   const uint32_t f0 = vrow * RB + (lane & 1) * 8;
-  uint32_t fa[FR], fb[FR];
+  uint32_t fa[FM], fb[FN];
 #pragma unroll
-  for (int i = 0; i < FR; ++i) {
-    fa[i] = f0 + (((4 * (wm * FR + i) + vch) ^ sw(vrow)) << 4);
-    fb[i] = HALF + f0 + (((4 * (wn * FR + i) + vch) ^ sw(vrow)) << 4);
-  }
+  for (int i = 0; i < FM; ++i) fa[i] = f0 + (((4 * (wm * FM + i) + vch) ^ sw(vrow)) << 4);
+#pragma unroll
+  for (int j = 0; j < FN; ++j) fb[j] = HALF + f0 + (((4 * (wn * FN + j) + vch) ^ sw(vrow)) << 4);
   auto frag = [&](const unsigned char* at) {
     const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)at));
     const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(at + 8 * RB)));
@@ -121,11 +120,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     return __builtin_bit_cast(bf16x8_t, v);
   };
 
-  f32x16_t acc[FR][FR] = {}, sum[FR] = {};
-  const u32x4 one4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, one4);
-  const int nsum = 2 * min(p.tn, kBiasTiles);
-  int turn = p.bias != nullptr && in < kBiasTiles ? 2 * in + wn : -1;  // next slice this wave sums
+  f32x16_t acc[FM][FN] = {};
+  float sum[FM] = {};  // of column l32 of each fragment, over this half's rows
+  const int nsum = WN * min(p.tn, kBiasTiles);
+  int turn = p.bias != nullptr && in < kBiasTiles ? WN * in + wn : -1;  // next slice this wave sums
 
 #pragma unroll
   for (int t = 0; t < NB - 1; ++t) load_slice(t, t);
@@ -141,48 +139,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (mine) turn += nsum;
 #pragma unroll
     for (int g = 0; g < BK / 16; ++g) {
-      bf16x8_t av[FR], bv[FR];
+      bf16x8_t av[FM], bv[FN];
 #pragma unroll
-      for (int i = 0; i < FR; ++i) av[i] = frag(base + fa[i] + g * (16 * RB));
+      for (int i = 0; i < FM; ++i) av[i] = frag(base + fa[i] + g * (16 * RB));
 #pragma unroll
-      for (int i = 0; i < FR; ++i) bv[i] = frag(base + fb[i] + g * (16 * RB));
+      for (int j = 0; j < FN; ++j) bv[j] = frag(base + fb[j] + g * (16 * RB));
 #pragma unroll
-      for (int i = 0; i < FR; ++i)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FR; ++j)
+        for (int j = 0; j < FN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
       if (mine) {
 #pragma unroll
-        for (int i = 0; i < FR; ++i)
-          sum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], ones, sum[i], 0, 0, 0);
+        for (int i = 0; i < FM; ++i) {
+          const u32x4 w = __builtin_bit_cast(u32x4, av[i]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            sum[i] += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
+        }
       }
     }
   }
   // no load may still be writing LDS when the workgroup ends
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
-  // acc[i][j][r]: row m0 + 32 (wm FR + i) + 8 (r/4) + 4 half + r%4, column n0 + 32 (wn FR + j) + l32
+  // acc[i][j][r]: row m0 + 32 (wm FM + i) + 8 (r/4) + 4 half + r%4, column n0 + 32 (wn FN + j) + l32
   float* out = p.out + static_cast<int64_t>(split) * p.m * p.n;
 #pragma unroll
-  for (int i = 0; i < FR; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = m0 + 32 * (wm * FR + i) + 8 * (r >> 2) + 4 * half + (r & 3);
+      const int m = m0 + 32 * (wm * FM + i) + 8 * (r >> 2) + 4 * half + (r & 3);
 #pragma unroll
-      for (int j = 0; j < FR; ++j) {
-        const int n = n0 + 32 * (wn * FR + j) + l32;
+      for (int j = 0; j < FN; ++j) {
+        const int n = n0 + 32 * (wn * FN + j) + l32;
         if (m < p.m && n < p.n) out[static_cast<int64_t>(m) * p.n + n] = acc[i][j][r];
       }
     }
-  if (p.bias != nullptr && in < kBiasTiles && l32 == 0) {
-    float* row = p.bias + (static_cast<int64_t>(split) * nsum + 2 * in + wn) * p.m;
+  if (p.bias != nullptr && in < kBiasTiles) {
+    float* row = p.bias + (static_cast<int64_t>(split) * nsum + WN * in + wn) * p.m;
 #pragma unroll
-    for (int i = 0; i < FR; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + 32 * (wm * FR + i) + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (m < p.m) row[m] = sum[i][r];
-      }
+    for (int i = 0; i < FM; ++i) {
+      const float v = half_swap_sum(sum[i]);
+      const int m = m0 + 32 * (wm * FM + i) + l32;
+      if (half == 0 && m < p.m) row[m] = v;
+    }
   }
 }
 
@@ -235,39 +236,51 @@ __global__ __launch_bounds__(256) void wgrad_sum_kernel(const float4* __restrict
   }
 }
 
-// 128-wide tiles read each operand half as often, 64-wide ones need fewer
-// splits to fill the two workgroups a CU holds (512 in all) and so write fewer
-// partial results: 768 x 768 over 4096 rows, 19.7 us in 36 tiles of 128 and 13
-// splits (30 MB) with the kernel of before, 14.6 in 144 tiles of 64 and 3.
-// Splits keep at least 128 rows.
-struct WgradPlan { int tile, tm, tn, splits, chunk; };
+// The tile width, and the splits that fill the workgroups the chip holds at
+// once (one of 256 per CU, two of the others); a split keeps at least 128
+// rows. 128-wide tiles read each operand half as often as 64-wide ones, which
+// need fewer splits and so write fewer partial results: 768 x 768 over 4096
+// rows, 19.7 us in 36 tiles of 128 and 13 splits (30 MB) with the kernel of
+// before, 14.6 in 144 tiles of 64 and 3. 256-wide ones, where they number at
+// least one per CU, halve both operands' reads again: the four products of a
+// 4096-wide block with 14336 hidden and of a 2048-wide one with 8192 (2048 to
+// 4096 rows) 1739 us in 128-wide tiles, 1550 with the 256-wide ones.
+struct WgradPlan { int tile, waves_n, tm, tn, splits, chunk; };
 
-WgradPlan wgrad_plan(int rows, int m, int n) {
-  WgradPlan p;
-  const int64_t t128 = static_cast<int64_t>((m + 127) / 128) * ((n + 127) / 128);
-  p.tile = t128 >= 64 ? 128 : 64;
+WgradPlan wgrad_tiles(int m, int n) {
+  auto tiles = [&](int64_t w) { return ((m + w - 1) / w) * ((n + w - 1) / w); };
+  WgradPlan p{};
+  p.tile = tiles(256) >= 256 ? 256 : tiles(128) >= 64 ? 128 : 64;
+  p.waves_n = p.tile == 256 ? 4 : 2;
   p.tm = (m + p.tile - 1) / p.tile;
   p.tn = (n + p.tile - 1) / p.tile;
-  const int64_t tiles = static_cast<int64_t>(p.tm) * p.tn;
-  const int64_t want = std::max<int64_t>(1, 512 / tiles), room = std::max(1, rows / 128);
-  const int s = static_cast<int>(std::min(want, room));
+  return p;
+}
+
+int wgrad_splits(const WgradPlan& p, int rows) {
+  const int64_t want = (p.tile == 256 ? 256 : 512) / (static_cast<int64_t>(p.tm) * p.tn);
+  return static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, want), std::max(1, rows / 128)));
+}
+
+WgradPlan wgrad_plan(int rows, int m, int n) {
+  WgradPlan p = wgrad_tiles(m, n);
+  const int s = wgrad_splits(p, rows);
   p.chunk = std::max(64, ((rows + s - 1) / s + 63) / 64 * 64);
   p.splits = std::max(1, (rows + p.chunk - 1) / p.chunk);
   return p;
 }
 
-size_t bias_rows(const WgradPlan& p) { return static_cast<size_t>(p.splits) * 2 * std::min(p.tn, kBiasTiles); }
+size_t bias_rows(const WgradPlan& p, int splits) {
+  return static_cast<size_t>(splits) * p.waves_n * std::min(p.tn, kBiasTiles);
+}
 
 }  // namespace
 
 size_t wgrad_workspace_bytes(int max_rows, int m, int n) {
-  // the splits never fall as the rows grow past a multiple of 128, so the
-  // most any number of rows needs is bounded by the wanted splits
-  const WgradPlan p = wgrad_plan(max_rows, m, n);
-  const int64_t tiles = static_cast<int64_t>(p.tm) * p.tn;
-  const size_t s = static_cast<size_t>(std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max(1, max_rows / 128)));
-  const size_t part = s > 1 ? s * m * n : 0;
-  return (part + s * 2 * std::min(p.tn, kBiasTiles) * m) * sizeof(float);
+  // the tiles do not depend on the rows, and fewer rows never take more splits
+  const WgradPlan p = wgrad_tiles(m, n);
+  const int s = wgrad_splits(p, max_rows);
+  return ((s > 1 ? static_cast<size_t>(s) * m * n : 0) + bias_rows(p, s) * m) * sizeof(float);
 }
 
 hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int n, int rows,
@@ -275,7 +288,7 @@ hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int
   if (m == 0 || n == 0) return hipSuccess;
   const WgradPlan p = wgrad_plan(rows, m, n);
   const size_t part = p.splits > 1 ? static_cast<size_t>(p.splits) * m * n : 0;
-  const size_t brows = db != nullptr ? bias_rows(p) : 0;
+  const size_t brows = db != nullptr ? bias_rows(p, p.splits) : 0;
   if (m % 8 != 0 || n % 8 != 0 || ws_bytes < (part + brows * m) * sizeof(float)) return hipErrorInvalidValue;
   float* w = static_cast<float*>(ws);
   WgradArgs a;
@@ -291,8 +304,9 @@ hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int
   a.out = p.splits > 1 ? w : dw;
   a.bias = db != nullptr ? w + part : nullptr;
   const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(p.tm) * p.tn * p.splits + 7) / 8 * 8);
-  const hipError_t e = p.tile == 128 ? launch(K_GEMM, wgrad_kernel<128, 32, 4>, dim3(grid), dim3(256), 0, s, a)
-                                     : launch(K_GEMM, wgrad_kernel<64, 64, 4>, dim3(grid), dim3(256), 0, s, a);
+  const hipError_t e = p.tile == 256   ? launch(K_GEMM, wgrad_kernel<256, 2, 4, 32, 4>, dim3(grid), dim3(512), 0, s, a)
+                       : p.tile == 128 ? launch(K_GEMM, wgrad_kernel<128, 2, 2, 32, 4>, dim3(grid), dim3(256), 0, s, a)
+                                       : launch(K_GEMM, wgrad_kernel<64, 2, 2, 64, 4>, dim3(grid), dim3(256), 0, s, a);
   if (e != hipSuccess || (part == 0 && db == nullptr)) return e;
   const int64_t total4 = part ? static_cast<int64_t>(m) * n / 4 : 0;
   const int blocks4 = static_cast<int>((total4 + 255) / 256);

@@ -1,5 +1,5 @@
 """Weight, bias, gain and shift gradients where their kernels' shapes end: the
-product dY^T X at the edges of its 64- and 128-wide tiles, one row, rows that
+product dY^T X at the edges of its 64-, 128- and 256-wide tiles, one row, rows that
 are no multiple of a slice, several row splits, and column counts below a
 tile; the norm's column sums with one row and with more rows than workgroups;
 the compaction's scatter with rows kept at either end."""
@@ -22,6 +22,9 @@ CASES = [
     (W.ENCODER, 1, 128, 136, [700, 323], True),       # several row splits, a short last one
     (W.DECODER, 8, 128, 520, [131], False),           # 128-wide tiles: 3072 x 1024, 1040 x 1024
     (W.ENCODER, 9, 64, 2056, [300, 1, 90], True),     # 128-wide tiles with a remainder both ways
+    (W.DECODER, 9, 128, 6560, [130, 33], True),       # 256-wide tiles, remainders
+    (W.ENCODER, 33, 128, 136, [40, 5], True),         # rows shared by four waves, the widest
+    (W.DECODER, 17, 128, 72, [9], False),             # ... and the narrowest
 ]
 
 
