@@ -13,8 +13,7 @@
 //     dV = P^T dO,  dP = dO V^T,  dS = P o (dP - D),  dK = scale dS^T Q,
 //     dQ = scale dS K.
 // attn_bwd_dkdv: one workgroup per (128-key block, key/value head,
-// sequence), 32 keys per wave; the waves walk the 32-query tiles together
-// from one double-buffered LDS stage (Q and dO in rows and transposed),
+// sequence), 32 keys per wave; the waves walk the query tiles together,
 // compute S = Q K^T and dP = dO V^T in the layout where a lane owns one key,
 // and multiply P and dS, packed as MFMA A operands, with the transposed
 // tiles. Each key's dK / dV is summed by one wave in query order (no
@@ -22,7 +21,15 @@
 // query heads that read its key/value head.
 // attn_bwd_dq: one workgroup per (128-query block, head, sequence), laid out
 // like the forward attention: S^T and dP^T with a lane owning one query, dS
-// packed as the B operand of dQ^T += K^T dS^T, K^T staged in LDS.
+// packed as the B operand of dQ^T += K^T dS^T.
+// Both take tiles straight to LDS in rows, one tile ahead, and read them
+// both ways: rows with 16-byte reads, and transposed with the transposing
+// reads (bwd_swizzle serves the two without bank conflicts). Staged through
+// registers into a row and a transposed copy, the transposition was most of
+// the vector work. us, dK dV / dQ, before and now: 16 x 512 rows, 12 heads of
+// 64, 78 / 43 and 42 / 27; 2 x 2048 causal, 32 heads of 64, 248 / 90 and 194 / 57;
+// 2 x 2048 causal, 32 heads of 128 on 8 key/value heads, 695 / 535 (256
+// workgroups, one per CU, whose waves wait for one another) and 395 / 135.
 #include <math.h>
 
 #include "zsa_internal.h"
@@ -114,17 +121,30 @@ __global__ __launch_bounds__(256) void transpose64_kernel(const TransposeArgs p)
 // ---------------------------------------------------------------------------
 constexpr int kNormBwdBlocks = 512;
 
-template <int RMS, int NC>
+template <int RMS, int NC, int WPR>
 __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict__ x,
                                                        const bf16_t* __restrict__ g,
                                                        const bf16_t* __restrict__ dh, const bf16_t* res,
                                                        bf16_t* out, int R, int d, float eps,
                                                        float* __restrict__ part) {
-  // lane owns the 8-column chunks lane, lane + 64, ... (NC of them, d <= NC *
-  // 512); rows stay packed in registers across the passes, chunks past d zero
-  constexpr int NS = RMS ? 1 : 2;
+  // a wave of a row's WPR owns 8-column chunks lane, lane + 64 WPR, ... (NC of
+  // them, d <= NC * WPR * 512); rows stay packed in registers across the
+  // passes, chunks past d zero
+  constexpr int NS = RMS ? 1 : 2, RPB = 4 / WPR;  // rows per workgroup and pass
   __shared__ float red[4][NS][512];
+  __shared__ float wsum[4][4];  // a row's sums by wave: x, (x - mean)^2, g dh, g dh xhat
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int sub = WPR == 1 ? 0 : wave;
+  auto col = [&](int k) { return ((k * WPR + sub) * 64 + lane) * 8; };
+  // sums a wave's value over the row (all waves of a row get here together)
+  auto row_sum = [&](float v, int slot, bool wait) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (WPR == 1) return v;
+    if (lane == 0) wsum[slot][wave] = v;
+    if (!wait) return 0.f;
+    __syncthreads();
+    return wsum[slot][0] + wsum[slot][1] + wsum[slot][2] + wsum[slot][3];
+  };
   const u32x4 none = {0u, 0u, 0u, 0u};
   auto unpack = [](const u32x4& v, int e) {
     const uint32_t w = v[e >> 1];
@@ -134,54 +154,47 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict_
   float gs[NC][8], bs[NC][8];
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
-    const int c = (k * 64 + lane) * 8;
+    const int c = col(k);
     gv[k] = c < d ? *reinterpret_cast<const u32x4*>(g + c) : none;
 #pragma unroll
     for (int e = 0; e < 8; ++e) gs[k][e] = bs[k][e] = 0.f;
   }
   // the next row's loads are in flight while this one is worked on
-  constexpr bool ahead = NC <= 8;
-  constexpr int NN = ahead ? NC : 1;
-  u32x4 xn[NN], dn[NN];
-  const int step = 4 * static_cast<int>(gridDim.x);
+  u32x4 xn[NC], dn[NC];
+  const int step = RPB * static_cast<int>(gridDim.x);
   auto fetch = [&](int row, u32x4* xr, u32x4* dr) {
     const int64_t base = static_cast<int64_t>(row) * d;
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
-      const int c = (k * 64 + lane) * 8;
+      const int c = col(k);
       xr[k] = c < d && row < R ? *reinterpret_cast<const u32x4*>(x + base + c) : none;
       dr[k] = c < d && row < R ? *reinterpret_cast<const u32x4*>(dh + base + c) : none;
     }
   };
-  int row = static_cast<int>(blockIdx.x) * 4 + wave;
-  if constexpr (ahead) fetch(row, xn, dn);
+  int row = static_cast<int>(blockIdx.x) * RPB + (WPR == 1 ? wave : 0);
+  fetch(row, xn, dn);
   for (; row < R; row += step) {
     const int64_t base = static_cast<int64_t>(row) * d;
     u32x4 xv[NC], dv[NC];
     float s = 0.f;
-    if constexpr (ahead) {
 #pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        xv[k] = xn[k];
-        dv[k] = dn[k];
-      }
-      fetch(row < R - step ? row + step : R, xn, dn);
-    } else {
-      fetch(row, xv, dv);
+    for (int k = 0; k < NC; ++k) {
+      xv[k] = xn[k];
+      dv[k] = dn[k];
     }
+    fetch(row < R - step ? row + step : R, xn, dn);
     float mean = 0.f;
     if (!RMS) {
 #pragma unroll
       for (int k = 0; k < NC; ++k)
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += unpack(xv[k], e);
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      mean = s / d;
+      mean = row_sum(s, 0, true) / d;
     }
     float ss = 0.f;
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
-      if ((k * 64 + lane) * 8 < d) {
+      if (col(k) < d) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float v = unpack(xv[k], e) - mean;
@@ -189,7 +202,7 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict_
         }
       }
     }
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    ss = row_sum(ss, 1, true);
     const float rstd = 1.0f / sqrtf(ss / d + eps);
     float s1 = 0.f, s2 = 0.f;  // sum(g dh), sum(g dh xhat)
 #pragma unroll
@@ -202,14 +215,13 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict_
         gs[k][e] += h * xh;
         if (!RMS) bs[k][e] += h;
       }
-    for (int o = 32; o > 0; o >>= 1) {
-      s1 += __shfl_xor(s1, o, 64);
-      s2 += __shfl_xor(s2, o, 64);
-    }
+    s1 = row_sum(s1, 2, false);
+    s2 = row_sum(s2, 3, true);
+    if (WPR > 1) s1 = wsum[2][0] + wsum[2][1] + wsum[2][2] + wsum[2][3];
     const float m1 = RMS ? 0.f : s1 / d, m2 = s2 / d;
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
-      const int c = (k * 64 + lane) * 8;
+      const int c = col(k);
       if (c < d) {
         float o[8], rv[8];
         if (res != nullptr) load8<bf16_t>(res + base + c, rv);
@@ -223,6 +235,19 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict_
     }
   }
   float* prow = part + static_cast<int64_t>(blockIdx.x) * NS * d;
+  if constexpr (WPR > 1) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const int c = col(k);
+      if (c >= d) continue;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        prow[c + e] = gs[k][e];
+        if (!RMS) prow[d + c + e] = bs[k][e];
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     if (k > 0) __syncthreads();
@@ -325,44 +350,49 @@ __global__ __launch_bounds__(256) void act_bwd_kernel(const bf16_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// undo compaction of two arrays: dst[kept[i]] = src[i], zeros elsewhere. kept
-// ascends, so wave i clears the rows between kept[i - 1] and kept[i] and
-// copies row i; the last one (i = t_out) clears the rest. An inverse index
-// (filled, then written, then read by one scatter per array) took six
-// launches, 21 us for 8192 rows of 768; this one 17.
+// undo compaction of two arrays: dst[kept[i]] = src[i], zeros elsewhere. A wave
+// takes a row of dst and looks it up in kept, which ascends, 64 entries at a
+// time (two steps up to 4096 kept rows). An inverse index (filled, then
+// written, then read by one scatter per array) took six launches, 21 us for
+// 8192 rows of 768; this one 8. (A wave per kept row that also clears the
+// dropped rows before it was as fast there, but 97 us a layer where long runs
+// of rows are dropped.)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void scatter_rows_kernel(const u32x4* __restrict__ src0, u32x4* __restrict__ dst0,
                                                            const u32x4* __restrict__ src1, u32x4* __restrict__ dst1,
                                                            const int32_t* __restrict__ kept, int t_out, int t_in,
                                                            int cpr) {
   const int lane = threadIdx.x & 63;
-  const int i = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
-  if (i > t_out) return;
-  const int prev = i == 0 ? -1 : kept[i - 1], here = i == t_out ? t_in : kept[i];
-  const int64_t from = static_cast<int64_t>(max(prev, -1) + 1) * cpr, to = static_cast<int64_t>(min(here, t_in)) * cpr;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  if (here >= 0 && here < t_in) {
-    const int64_t at = static_cast<int64_t>(i) * cpr;
-#pragma unroll 2
-    for (int c = lane; c < cpr; c += 64) {
-      const u32x4 v0 = src0[at + c], v1 = src1[at + c];
-      dst0[to + c] = v0;
-      dst1[to + c] = v1;
-    }
+  const int r = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x >> 6));
+  if (r >= t_in) return;
+  int lo = 0, len = t_out;
+  while (len > 64) {
+    const int stride = (len + 63) / 64;
+    const int64_t i = static_cast<int64_t>(lane + 1) * stride - 1;
+    const bool below = i < len && kept[lo + i] < r;
+    const int c = __popcll(__builtin_amdgcn_ballot_w64(below));
+    lo += c * stride;
+    len = min(stride, len - c * stride);
   }
-  for (int64_t c = from + lane; c < to; c += 64) {
-    dst0[c] = zero;
-    dst1[c] = zero;
+  const uint64_t hit = __builtin_amdgcn_ballot_w64(lane < len && kept[lo + min(lane, max(len - 1, 0))] == r);
+  const int64_t at = hit != 0 ? static_cast<int64_t>(lo + __builtin_ctzll(hit)) * cpr : -1;
+  const int64_t to = static_cast<int64_t>(r) * cpr;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll 2
+  for (int c = lane; c < cpr; c += 64) {
+    dst0[to + c] = at >= 0 ? src0[at + c] : zero;
+    dst1[to + c] = at >= 0 ? src1[at + c] : zero;
   }
 }
 
-// D[h][r] = sum_c dO[r][h hd + c] O[r][h hd + c]: each thread takes 8
-// consecutive columns, the L = hd / 8 threads of one head (L a power of two
-// up to 64, adjacent lanes of one wave) add theirs in a fixed butterfly
-template <typename T>
-__global__ __launch_bounds__(256) void rowdot_kernel(const T* __restrict__ dO,
-                                                     const T* __restrict__ O, int64_t ld, int T_,
-                                                     int H, int hd, float* __restrict__ D) {
+// LD[h][r] = (lse[h][r] log2 e, D) with D = sum_c dO[r][h hd + c] O[r][h hd +
+// c]: each thread takes 8 consecutive columns, the L = hd / 8 threads of one
+// head (L a power of two up to 64, adjacent lanes of one wave) add theirs in a
+// fixed butterfly
+__global__ __launch_bounds__(256) void rowdot_kernel(const bf16_t* __restrict__ dO,
+                                                     const bf16_t* __restrict__ O, int64_t ld, int T_,
+                                                     int H, int hd, const float* __restrict__ lse,
+                                                     float2* __restrict__ LD) {
   const int L = hd / 8, per_row = H * L;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const bool live = i < static_cast<int64_t>(T_) * per_row;
@@ -371,15 +401,18 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const T* __restrict__ dO,
   float s = 0.f;
   if (live) {
     float va[8], vb[8];
-    load8<T>(dO + static_cast<int64_t>(r) * ld + c8 * 8, va);
-    load8<T>(O + static_cast<int64_t>(r) * ld + c8 * 8, vb);
+    load8<bf16_t>(dO + static_cast<int64_t>(r) * ld + c8 * 8, va);
+    load8<bf16_t>(O + static_cast<int64_t>(r) * ld + c8 * 8, vb);
 #pragma unroll
     for (int e = 0; e < 8; ++e) s = fmaf(va[e], vb[e], s);
   }
   // groups of L lanes start at multiples of L within the wave (64 % L == 0
   // and each block is 256 threads), so the butterfly stays inside one head
   for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
-  if (live && (c8 & (L - 1)) == 0) D[static_cast<int64_t>(c8 / L) * T_ + r] = s;
+  if (live && (c8 & (L - 1)) == 0) {
+    const int64_t at = static_cast<int64_t>(c8 / L) * T_ + r;
+    LD[at] = make_float2(lse[at] * kLog2e, s);
+  }
 }
 
 // inverse rotary rotation of the gradient, in place, on the first `cols`
@@ -405,354 +438,333 @@ __global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, int64_
 }
 
 // ---------------------------------------------------------------------------
-// attention backward, dK and dV
+// attention backward
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float pick4(const float4& v, int i) {
-  return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) const char lds_char;
+
+// Tile row r keeps its 16-byte chunk c at c ^ swizzle(r). The 16 rows of a
+// row read's phase fall on all 64 banks, and so do the four rows r .. r + 3
+// (r a multiple of four) by four chunks of a transposing read's.
+template <int HD>
+__device__ __forceinline__ constexpr int bwd_swizzle(int r) {
+  return HD == 64 ? ((r >> 1) & 1) << 2 | ((r >> 2) & 1) << 1 | ((r >> 3) & 1) : (r & 3) << 2 | ((r >> 2) & 3);
 }
 
-// Each workgroup owns 128 consecutive keys of one kv head, 32 per wave. The
-// waves sweep the query tiles of 32 together: each tile of Q and dO (with
-// the rows' log-sum-exp and D) is staged once per workgroup into LDS, in
-// rows (the A operands of S = Q K^T and dP = dO V^T) and transposed (the B
-// operands of dV += P^T dO and dK += dS^T Q), double-buffered so the next
-// tile's global loads overlap this tile's MFMAs. P and dS leave the
-// accumulators with the keys on the lanes and the queries in the registers,
-// so they are the A operands of the dV and dK products as they are; each
-// wave keeps its keys' dK and dV and writes them once.
+__device__ __forceinline__ u32x4 buffer_resource(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
+                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
+                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
+  return r;
+}
+
+// The reading side of a tile of HD-wide rows: a lane's offsets of the row
+// fragment of channels 16 kk .. (row l32, channels 16 kk + 8 half + 0 .. 7)
+// and of the transposed fragment of channels 32 ct .. (channel 32 ct + l32,
+// rows 4 half + 0 .. 3 and these + 8)
 template <int HD>
-__global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    int64_t rs, const bf16_t* __restrict__ dO, int64_t ors, const float* __restrict__ lse,
-    const float* __restrict__ Dv, int T, int kv_group, int causal, float scale,
-    float scale_log2, const int32_t* __restrict__ cu, bf16_t* __restrict__ dK,
-    bf16_t* __restrict__ dV, int64_t grs) {
-  constexpr int KW = 128, QT = 32;
-  constexpr int KK = HD / 16, CT = HD / 32;
-  constexpr int RLD = HD + 8;            // row tile stride (bf16)
-  constexpr int TLD = QT + 4;            // transposed tile stride (bf16), 18 dwords
-  constexpr int ROW_E = QT * RLD, TR_E = HD * TLD;
-  constexpr int BUF = 4 * ROW_E + 4 * TR_E + 2 * QT * 4;  // bytes of one stage
-  constexpr int TASKS = 2 * (QT / 2) * (HD / 8);          // (tensor, query pair, chunk)
-  constexpr int NT = TASKS / 256;
-  static_assert(NT >= 1 && NT * 256 == TASKS, "staging tasks must fill the block");
-  static_assert(BUF % 16 == 0, "stage size");
-  static_assert(8 * 32 * RLD * 2 <= 2 * BUF, "output staging fits the stages");
-  __shared__ __align__(16) unsigned char smem[2 * BUF];
-
-  const int b = blockIdx.z, g = blockIdx.y;
-  const int lo = cu[b];
-  const int n = cu[b + 1] - lo;
-  const int j0 = blockIdx.x * KW;
-  if (j0 >= n) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
-  const int jw = j0 + wave * 32;  // the wave's first key
-  const bool wave_live = jw < n;
-
-  bf16x8_t kf[KK], vf[KK];
-  {
-    const int jr = lo + min(jw + l32, n - 1);
+struct TileReads {
+  static constexpr int RB = HD * 2, KK = HD / 16, CT = HD / 32;
+  uint32_t row[KK], lo[CT], hi[CT];
+  __device__ __forceinline__ explicit TileReads(int lane) {
+    const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                K + static_cast<int64_t>(jr) * rs + g * HD + kk * 16 + half * 8));
-      vf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                V + static_cast<int64_t>(jr) * rs + g * HD + kk * 16 + half * 8));
+    for (int kk = 0; kk < KK; ++kk) row[kk] = l32 * RB + (((2 * kk + half) ^ bwd_swizzle<HD>(l32)) << 4);
+    // a transposing read gives each lane of a 16-lane group element (its
+    // number in the group) of four 16-element rows, row r pieced together
+    // from the runs at the addresses of the group's lanes 4r .. 4r + 3
+    const int r = 4 * half + ((lane & 15) >> 2), ch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      lo[ct] = r * RB + (((4 * ct + ch) ^ bwd_swizzle<HD>(r)) << 4) + (lane & 1) * 8;
+      hi[ct] = (r + 8) * RB + (((4 * ct + ch) ^ bwd_swizzle<HD>(r + 8)) << 4) + (lane & 1) * 8;
     }
   }
-  f32x16_t dk[CT], dv[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      dk[ct][r] = 0.f;
-      dv[ct][r] = 0.f;
-    }
+  __device__ __forceinline__ bf16x8_t rows(const unsigned char* tile, int kk) const {
+    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(tile + row[kk]));
+  }
+  // tile rows 16 g + ...
+  __device__ __forceinline__ bf16x8_t cols(const unsigned char* tile, int g, int ct) const {
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(tile + lo[ct] + g * (16 * RB))));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(tile + hi[ct] + g * (16 * RB))));
+    const uint2 a2 = __builtin_bit_cast(uint2, a), b2 = __builtin_bit_cast(uint2, b);
+    const u32x4 v = {a2.x, a2.y, b2.x, b2.y};
+    return __builtin_bit_cast(bf16x8_t, v);
+  }
+};
 
+__device__ __forceinline__ bf16x8_t pack_slots(const f32x16_t& v, int g) {
+  const int r = 8 * g;
+  const u32x4 w = {pack_bf16x2(v[r], v[r + 1]), pack_bf16x2(v[r + 2], v[r + 3]), pack_bf16x2(v[r + 4], v[r + 5]),
+                   pack_bf16x2(v[r + 6], v[r + 7])};
+  return __builtin_bit_cast(bf16x8_t, w);
+}
+
+// every wave's tile loads have landed, and all waves are past the last tile
+__device__ __forceinline__ void bwd_turn_over() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Rows per tile: 64 at head dim 64, 32 at 128 (8 KB an operand either way),
+// two tiles in LDS. Loads are asm without outputs: the compiler would wait
+// for a load it knows to write LDS before any later LDS read. (m0 is set by
+// the compiler right before each use of its own.)
+#define ZSA_LDS_LOAD(width, lds, off, res)                                                              \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_" width " %1, %2, 0 offen lds" ::"s"(lds), \
+               "v"(off), "s"(res)                                                                       \
+               : "memory")
+
+template <int HD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void attn_bwd_dkdv_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    int64_t rs, const bf16_t* __restrict__ dO, int64_t ors, const float2* __restrict__ LD, int T,
+    int Hkv, int kv_group, int causal, float scale, float scale_log2, const int32_t* __restrict__ cu,
+    bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int64_t grs, int pairs) {
+  constexpr int KW = 128, QT = HD == 64 ? 64 : 32;
+  constexpr int KK = HD / 16, CT = HD / 32, CPR = HD / 8, RB = HD * 2, OLD = HD + 8;
+  constexpr int TB = QT * RB, BUF = 2 * TB + 1024;  // Q, dO, (lse, D) pairs
+  constexpr int RPL = 1024 / RB, LPW = TB / 4096;   // rows per load, loads per wave and operand
+  constexpr int SBYTES = 2 * BUF > 8 * 32 * OLD * 2 ? 2 * BUF : 8 * 32 * OLD * 2;
+  static_assert(LPW * 4096 == TB, "tile split");
+  __shared__ __align__(1024) unsigned char smem[SBYTES];
+
+  Place at;
+  if (!place(Hkv, pairs, true, &at)) return;
+  const int b = at.b, g = at.h;
+  const int lo = cu[b];
+  const int n = cu[b + 1] - lo;
+  const int j0 = at.i * KW;
+  if (j0 >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int jw = j0 + wave * 32;  // the wave's first key
+
+  const uint32_t q_row = static_cast<uint32_t>(rs * 2), o_row = static_cast<uint32_t>(ors * 2);
+  const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
+  const uint32_t lchunk = ((lane % CPR) ^ bwd_swizzle<HD>(lrow)) << 4;
+  const uint32_t qoff = lrow * q_row + lchunk, ooff = lrow * o_row + lchunk;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem));
   // queries before the first key see none of the keys (causal)
   const int qs = causal ? j0 : 0;
   const int ntile = (n - qs + QT - 1) / QT;
   const int rounds = ntile * kv_group;
-
-  u32x4 st[NT][2];
-  float stl = 0.f;
-  auto fetch = [&](int t) {
+  // rows past the sequence read as zeros (masked)
+  auto load_tile = [&](int t, int buf) {
     const int e = t / ntile, i0 = qs + (t - e * ntile) * QT, h = g * kv_group + e;
+    const u32x4 qres = buffer_resource(Q + static_cast<int64_t>(lo) * rs + h * HD, static_cast<uint32_t>(n) * q_row);
+    const u32x4 ores = buffer_resource(dO + static_cast<int64_t>(lo) * ors + h * HD, static_cast<uint32_t>(n) * o_row);
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const int task = tid + 256 * k;
-      const int tensor = task / (TASKS / 2), rem = task % (TASKS / 2);
-      const int rp = rem / (HD / 8), ch = (rem % (HD / 8)) * 8;
-      const int r0 = lo + min(i0 + 2 * rp, n - 1), r1 = lo + min(i0 + 2 * rp + 1, n - 1);
-      const bf16_t* src = tensor ? dO : Q;
-      const int64_t ld = tensor ? ors : rs;
-      st[k][0] = *reinterpret_cast<const u32x4*>(src + static_cast<int64_t>(r0) * ld + h * HD + ch);
-      st[k][1] = *reinterpret_cast<const u32x4*>(src + static_cast<int64_t>(r1) * ld + h * HD + ch);
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t d = lds0 + buf * BUF + wave * 1024 + i * 4096;
+      ZSA_LDS_LOAD("dwordx4", d, qoff + static_cast<uint32_t>(i0 + i * 4 * RPL) * q_row, qres);
+      ZSA_LDS_LOAD("dwordx4", d + TB, ooff + static_cast<uint32_t>(i0 + i * 4 * RPL) * o_row, ores);
     }
-    if (tid < 2 * QT) {
-      const int64_t i = static_cast<int64_t>(h) * T + lo + min(i0 + (tid & (QT - 1)), n - 1);
-      stl = tid < QT ? lse[i] * kLog2e : Dv[i];
+    if (wave < QT / 32) {
+      const u32x4 lres = buffer_resource(LD + static_cast<int64_t>(h) * T + lo, static_cast<uint32_t>(n) * 8u);
+      ZSA_LDS_LOAD("dword", lds0 + buf * BUF + 2 * TB + wave * 256, static_cast<uint32_t>(i0) * 8u + (wave * 64 + lane) * 4u,
+                   lres);
     }
   };
-  auto stash = [&](int buf) {
-    bf16_t* rowQ = reinterpret_cast<bf16_t*>(smem + buf * BUF);
-    bf16_t* trQ = rowQ + 2 * ROW_E;
-    float* LD = reinterpret_cast<float*>(trQ + 2 * TR_E);
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const int task = tid + 256 * k;
-      const int tensor = task / (TASKS / 2), rem = task % (TASKS / 2);
-      const int rp = rem / (HD / 8), ch = (rem % (HD / 8)) * 8;
-      bf16_t* rw = rowQ + tensor * ROW_E;
-      bf16_t* tr = trQ + tensor * TR_E;
-      *reinterpret_cast<u32x4*>(rw + (2 * rp) * RLD + ch) = st[k][0];
-      *reinterpret_cast<u32x4*>(rw + (2 * rp + 1) * RLD + ch) = st[k][1];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const uint32_t a0 = st[k][0][c >> 1], a1 = st[k][1][c >> 1];
-        const uint32_t lo16 = (c & 1) ? (a0 >> 16) : (a0 & 0xffffu);
-        const uint32_t hi16 = (c & 1) ? (a1 & 0xffff0000u) : (a1 << 16);
-        *reinterpret_cast<uint32_t*>(tr + (ch + c) * TLD + 2 * rp) = lo16 | hi16;
-      }
-    }
-    if (tid < 2 * QT) LD[tid] = stl;
-  };
+  load_tile(0, 0);
 
-  fetch(0);
-  stash(0);
-  __syncthreads();
+  bf16x8_t kf[KK], vf[KK];
+  {
+    // keys past the sequence repeat its last row; they are not written
+    const int64_t at_row = static_cast<int64_t>(lo + min(jw + l32, n - 1)) * rs + g * HD + half * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      kf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(K + at_row + kk * 16));
+      vf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(V + at_row + kk * 16));
+    }
+  }
+  f32x16_t dk[CT] = {}, dv[CT] = {};
+  const TileReads<HD> rd(lane);
+  const f32x16_t zero = {};
   for (int t = 0; t < rounds; ++t) {
-    if (t + 1 < rounds) fetch(t + 1);
-    const int e = t / ntile, i0 = qs + (t - e * ntile) * QT;
-    // a wave whose keys all lie past this tile's last query sees none of it
-    if (wave_live && !(causal && jw > i0 + QT - 1)) {
-      const bf16_t* rowQ = reinterpret_cast<const bf16_t*>(smem + (t & 1) * BUF);
-      const bf16_t* rowD = rowQ + ROW_E;
-      const bf16_t* trQ = rowQ + 2 * ROW_E;
-      const bf16_t* trD = trQ + TR_E;
-      const float* LD = reinterpret_cast<const float*>(trQ + 2 * TR_E);
+    bwd_turn_over();
+    if (t + 1 < rounds) load_tile(t + 1, (t + 1) & 1);
+    const int i_tile = qs + (t % ntile) * QT;
+    const unsigned char* tq = smem + (t & 1) * BUF;
+#pragma unroll 1
+    for (int u = 0; u < QT / 32; ++u) {
+      const int i0 = i_tile + 32 * u;
+      // steps past the sequence, and a wave whose keys all lie past the sequence or the step's last query
+      if (i0 >= n || jw >= n || (causal && jw > i0 + 31)) continue;
+      const unsigned char *uq = tq + u * (32 * RB), *ud = uq + TB;
+      const float4* lp = reinterpret_cast<const float4*>(tq + 2 * TB) + 16 * u + 2 * half;
       f32x16_t s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = 0.f;
-        dp[r] = 0.f;
-      }
-#pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        const bf16x8_t qa = __builtin_bit_cast(
-            bf16x8_t, *reinterpret_cast<const u32x4*>(rowQ + l32 * RLD + kk * 16 + half * 8));
-        const bf16x8_t da = __builtin_bit_cast(
-            bf16x8_t, *reinterpret_cast<const u32x4*>(rowD + l32 * RLD + kk * 16 + half * 8));
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, vf[kk], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd.rows(uq, kk), kf[kk], kk == 0 ? zero : s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd.rows(ud, kk), vf[kk], kk == 0 ? zero : dp, 0, 0, 0);
       }
-      // s[r], dp[r]: query i0 + 8 (r/4) + 4 half + r%4, key jw + l32. Keys
-      // past the sequence only feed accumulator rows that are not written.
-      const int j = jw + l32;
-      const bool edge = i0 + QT > n || (causal && jw + 31 > i0);
+      // s[r], dp[r]: query i0 + 8 (r/4) + 4 half + r%4, key jw + l32
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const float4 L4 = *reinterpret_cast<const float4*>(LD + 8 * a + 4 * half);
-        const float4 D4 = *reinterpret_cast<const float4*>(LD + QT + 8 * a + 4 * half);
+      for (int a = 0; a < 8; ++a) {
+        const float4 w = lp[4 * (a >> 1) + (a & 1)];  // (lse, D) of queries 8 (a/2) + 4 half + 2 (a%2) and the next
+        const int r = 2 * a;
+        s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -w.x));
+        s[r + 1] = __builtin_amdgcn_exp2f(fmaf(s[r + 1], scale_log2, -w.z));
+        dp[r] -= w.y;
+        dp[r + 1] -= w.w;
+      }
+      if (i0 + 32 > n || (causal && jw + 31 > i0)) {
+        // queries from first on (and before n) see the key
+        const int first = (causal ? jw + l32 : 0) - i0 - 4 * half, last = n - i0 - 4 * half;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * a + q;
-          float p = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -pick4(L4, q)));
-          if (edge) {
-            const int i = i0 + 8 * a + 4 * half + q;
-            if (i >= n || (causal && j > i)) p = 0.f;
-          }
-          s[r] = p;
-          dp[r] = p * (dp[r] - pick4(D4, q));
+        for (int r = 0; r < 16; ++r) {
+          const int q = 8 * (r >> 2) + (r & 3);
+          if (q < first || q >= last) s[r] = 0.f;
         }
       }
 #pragma unroll
-      for (int g4 = 0; g4 < 2; ++g4) {
-        const int rb = 8 * g4;
-        const u32x4 pw = {pack_bf16x2(s[rb], s[rb + 1]), pack_bf16x2(s[rb + 2], s[rb + 3]),
-                          pack_bf16x2(s[rb + 4], s[rb + 5]), pack_bf16x2(s[rb + 6], s[rb + 7])};
-        const u32x4 sw = {pack_bf16x2(dp[rb], dp[rb + 1]), pack_bf16x2(dp[rb + 2], dp[rb + 3]),
-                          pack_bf16x2(dp[rb + 4], dp[rb + 5]), pack_bf16x2(dp[rb + 6], dp[rb + 7])};
-        const bf16x8_t pa = __builtin_bit_cast(bf16x8_t, pw);
-        const bf16x8_t sa = __builtin_bit_cast(bf16x8_t, sw);
-        const int base = 16 * g4 + 4 * half;  // queries base..+3, base+8..+11
+      for (int r = 0; r < 16; ++r) dp[r] *= s[r];
+#pragma unroll
+      for (int gg = 0; gg < 2; ++gg) {
+        const bf16x8_t pa = pack_slots(s, gg), sa = pack_slots(dp, gg);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          const bf16_t* dr = trD + (ct * 32 + l32) * TLD + base;
-          const bf16_t* qrw = trQ + (ct * 32 + l32) * TLD + base;
-          const uint2 d_lo = *reinterpret_cast<const uint2*>(dr);
-          const uint2 d_hi = *reinterpret_cast<const uint2*>(dr + 8);
-          const uint2 q_lo = *reinterpret_cast<const uint2*>(qrw);
-          const uint2 q_hi = *reinterpret_cast<const uint2*>(qrw + 8);
-          const u32x4 bd = {d_lo.x, d_lo.y, d_hi.x, d_hi.y};
-          const u32x4 bq = {q_lo.x, q_lo.y, q_hi.x, q_hi.y};
-          dv[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, __builtin_bit_cast(bf16x8_t, bd),
-                                                           dv[ct], 0, 0, 0);
-          dk[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa, __builtin_bit_cast(bf16x8_t, bq),
-                                                           dk[ct], 0, 0, 0);
+          dv[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, rd.cols(ud, gg, ct), dv[ct], 0, 0, 0);
+          dk[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa, rd.cols(uq, gg, ct), dk[ct], 0, 0, 0);
         }
       }
     }
-    if (t + 1 < rounds) stash((t + 1) & 1);
-    __syncthreads();
   }
+  __syncthreads();
   // acc[ct][r]: key jw + 8 (r/4) + 4 half + r%4, channel ct*32 + l32; staged
   // as bf16 rows in LDS (the wave's own region), then written 16 bytes a lane
-  bf16_t* ov = reinterpret_cast<bf16_t*>(smem) + wave * 2 * 32 * RLD;
-  bf16_t* okk = ov + 32 * RLD;
+  bf16_t* ov = reinterpret_cast<bf16_t*>(smem) + wave * 2 * 32 * OLD;
+  bf16_t* ok = ov + 32 * OLD;
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = 8 * (r >> 2) + 4 * half + (r & 3);
-      ov[key * RLD + ct * 32 + l32] = f32_to_bf16(dv[ct][r]);
-      okk[key * RLD + ct * 32 + l32] = f32_to_bf16(dk[ct][r] * scale);
+      ov[key * OLD + ct * 32 + l32] = f32_to_bf16(dv[ct][r]);
+      ok[key * OLD + ct * 32 + l32] = f32_to_bf16(dk[ct][r] * scale);
     }
   __syncthreads();
-  for (int c = lane; c < 32 * (HD / 8); c += 64) {
-    const int key = c / (HD / 8), ch = (c % (HD / 8)) * 8;
+  for (int c = lane; c < 32 * CPR; c += 64) {
+    const int key = c / CPR, ch = (c % CPR) * 8;
     if (jw + key >= n) continue;
     const int64_t o = static_cast<int64_t>(lo + jw + key) * grs + g * HD + ch;
-    *reinterpret_cast<u32x4*>(dV + o) = *reinterpret_cast<const u32x4*>(ov + key * RLD + ch);
-    *reinterpret_cast<u32x4*>(dK + o) = *reinterpret_cast<const u32x4*>(okk + key * RLD + ch);
+    *reinterpret_cast<u32x4*>(dV + o) = *reinterpret_cast<const u32x4*>(ov + key * OLD + ch);
+    *reinterpret_cast<u32x4*>(dK + o) = *reinterpret_cast<const u32x4*>(ok + key * OLD + ch);
   }
 }
 
-// ---------------------------------------------------------------------------
-// attention backward, dQ
-// ---------------------------------------------------------------------------
 template <int HD>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    int64_t rs, const bf16_t* __restrict__ dO, int64_t ors, const float* __restrict__ lse,
-    const float* __restrict__ Dv, int T, int kv_group, int causal, float scale, float scale_log2,
-    const int32_t* __restrict__ cu, bf16_t* __restrict__ dQ, int64_t grs) {
-  constexpr int BQ = 128, BKEY = 64;
-  constexpr int KLD = HD + 8, TLD = BKEY + 8, OLD = HD + 8;
-  constexpr int KK = HD / 16, CT = HD / 32;
-  constexpr int KB = BKEY * KLD * 2, TB = HD * TLD * 2;
-  constexpr int SMEM = 2 * KB + TB > 4 * 32 * OLD * 2 ? 2 * KB + TB : 4 * 32 * OLD * 2;
-  __shared__ __align__(16) unsigned char smem[SMEM];
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem);
-  bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + KB);
-  bf16_t* Kt = reinterpret_cast<bf16_t*>(smem + 2 * KB);
+    int64_t rs, const bf16_t* __restrict__ dO, int64_t ors, const float2* __restrict__ LD, int T, int H,
+    int kv_group, int causal, float scale, float scale_log2, const int32_t* __restrict__ cu,
+    bf16_t* __restrict__ dQ, int64_t grs, int pairs) {
+  constexpr int BQ = 128, KT = HD == 64 ? 64 : 32;
+  constexpr int KK = HD / 16, CT = HD / 32, CPR = HD / 8, RB = HD * 2, OLD = HD + 8;
+  constexpr int TB = KT * RB, BUF = 2 * TB;        // K, V
+  constexpr int RPL = 1024 / RB, LPW = TB / 4096;  // rows per load, loads per wave and operand
+  constexpr int SBYTES = 2 * BUF > 4 * 32 * OLD * 2 ? 2 * BUF : 4 * 32 * OLD * 2;
+  static_assert(LPW * 4096 == TB, "tile split");
+  __shared__ __align__(1024) unsigned char smem[SBYTES];
 
-  const int b = blockIdx.z, h = blockIdx.y;
+  Place at;
+  if (!place(H, pairs, false, &at)) return;
+  const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
-  const int q0 = blockIdx.x * BQ;
+  const int q0 = at.i * BQ;
   if (q0 >= n) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, l32 = lane & 31;
-  const int qrow = q0 + wave * 32 + l32;
-  const int qr = lo + min(qrow, n - 1);
-  const int hk = h / kv_group;
+  const int wq0 = q0 + wave * 32, hk = h / kv_group;
+
+  const uint32_t row_bytes = static_cast<uint32_t>(rs * 2);
+  const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
+  const uint32_t off = lrow * row_bytes + (((lane % CPR) ^ bwd_swizzle<HD>(lrow)) << 4);
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
+  // keys past the sequence read as zeros (masked)
+  const u32x4 kres = buffer_resource(K + static_cast<int64_t>(lo) * rs + hk * HD, static_cast<uint32_t>(n) * row_bytes);
+  const u32x4 vres = buffer_resource(V + static_cast<int64_t>(lo) * rs + hk * HD, static_cast<uint32_t>(n) * row_bytes);
+  auto load_tile = [&](int t, int buf) {
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const uint32_t d = lds0 + buf * BUF + i * 4096, o = off + static_cast<uint32_t>(t * KT + i * 4 * RPL) * row_bytes;
+      ZSA_LDS_LOAD("dwordx4", d, o, kres);
+      ZSA_LDS_LOAD("dwordx4", d + TB, o, vres);
+    }
+  };
+  load_tile(0, 0);
+
+  // queries past the sequence repeat its last row; they are not written
+  const int64_t qr = lo + min(wq0 + l32, n - 1);
   bf16x8_t qf[KK], df[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    qf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                              Q + static_cast<int64_t>(qr) * rs + h * HD + kk * 16 + half * 8));
-    df[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                              dO + static_cast<int64_t>(qr) * ors + h * HD + kk * 16 + half * 8));
+    qf[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(Q + qr * rs + h * HD + kk * 16 + half * 8));
+    df[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(dO + qr * ors + h * HD + kk * 16 + half * 8));
   }
-  const float Lq = lse[static_cast<int64_t>(h) * T + qr] * kLog2e;
-  const float Dq = Dv[static_cast<int64_t>(h) * T + qr];
-  f32x16_t acc[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[ct][r] = 0.f;
-
+  const float2 ld = LD[static_cast<int64_t>(h) * T + qr];
+  f32x16_t acc[CT] = {};
+  const TileReads<HD> rd(lane);
+  const f32x16_t zero = {};
   const int kend = causal ? min(n, q0 + BQ) : n;
-  const int wave_q0 = q0 + wave * 32;
-  for (int j0 = 0; j0 < kend; j0 += BKEY) {
-    __syncthreads();
-    for (int c = tid; c < BKEY * HD / 8; c += 256) {
-      const int r = c / (HD / 8), ch = (c % (HD / 8)) * 8;
-      const int64_t row = lo + min(j0 + r, n - 1);
-      *reinterpret_cast<u32x4*>(Ks + r * KLD + ch) =
-          *reinterpret_cast<const u32x4*>(K + row * rs + hk * HD + ch);
-      *reinterpret_cast<u32x4*>(Vs + r * KLD + ch) =
-          *reinterpret_cast<const u32x4*>(V + row * rs + hk * HD + ch);
-    }
-    // K^T with key pairs packed
-    for (int c = tid; c < (BKEY / 2) * (HD / 8); c += 256) {
-      const int rp = c / (HD / 8), ch = (c % (HD / 8)) * 8;
-      const int64_t r0 = lo + min(j0 + 2 * rp, n - 1), r1 = lo + min(j0 + 2 * rp + 1, n - 1);
-      const u32x4 k0 = *reinterpret_cast<const u32x4*>(K + r0 * rs + hk * HD + ch);
-      const u32x4 k1 = *reinterpret_cast<const u32x4*>(K + r1 * rs + hk * HD + ch);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t w0 = k0[e >> 1], w1 = k1[e >> 1];
-        const uint32_t x0 = (e & 1) ? (w0 >> 16) : (w0 & 0xffffu);
-        const uint32_t x1 = (e & 1) ? (w1 & 0xffff0000u) : (w1 << 16);
-        *reinterpret_cast<uint32_t*>(Kt + (ch + e) * TLD + 2 * rp) = x0 | x1;
-      }
-    }
-    __syncthreads();
-    if (causal && j0 > wave_q0 + 31) continue;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+  const int nt = (kend + KT - 1) / KT;
+  for (int t = 0; t < nt; ++t) {
+    bwd_turn_over();
+    if (t + 1 < nt) load_tile(t + 1, (t + 1) & 1);
+    const unsigned char* tk = smem + (t & 1) * BUF;
+#pragma unroll 1
+    for (int u = 0; u < KT / 32; ++u) {
+      const int j0 = t * KT + 32 * u;
+      // steps past the sequence, and under the causal mask past the wave's last query
+      if (j0 >= n || (causal && j0 > wq0 + 31)) continue;
+      const unsigned char *uk = tk + u * (32 * RB), *uv = uk + TB;
       f32x16_t s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = 0.f;
-        dp[r] = 0.f;
-      }
-#pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        const bf16x8_t ka = __builtin_bit_cast(
-            bf16x8_t, *reinterpret_cast<const u32x4*>(Ks + (ks * 32 + l32) * KLD + kk * 16 + half * 8));
-        const bf16x8_t va = __builtin_bit_cast(
-            bf16x8_t, *reinterpret_cast<const u32x4*>(Vs + (ks * 32 + l32) * KLD + kk * 16 + half * 8));
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, df[kk], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd.rows(uk, kk), qf[kk], kk == 0 ? zero : s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd.rows(uv, kk), df[kk], kk == 0 ? zero : dp, 0, 0, 0);
       }
-      // s[r], dp[r]: key j0 + 32 ks + 8 (r/4) + 4 half + r%4, query qrow
-      const bool edge = j0 + BKEY > n || (causal && j0 + BKEY - 1 > wave_q0);
+      // s[r], dp[r]: key j0 + 8 (r/4) + 4 half + r%4, query wq0 + l32
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float p = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -Lq));
-        if (edge) {
-          const int j = j0 + ks * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-          if (j >= n || qrow >= n || (causal && j > qrow)) p = 0.f;
-        }
-        s[r] = p * (dp[r] - Dq);  // dS
+      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -ld.x));
+      if (j0 + 32 > n || (causal && j0 + 31 > wq0)) {
+        // keys from this lane's limit on are masked
+        const int lim = (causal ? min(n, wq0 + l32 + 1) : n) - j0 - 4 * half;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r >> 2) + (r & 3) >= lim) s[r] = 0.f;
       }
 #pragma unroll
-      for (int g4 = 0; g4 < 2; ++g4) {
-        const int rb = 8 * g4;
-        const u32x4 sw = {pack_bf16x2(s[rb], s[rb + 1]), pack_bf16x2(s[rb + 2], s[rb + 3]),
-                          pack_bf16x2(s[rb + 4], s[rb + 5]), pack_bf16x2(s[rb + 6], s[rb + 7])};
-        const bf16x8_t sb = __builtin_bit_cast(bf16x8_t, sw);
-        const int base = ks * 32 + 16 * g4 + 4 * half;
+      for (int r = 0; r < 16; ++r) s[r] *= dp[r] - ld.y;  // dS
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const bf16_t* kr = Kt + (ct * 32 + l32) * TLD + base;
-          const uint2 a_lo = *reinterpret_cast<const uint2*>(kr);
-          const uint2 a_hi = *reinterpret_cast<const uint2*>(kr + 8);
-          const u32x4 av = {a_lo.x, a_lo.y, a_hi.x, a_hi.y};
-          acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av), sb,
-                                                             acc[ct], 0, 0, 0);
-        }
+      for (int gg = 0; gg < 2; ++gg) {
+        const bf16x8_t sb = pack_slots(s, gg);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd.cols(uk, gg, ct), sb, acc[ct], 0, 0, 0);
       }
     }
   }
-  // acc[ct][r] = dQ^T[channel ct*32 + 8 (r/4) + 4 half + r%4][query qrow] / scale
+  // acc[ct][r] = dQ^T[channel ct*32 + 8 (r/4) + 4 half + r%4][query wq0 + l32] / scale
   __syncthreads();
   bf16_t* Os = reinterpret_cast<bf16_t*>(smem) + wave * 32 * OLD;
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int c = ct * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-      Os[l32 * OLD + c] = f32_to_bf16(acc[ct][r] * scale);
+    for (int r = 0; r < 16; r += 4) {
+      const uint2 w = {pack_bf16x2(acc[ct][r] * scale, acc[ct][r + 1] * scale),
+                       pack_bf16x2(acc[ct][r + 2] * scale, acc[ct][r + 3] * scale)};
+      *reinterpret_cast<uint2*>(Os + l32 * OLD + ct * 32 + 2 * r + 4 * half) = w;
     }
   __syncthreads();
-  for (int c = lane; c < 32 * HD / 8; c += 64) {
-    const int r = c / (HD / 8), ch = (c % (HD / 8)) * 8;
-    const int q = q0 + wave * 32 + r;
+  for (int c = lane; c < 32 * CPR; c += 64) {
+    const int r = c / CPR, ch = (c % CPR) * 8;
+    const int q = wq0 + r;
     if (q < n)
       *reinterpret_cast<u32x4*>(dQ + static_cast<int64_t>(lo + q) * grs + h * HD + ch) =
           *reinterpret_cast<const u32x4*>(Os + r * OLD + ch);
@@ -794,11 +806,11 @@ hipError_t launch_norm_bwd(hipStream_t s, int kind, const void* x, const void* g
                   static_cast<const bf16_t*>(dh), static_cast<const bf16_t*>(res),
                   static_cast<bf16_t*>(out), R, d, eps, scratch);
   };
-  const hipError_t e = nc <= 1   ? go(norm_bwd_kernel<1, 1>, norm_bwd_kernel<0, 1>)
-                       : nc <= 2 ? go(norm_bwd_kernel<1, 2>, norm_bwd_kernel<0, 2>)
-                       : nc <= 4 ? go(norm_bwd_kernel<1, 4>, norm_bwd_kernel<0, 4>)
-                       : nc <= 8 ? go(norm_bwd_kernel<1, 8>, norm_bwd_kernel<0, 8>)
-                                 : go(norm_bwd_kernel<1, 16>, norm_bwd_kernel<0, 16>);
+  const hipError_t e = nc <= 1   ? go(norm_bwd_kernel<1, 1, 1>, norm_bwd_kernel<0, 1, 1>)
+                       : nc <= 2 ? go(norm_bwd_kernel<1, 2, 1>, norm_bwd_kernel<0, 2, 1>)
+                       : nc <= 4 ? go(norm_bwd_kernel<1, 4, 1>, norm_bwd_kernel<0, 4, 1>)
+                       : nc <= 8 ? go(norm_bwd_kernel<1, 2, 4>, norm_bwd_kernel<0, 2, 4>)
+                                 : go(norm_bwd_kernel<1, 4, 4>, norm_bwd_kernel<0, 4, 4>);
   if (e != hipSuccess) return e;
   return launch(K_NORM, col_total_kernel, dim3((cols + 31) / 32), dim3(256), 0, s,
                 static_cast<const float*>(scratch), blocks, cols, d, dg, db);
@@ -817,24 +829,21 @@ hipError_t launch_act_bwd(hipStream_t s, const void* dF, const void* u, void* du
 hipError_t launch_scatter_rows(hipStream_t s, int d, const void* src0, void* dst0, const void* src1,
                                void* dst1, const int32_t* kept, int t_out, int t_in) {
   if (t_in == 0) return hipSuccess;
-  return launch(K_MISC, scatter_rows_kernel, dim3(t_out / 4 + 1), dim3(256), 0, s,
+  return launch(K_MISC, scatter_rows_kernel, dim3((t_in + 3) / 4), dim3(256), 0, s,
                 static_cast<const u32x4*>(src0), static_cast<u32x4*>(dst0),
                 static_cast<const u32x4*>(src1), static_cast<u32x4*>(dst1), kept, t_out, t_in,
                 d * 2 / 16);
 }
 
-hipError_t launch_rowdot(hipStream_t s, int dtype, const void* dO, const void* O, int64_t ld,
-                         int T, int H, int hd, float* D) {
+hipError_t launch_rowdot(hipStream_t s, const void* dO, const void* O, int64_t ld, int T, int H,
+                         int hd, const float* lse, float* LD) {
   const int L = hd / 8;
   if (hd % 8 != 0 || L > 64 || (L & (L - 1)) != 0) return hipErrorInvalidValue;
   const int64_t total = static_cast<int64_t>(T) * H * L;
   if (total == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((total + 255) / 256));
-  if (dtype == 1)
-    return launch(K_MISC, rowdot_kernel<bf16_t>, grid, dim3(256), 0, s,
-                  static_cast<const bf16_t*>(dO), static_cast<const bf16_t*>(O), ld, T, H, hd, D);
-  return launch(K_MISC, rowdot_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(dO),
-                static_cast<const float*>(O), ld, T, H, hd, D);
+  return launch(K_MISC, rowdot_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s,
+                static_cast<const bf16_t*>(dO), static_cast<const bf16_t*>(O), ld, T, H, hd, lse,
+                reinterpret_cast<float2*>(LD));
 }
 
 hipError_t launch_rope_bwd(hipStream_t s, int dtype, void* g, int64_t ld, int rows, int cols,
@@ -850,34 +859,28 @@ hipError_t launch_rope_bwd(hipStream_t s, int dtype, void* g, int64_t ld, int ro
 }
 
 hipError_t launch_attention_bwd(hipStream_t s, const void* q, const void* k, const void* v,
-                                int64_t rs, const void* dO, int64_t ors, const float* lse,
-                                const float* D, int H, int kv_group, int hd, int causal,
-                                float scale, int B, int max_len, int T, const int32_t* cu_dev,
-                                void* dq, void* dk, void* dv, int64_t grs) {
+                                int64_t rs, const void* dO, int64_t ors, const float* LD, int H,
+                                int kv_group, int hd, int causal, float scale, int B, int max_len,
+                                int T, const int32_t* cu_dev, void* dq, void* dk, void* dv,
+                                int64_t grs) {
   if (B == 0 || max_len == 0) return hipSuccess;
-  const float sl = scale * kLog2e;
-  auto* qp = static_cast<const bf16_t*>(q);
-  auto* kp = static_cast<const bf16_t*>(k);
-  auto* vp = static_cast<const bf16_t*>(v);
-  auto* dp = static_cast<const bf16_t*>(dO);
   const int Hkv = H / kv_group;
-  hipError_t e;
-  if (hd == 64) {
-    e = launch(K_ATTENTION, attn_bwd_dkdv_kernel<64>, dim3((max_len + 127) / 128, Hkv, B),
-               dim3(256), 0, s, qp, kp, vp, rs, dp, ors, lse, D, T, kv_group, causal, scale, sl,
-               cu_dev, static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), grs);
+  auto go = [&](auto dkdv, auto dq_kernel) {
+    const float sl = scale * kLog2e;
+    auto* qp = static_cast<const bf16_t*>(q);
+    auto* kp = static_cast<const bf16_t*>(k);
+    auto* vp = static_cast<const bf16_t*>(v);
+    auto* op = static_cast<const bf16_t*>(dO);
+    auto* lp = reinterpret_cast<const float2*>(LD);
+    const hipError_t e = launch(K_ATTENTION, dkdv, place_grid(Hkv, B, max_len, T, causal, 128), dim3(256), 0, s, qp,
+                                kp, vp, rs, op, ors, lp, T, Hkv, kv_group, causal, scale, sl, cu_dev,
+                                static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), grs, Hkv * B);
     if (e != hipSuccess) return e;
-    return launch(K_ATTENTION, attn_bwd_dq_kernel<64>, dim3((max_len + 127) / 128, H, B),
-                  dim3(256), 0, s, qp, kp, vp, rs, dp, ors, lse, D, T, kv_group, causal, scale, sl,
-                  cu_dev, static_cast<bf16_t*>(dq), grs);
-  }
-  e = launch(K_ATTENTION, attn_bwd_dkdv_kernel<128>, dim3((max_len + 127) / 128, Hkv, B),
-             dim3(256), 0, s, qp, kp, vp, rs, dp, ors, lse, D, T, kv_group, causal, scale, sl,
-             cu_dev, static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), grs);
-  if (e != hipSuccess) return e;
-  return launch(K_ATTENTION, attn_bwd_dq_kernel<128>, dim3((max_len + 127) / 128, H, B),
-                dim3(256), 0, s, qp, kp, vp, rs, dp, ors, lse, D, T, kv_group, causal, scale, sl,
-                cu_dev, static_cast<bf16_t*>(dq), grs);
+    return launch(K_ATTENTION, dq_kernel, place_grid(H, B, max_len, T, causal, 128), dim3(256), 0, s, qp, kp, vp, rs,
+                  op, ors, lp, T, H, kv_group, causal, scale, sl, cu_dev, static_cast<bf16_t*>(dq), grs, H * B);
+  };
+  return hd == 64 ? go(attn_bwd_dkdv_kernel<64>, attn_bwd_dq_kernel<64>)
+                  : go(attn_bwd_dkdv_kernel<128>, attn_bwd_dq_kernel<128>);
 }
 
 }  // namespace zsa

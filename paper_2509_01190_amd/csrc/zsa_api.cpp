@@ -915,7 +915,7 @@ namespace {
 
 // buffers of one layer's backward, for up to T rows
 struct BwdLayout {
-  size_t h1, x1, h2, u, dF, du, dh2, dx1, dog, dofull, dxr, dqkv, dh1, D, wqkvT, woT, wupT, wdownT,
+  size_t h1, x1, h2, u, dF, du, dh2, dx1, dog, dofull, dxr, dqkv, dh1, LD, wqkvT, woT, wupT, wdownT,
       col, splitk, splitk_bytes, end;
 };
 
@@ -937,7 +937,7 @@ BwdLayout bwd_layout(const zsa_layer_cfg* c, int64_t T, Carver& cv) {
   B.dxr = cv.take(T * d * e);
   B.dqkv = cv.take(T * qw * e);
   B.dh1 = cv.take(T * d * e);
-  B.D = cv.take(static_cast<size_t>(c->n_heads) * T * 4);
+  B.LD = cv.take(static_cast<size_t>(c->n_heads) * T * 8);
   B.wqkvT = cv.take(static_cast<size_t>(d) * qw * e);
   B.woT = cv.take(static_cast<size_t>(d) * d * e);
   B.wupT = cv.take(static_cast<size_t>(d) * up_n * e);
@@ -1072,10 +1072,10 @@ int layer_backward(hipStream_t s, const zsa_layer_cfg& c, const zsa_layer_weight
     dxr = P(B.dxr);
   }
   // ---- attention
-  float* Dv = reinterpret_cast<float*>(base + B.D);
-  HIP_TRY(launch_rowdot(s, dt, dof, wb.o, d, T, H, hd, Dv), "rowdot");
+  float* LD = reinterpret_cast<float*>(base + B.LD);
+  HIP_TRY(launch_rowdot(s, dof, wb.o, d, T, H, hd, wb.lse, LD), "rowdot");
   char* dqkv = base + B.dqkv;
-  HIP_TRY(launch_attention_bwd(s, q, k, v, qw, dof, d, wb.lse, Dv, H, kvg, hd, c.causal, scale,
+  HIP_TRY(launch_attention_bwd(s, q, k, v, qw, dof, d, LD, H, kvg, hd, c.causal, scale,
                                in.B, in.max_len, T, in.cu_dev, dqkv, dqkv + d * e,
                                dqkv + (d + kvd) * e, qw),
           "attention gradient");

@@ -305,15 +305,16 @@ hipError_t launch_act_bwd(hipStream_t s, const void* dF, const void* u, void* du
 // zeros elsewhere (kept ascending)
 hipError_t launch_scatter_rows(hipStream_t s, int d, const void* src0, void* dst0, const void* src1,
                                void* dst1, const int32_t* kept, int t_out, int t_in);
-hipError_t launch_rowdot(hipStream_t s, int dtype, const void* dO, const void* O, int64_t ld,
-                         int T, int H, int hd, float* D);
+// LD[h][r] = (lse[h][r] log2 e, dO_r . O_r over head h's columns)
+hipError_t launch_rowdot(hipStream_t s, const void* dO, const void* O, int64_t ld, int T, int H,
+                         int hd, const float* lse, float* LD);
 hipError_t launch_rope_bwd(hipStream_t s, int dtype, void* g, int64_t ld, int rows, int cols,
                            int hd, const int32_t* pos, const EpiParams& ep);
 hipError_t launch_attention_bwd(hipStream_t s, const void* q, const void* k, const void* v,
-                                int64_t rs, const void* dO, int64_t ors, const float* lse,
-                                const float* D, int H, int kv_group, int hd, int causal,
-                                float scale, int B, int max_len, int T, const int32_t* cu_dev,
-                                void* dq, void* dk, void* dv, int64_t grs);
+                                int64_t rs, const void* dO, int64_t ors, const float* LD, int H,
+                                int kv_group, int hd, int causal, float scale, int B, int max_len,
+                                int T, const int32_t* cu_dev, void* dq, void* dk, void* dv,
+                                int64_t grs);
 
 // row gather of up to two [*, d] arrays plus pos
 hipError_t launch_gather(hipStream_t s, int dtype, int d, int t_in, const int32_t* kept,

@@ -95,8 +95,8 @@ hipError_t launch_scatter_rows(hipStream_t, int, const void*, void*, const void*
                                const int32_t*, int, int) {
   reached("launch_scatter_rows");
 }
-hipError_t launch_rowdot(hipStream_t, int, const void*, const void*, int64_t, int, int, int,
-                         float*) {
+hipError_t launch_rowdot(hipStream_t, const void*, const void*, int64_t, int, int, int,
+                         const float*, float*) {
   reached("launch_rowdot");
 }
 hipError_t launch_rope_bwd(hipStream_t, int, void*, int64_t, int, int, int, const int32_t*,
@@ -104,9 +104,8 @@ hipError_t launch_rope_bwd(hipStream_t, int, void*, int64_t, int, int, int, cons
   reached("launch_rope_bwd");
 }
 hipError_t launch_attention_bwd(hipStream_t, const void*, const void*, const void*, int64_t,
-                                const void*, int64_t, const float*, const float*, int, int, int,
-                                int, float, int, int, int, const int32_t*, void*, void*, void*,
-                                int64_t) {
+                                const void*, int64_t, const float*, int, int, int, int, float,
+                                int, int, int, const int32_t*, void*, void*, void*, int64_t) {
   reached("launch_attention_bwd");
 }
 hipError_t launch_rope_table(hipStream_t, const int32_t*, int, const EpiParams&, float*) {
