@@ -85,6 +85,74 @@ __global__ __launch_bounds__(256) void norm_kernel(const T* __restrict__ x,
   }
 }
 
+// Few wide rows (generation): a workgroup per row, the gain and shift loaded
+// with the row. What is left is one memory round trip and the reductions;
+// the kernel above has the round trips of the row and then of the gain and
+// shift, and one wave's share of the row is four times as long. 4 rows of
+// 4096: FEWROW_US; from one workgroup per CU on the other keeps more rows in
+// flight.
+template <typename T, int MAXC, bool RMS>
+__global__ __launch_bounds__(256) void norm_few_kernel(const T* __restrict__ x, const T* __restrict__ g,
+                                                       const T* __restrict__ b, int d, float eps,
+                                                       T* __restrict__ y) {
+  constexpr int V = Vec16<T>::N;
+  __shared__ float part[2][4];
+  const int tid = threadIdx.x, C = d / V;
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * d;
+  const uint4* xr = reinterpret_cast<const uint4*>(x + base);
+  const bool shift = !RMS && b != nullptr;
+  uint4 xv[MAXC], gv[MAXC], bv[MAXC];
+#pragma unroll
+  for (int i = 0; i < MAXC; ++i) {
+    const int c = tid + 256 * i;
+    const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+    xv[i] = c < C ? xr[c] : none;
+    gv[i] = c < C ? reinterpret_cast<const uint4*>(g)[c] : none;
+    bv[i] = shift && c < C ? reinterpret_cast<const uint4*>(b)[c] : none;
+  }
+  auto total = [&](float v, int slot) {
+    v = row_sum<64>(v);
+    if ((tid & 63) == 0) part[slot][tid >> 6] = v;
+    __syncthreads();
+    return part[slot][0] + part[slot][1] + part[slot][2] + part[slot][3];
+  };
+  const float inv_d = 1.0f / static_cast<float>(d);
+  float mean = 0.f, sq = 0.f;
+  if (!RMS) {
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+      float v[V];
+      unpack16(xv[i], v, T());
+#pragma unroll
+      for (int e = 0; e < V; ++e) sum += v[e];
+    }
+    mean = total(sum, 0) * inv_d;
+  }
+#pragma unroll
+  for (int i = 0; i < MAXC; ++i) {
+    if (tid + 256 * i >= C) continue;
+    float v[V];
+    unpack16(xv[i], v, T());
+#pragma unroll
+    for (int e = 0; e < V; ++e) sq += (v[e] - mean) * (v[e] - mean);
+  }
+  const float rstd = 1.0f / sqrtf(total(sq, 1) * inv_d + eps);
+  uint4* yr = reinterpret_cast<uint4*>(y + base);
+#pragma unroll
+  for (int i = 0; i < MAXC; ++i) {
+    const int c = tid + 256 * i;
+    if (c >= C) continue;
+    float v[V], gg[V], bb[V], o[V];
+    unpack16(xv[i], v, T());
+    unpack16(gv[i], gg, T());
+    unpack16(bv[i], bb, T());
+#pragma unroll
+    for (int e = 0; e < V; ++e) o[e] = (v[e] - mean) * rstd * gg[e] + bb[e];
+    yr[c] = pack16(o, T());
+  }
+}
+
 template <typename T, bool RMS>
 hipError_t dispatch(hipStream_t s, const void* x, const void* g, const void* b, int rows, int d,
                     float eps, void* y) {
@@ -101,6 +169,12 @@ hipError_t dispatch(hipStream_t s, const void* x, const void* g, const void* b, 
     if (C <= 32) return launch(K_NORM, norm_kernel<T, 1, RMS, 32>, grid, block, 0, s, xp, gp, bp, rows, d, eps, yp);
     if (C <= 64) return launch(K_NORM, norm_kernel<T, 2, RMS, 32>, grid, block, 0, s, xp, gp, bp, rows, d, eps, yp);
     return launch(K_NORM, norm_kernel<T, 3, RMS, 32>, grid, block, 0, s, xp, gp, bp, rows, d, eps, yp);
+  }
+  if (rows <= 256 && C > 128) {
+    const dim3 few(rows);
+    if (C <= 256) return launch(K_NORM, norm_few_kernel<T, 1, RMS>, few, block, 0, s, xp, gp, bp, d, eps, yp);
+    if (C <= 512) return launch(K_NORM, norm_few_kernel<T, 2, RMS>, few, block, 0, s, xp, gp, bp, d, eps, yp);
+    if (C <= 1024) return launch(K_NORM, norm_few_kernel<T, 4, RMS>, few, block, 0, s, xp, gp, bp, d, eps, yp);
   }
   const dim3 grid((rows + 3) / 4);
   if (C <= 128) return launch(K_NORM, norm_kernel<T, 2, RMS, 64>, grid, block, 0, s, xp, gp, bp, rows, d, eps, yp);
