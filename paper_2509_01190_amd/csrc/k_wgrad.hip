@@ -17,10 +17,11 @@
 // The rows are split over S workgroups per tile where the tiles alone would
 // not fill the chip; wgrad_sum_kernel adds the S partial results in order.
 // us with all their launches, before (two transposes, product, sum, two
-// column-sum passes) / now: 4096 rows, 3072 x 768 63.4 / 39.5, 768 x 768 45.5 /
-// 19.6, 2304 x 768 54.3 / 32.9; 8192 rows, 2304 x 768 85.6 / 50.2. What bounds the
+// column-sum passes) / now: 4096 rows, 3072 x 768 63.4 / 35, 768 x 768 45.5 /
+// 17.4, 2304 x 768 54.3 / 29.1; 8192 rows, 2304 x 768 85.6 / 43.7. What bounds the
 // product: the partial results it writes (28 MB at 3072 x 768) and the LDS, whose
-// reads and writes take 1.5 times the matrix instructions' time.
+// reads and writes take 1.5 times the matrix instructions' time and more (the
+// transposing reads measure about half the rate of plain ones).
 #include "zsa_internal.h"
 
 namespace zsa {
@@ -41,7 +42,11 @@ struct WgradArgs {
 };
 
 // TILE x TILE outputs on WM x WN waves, BK rows per slice, NB slices in LDS,
-// NB - 1 of them in flight; one barrier per slice.
+// NB - 1 of them in flight; one barrier per slice. 64 KB of LDS a workgroup at
+// the narrower tiles: two slices of 64 (128) rows beat four of half as many,
+// whose barriers are twice as many (us with the sums: 4096 rows, 3072 x 768
+// 37.7 / 34.6, 768 x 768 18.2 / 17.4; 8192 rows, 2304 x 768 45.4 / 43.7); at 256
+// the two are alike.
 template <int TILE, int WM, int WN, int BK, int NB>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(const WgradArgs p) {
   constexpr int NW = WM * WN, RB = TILE * 2, CPR = TILE / 8;  // bytes and 16-byte chunks of a slice row
@@ -238,7 +243,8 @@ __global__ __launch_bounds__(256) void wgrad_sum_kernel(const float4* __restrict
 
 // The tile width, and the splits that fill the workgroups the chip holds at
 // once (one of 256 per CU, two of the others); a split keeps at least 128
-// rows. 128-wide tiles read each operand half as often as 64-wide ones, which
+// rows, 512 where a partial result is 2 MB or more (1000 rows, 3072 x 768: one
+// split 18.8 us, three 23.1). 128-wide tiles read each operand half as often as 64-wide ones, which
 // need fewer splits and so write fewer partial results: 768 x 768 over 4096
 // rows, 19.7 us in 36 tiles of 128 and 13 splits (30 MB) with the kernel of
 // before, 14.6 in 144 tiles of 64 and 3. 256-wide ones, where they number at
@@ -259,7 +265,8 @@ WgradPlan wgrad_tiles(int m, int n) {
 
 int wgrad_splits(const WgradPlan& p, int rows) {
   const int64_t want = (p.tile == 256 ? 256 : 512) / (static_cast<int64_t>(p.tm) * p.tn);
-  return static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, want), std::max(1, rows / 128)));
+  const int least = static_cast<int64_t>(p.tm) * p.tn * p.tile * p.tile >= (1 << 19) ? 512 : 128;
+  return static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, want), std::max(1, rows / least)));
 }
 
 WgradPlan wgrad_plan(int rows, int m, int n) {
@@ -305,8 +312,8 @@ hipError_t launch_wgrad(hipStream_t s, const void* dy, int m, const void* x, int
   a.bias = db != nullptr ? w + part : nullptr;
   const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(p.tm) * p.tn * p.splits + 7) / 8 * 8);
   const hipError_t e = p.tile == 256   ? launch(K_GEMM, wgrad_kernel<256, 2, 4, 32, 4>, dim3(grid), dim3(512), 0, s, a)
-                       : p.tile == 128 ? launch(K_GEMM, wgrad_kernel<128, 2, 2, 32, 4>, dim3(grid), dim3(256), 0, s, a)
-                                       : launch(K_GEMM, wgrad_kernel<64, 2, 2, 64, 4>, dim3(grid), dim3(256), 0, s, a);
+                       : p.tile == 128 ? launch(K_GEMM, wgrad_kernel<128, 2, 2, 64, 2>, dim3(grid), dim3(256), 0, s, a)
+                                       : launch(K_GEMM, wgrad_kernel<64, 2, 2, 128, 2>, dim3(grid), dim3(256), 0, s, a);
   if (e != hipSuccess || (part == 0 && db == nullptr)) return e;
   const int64_t total4 = part ? static_cast<int64_t>(m) * n / 4 : 0;
   const int blocks4 = static_cast<int>((total4 + 255) / 256);
