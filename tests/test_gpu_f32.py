@@ -85,3 +85,33 @@ def test_attention_f32_masked_rows_stay_out(bad):
     out = zsa.attention_with_scores(q, k, v, H, seqs, True)[0]
     assert_close(f64(out)[:at], f64(ref)[:at], 1e-6, "rows before the one that is not finite")
     assert not torch.isfinite(out[at:]).any()
+
+
+@pytest.mark.parametrize("hd", [16, 64])
+@pytest.mark.parametrize("top,first", [(0, 1), (0, 32), (140, 1)])  # special keys beside the top one, in another
+def test_attention_f32_small_probabilities(hd, top, first):         # wave's tile, and before it in the same wave
+    """Probabilities down to e^-48 keep fp32's relative precision. Query 0's
+    scores are exact (one product each): 0 for key ``top``, -x for 16 special
+    keys, -200 for the rest, so its sum rounds to 1 and its log-sum-exp to 0
+    and every exponent is exact. Each special key has a V channel to itself
+    and, as the other queries' scores are four times as low, a contribution
+    score of e^-x (1 + 1e-14). Bounds, with u = 2^-24: an exponential is
+    within 2u; at most three of them and three products make a probability;
+    the sums add terms below 1e-9: 10 u = 6e-7. (An exponential that rounds
+    its argument times log2 e to fp32 is off by up to 2^-24 times that
+    argument, 58 here.)"""
+    n, x = 150, 18.0 + 2.0 * np.arange(16) - 0.0625 * np.arange(16) ** 2 + np.linspace(0, 15, 16)
+    x = np.float32(np.round(x * 64) / 64)
+    qkv = np.zeros((n, 3 * hd), dtype=np.float32)
+    qkv[:, 0] = 4.0
+    qkv[0, 0] = 1.0
+    qkv[:, hd] = -200.0
+    qkv[top, hd] = 0.0
+    qkv[first:first + 16, hd] = -x
+    qkv[first + np.arange(16), 2 * hd + np.arange(16)] = 1.0
+    q, k, v = to_dev(qkv, "f32").split(hd, dim=1)
+    out, lse, scores = zsa.attention_with_scores(q, k, v, 1, zsa.Seqs([n], dev()), False, scale=1.0)
+    p = np.exp(-x.astype(np.float64))
+    assert abs(f64(lse)[0, 0]) <= 3e-7  # the sum of the others, and one rounding
+    assert np.abs(f64(out)[0, :16] / p - 1.0).max() <= 6e-7
+    assert np.abs(f64(scores)[first:first + 16] / p - 1.0).max() <= 6e-7
