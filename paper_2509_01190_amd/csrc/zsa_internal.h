@@ -114,24 +114,41 @@ __device__ __forceinline__ uint4 keep16(const uint4& v, bool keep) {
 // them (the longest blocks first, the shortest at the end) under the mask or
 // with sequences of several lengths, and a sequence's otherwise.
 struct Place { int b, h, i; };
-// grid: x = 8 * chunk (XCD fastest), y = blocks, z = chunks of pairs; i counts
-// the blocks from the last (attention: the queries that see most keys) or,
-// with `first`, from the first (scores: the keys that most queries see)
-__device__ __forceinline__ bool place(int H, int pairs, bool first, Place* at) {
-  const int e = static_cast<int>((blockIdx.z * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7));
-  if (e >= pairs) return false;
-  at->b = e / H;
-  const int x = e - at->b * H;
+// grid (place_grid): x = 8 * chunk (XCD fastest), y = blocks, z = chunks of
+// pairs, or, with all pairs in x, runs of blocks; i counts the blocks from the
+// last (attention: the queries that see most keys) or, with `first`, from the
+// first (scores: the keys that most queries see)
+__host__ __device__ __forceinline__ bool place_at(dim3 grid, dim3 at_block, int H, int pairs, bool first,
+                                                  Place* at) {
+  const uint32_t chunk = grid.x >> 3;
+  const bool whole = 8 * static_cast<uint64_t>(chunk) >= static_cast<uint64_t>(pairs);
+  const uint32_t pz = whole ? 0 : at_block.z, iz = whole ? at_block.z : 0;
+  const uint32_t e = (pz * chunk + (at_block.x >> 3)) * 8 + (at_block.x & 7);
+  if (e >= static_cast<uint32_t>(pairs)) return false;
+  at->b = static_cast<int>(e) / H;
+  const int x = static_cast<int>(e) - at->b * H;
   at->h = H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
-  at->i = static_cast<int>(first ? blockIdx.y : gridDim.y - 1 - blockIdx.y);
+  const uint32_t i = iz * grid.y + at_block.y, blocks = grid.y * (whole ? grid.z : 1);
+  at->i = static_cast<int>(first ? i : blocks - 1 - i);
   return true;
 }
+__device__ __forceinline__ bool place(int H, int pairs, bool first, Place* at) {
+  return place_at(gridDim, blockIdx, H, pairs, first, at);
+}
+
+constexpr uint32_t kGridYZ = 65535;  // HIP's limit on a grid's y and z
 
 inline dim3 place_grid(int H, int B, int max_len, int T, int causal, int block) {
-  const int p8 = (H * B + 7) / 8;  // pairs per XCD
+  const int64_t p8 = (static_cast<int64_t>(H) * B + 7) / 8;  // pairs per XCD
   const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
-  const int chunk = alike ? std::min(p8, std::max(1, H / 8)) : p8;
-  return dim3(8u * chunk, (max_len + block - 1) / block, (p8 + chunk - 1) / chunk);
+  int64_t chunk = alike ? std::min<int64_t>(p8, std::max(1, H / 8)) : p8;
+  // the chunks number at most 65535, and at 512 threads a workgroup x stays below 2^32 threads
+  chunk = std::min<int64_t>(std::max(chunk, (p8 + kGridYZ - 1) / kGridYZ), (1 << 20) - 1);
+  const int64_t blocks = (static_cast<int64_t>(max_len) + block - 1) / block;
+  // sequences of more blocks than y holds (8.4 M rows in 128-row blocks): all pairs in x, the blocks in y and z
+  if (blocks > kGridYZ)
+    return dim3(static_cast<uint32_t>(8 * p8), kGridYZ, static_cast<uint32_t>((blocks + kGridYZ - 1) / kGridYZ));
+  return dim3(static_cast<uint32_t>(8 * chunk), static_cast<uint32_t>(blocks), static_cast<uint32_t>((p8 + chunk - 1) / chunk));
 }
 
 // ---------------------------------------------------------------------------

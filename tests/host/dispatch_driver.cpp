@@ -1,0 +1,72 @@
+// Host checks of how calls are laid out on the GPU: launch grids within HIP's
+// limits, every block of work reached exactly once. Prints "ok <checks>" and exits 0 when every check holds.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <vector>
+
+#include "../../paper_2509_01190_amd/csrc/zsa_internal.h"
+
+namespace {
+
+int g_checks = 0;
+
+void check(bool ok, const char* what, int line) {
+  ++g_checks;
+  if (!ok) {
+    fprintf(stderr, "check failed (line %d): %s\n", line, what);
+    exit(1);
+  }
+}
+#define CHECK_TRUE(cond) check((cond), #cond, __LINE__)
+
+// every (sequence, head, block) has exactly one workgroup of a legal grid
+void check_place(int H, int B, int max_len, int T, int causal, int block) {
+  fprintf(stderr, "place: %d heads, %d sequences of up to %d rows, %d in all, causal %d, blocks of %d\n", H, B,
+          max_len, T, causal, block);
+  const dim3 g = zsa::place_grid(H, B, max_len, T, causal, block);
+  CHECK_TRUE(g.y <= 65535 && g.z <= 65535 && 512ull * g.x <= 0xffffffffull);
+  const int blocks = (max_len + block - 1) / block;
+  for (int first = 0; first < 2; ++first) {
+    std::vector<unsigned char> hit(static_cast<size_t>(B) * H * blocks, 0);
+    for (uint32_t z = 0; z < g.z; ++z)
+      for (uint32_t y = 0; y < g.y; ++y)
+        for (uint32_t x = 0; x < g.x; ++x) {
+          zsa::Place at;
+          if (!zsa::place_at(g, dim3(x, y, z), H, H * B, first != 0, &at)) continue;
+          if (at.i >= blocks) continue;  // past every sequence: the kernels return
+          if (at.b < 0 || at.b >= B || at.h < 0 || at.h >= H || at.i < 0) CHECK_TRUE(!"out of range");
+          if (hit[(static_cast<size_t>(at.b) * H + at.h) * blocks + at.i]++) CHECK_TRUE(!"reached twice");
+        }
+    for (unsigned char h : hit)
+      if (!h) CHECK_TRUE(!"not reached");
+    ++g_checks;
+  }
+}
+
+void places() {
+  for (int causal = 0; causal < 2; ++causal) {
+    for (int H : {1, 3, 7, 8, 12, 16, 32}) {
+      check_place(H, 1, 1, 1, causal, 128);
+      check_place(H, 5, 300, 5 * 300, causal, 128);
+      check_place(H, 5, 300, 5 * 300 - 7, causal, 256);
+      check_place(H, 33, 1000, 33 * 1000, causal, 128);
+    }
+    // as many sequences as a grid's z once held, one pair of rows each
+    check_place(12, 65535, 2, 2 * 65535, causal, 128);
+    check_place(7, 65535, 2, 2 * 65535, causal, 256);
+    check_place(2, 65535, 3, 3 * 65535, causal, 256);
+    check_place(16, 43700, 1, 43700, causal, 128);
+    // one sequence of more blocks than a grid's y holds
+    check_place(1, 1, 9000000, 9000000, causal, 128);
+    check_place(3, 2, 8388481, 8388482, causal, 128);
+  }
+}
+
+}  // namespace
+
+int main() {
+  places();
+  printf("ok %d\n", g_checks);
+  return 0;
+}

@@ -1,0 +1,33 @@
+"""How calls are laid out on the GPU and which kernel takes them, checked on
+the host: the placement functions and dispatch rules are compiled into a small
+driver (and, for the rules, linked with the built library), which no GPU is
+needed for."""
+import os
+import shutil
+import subprocess
+import tempfile
+
+import pytest
+
+from paper_2509_01190_amd import _build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+DRIVER = os.path.join(ROOT, "tests", "host", "dispatch_driver.cpp")
+
+
+@pytest.mark.skipif(not os.path.exists(_build.HIPCC), reason="ROCm compilers not installed")
+def test_placement_and_dispatch_rules():
+    tmp = tempfile.mkdtemp(prefix="zsa_dispatch_")
+    try:
+        exe = os.path.join(tmp, "dispatch_driver")
+        lib = os.path.dirname(_build.LIB_PATH)
+        subprocess.run([_build.HIPCC, "-x", "hip", "--cuda-host-only", f"--offload-arch={_build.ARCH}", "-O2",
+                        "-std=c++17", "-c", DRIVER, "-o", exe + ".o"],
+                       check=True, capture_output=True, text=True, timeout=300)
+        subprocess.run([_build.HIPCC, exe + ".o", _build.LIB_PATH, f"-Wl,-rpath,{lib}", "-o", exe],
+                       check=True, capture_output=True, text=True, timeout=300)
+        r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout + r.stderr
+        assert r.stdout.startswith("ok "), r.stdout
+    finally:
+        shutil.rmtree(tmp, ignore_errors=True)
