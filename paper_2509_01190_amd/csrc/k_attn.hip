@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   __shared__ __align__(16) unsigned char smem[SBYTES];
 
   Place at;
-  if (!place(H, pairs, false, &at)) return;
+  if (!place(H, kv_group, pairs, false, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   typedef __attribute__((address_space(3))) const char lds_char;
 
   Place at;
-  if (!place(H, pairs, false, &at)) return;
+  if (!place(H, kv_group, pairs, false, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;

@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   __shared__ __align__(1024) unsigned char smem[SBYTES];
 
   Place at;
-  if (!place(Hkv, pairs, true, &at)) return;
+  if (!place(Hkv, 1, pairs, true, &at)) return;
   const int b = at.b, g = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
@@ -672,7 +672,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   __shared__ __align__(1024) unsigned char smem[SBYTES];
 
   Place at;
-  if (!place(H, pairs, false, &at)) return;
+  if (!place(H, kv_group, pairs, false, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;

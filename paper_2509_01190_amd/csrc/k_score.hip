@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) __attribute__((amdgpu_waves_per_e
   bf16_t* Ks = reinterpret_cast<bf16_t*>(smem);
 
   Place at;
-  if (!place(H, pairs, true, &at)) return;
+  if (!place(H, kv_group, pairs, true, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   typedef __attribute__((address_space(3))) const char lds_char;
 
   Place at;
-  if (!place(H, pairs, true, &at)) return;
+  if (!place(H, kv_group, pairs, true, &at)) return;
   const int b = at.b, h = at.h;
   const int lo = cu[b];
   const int n = cu[b + 1] - lo;

@@ -98,9 +98,12 @@ __device__ __forceinline__ uint4 keep16(const uint4& v, bool keep) {
 // ---------------------------------------------------------------------------
 // Which (sequence, head, block of queries or keys) an attention or score
 // workgroup takes. Workgroup L runs on XCD L % 8, in order of L within it. The (sequence,
-// head) pairs are dealt to the XCDs in turn (with a multiple of 8 heads each
-// XCD takes neighbouring ones, which share key/value heads and so its L2), and
-// an XCD walks `chunk` of its pairs at a time, last query block first. With
+// head) pairs are dealt to the XCDs in turn, and an XCD walks `chunk` of its
+// pairs at a time, last query block first. Where `group` heads share a
+// key/value head and the heads are a multiple of 8, an XCD takes neighbouring
+// ones, and their K and V stay in its L2 (32 heads on 8, 32 ragged sequences
+// of up to 300 rows 50 us, in plain order 57); heads that share nothing are in
+// plain order (64 x 128 rows, 32 heads of 64: 26.6, neighbours 27.4). With
 // the query block in the grid's fastest dimension, as these kernels had it,
 // equal sequences put the same query block on the same XCD throughout: under
 // the causal mask one XCD got every longest block and another every shortest
@@ -118,8 +121,8 @@ struct Place { int b, h, i; };
 // pairs, or, with all pairs in x, runs of blocks; i counts the blocks from the
 // last (attention: the queries that see most keys) or, with `first`, from the
 // first (scores: the keys that most queries see)
-__host__ __device__ __forceinline__ bool place_at(dim3 grid, dim3 at_block, int H, int pairs, bool first,
-                                                  Place* at) {
+__host__ __device__ __forceinline__ bool place_at(dim3 grid, dim3 at_block, int H, int group, int pairs,
+                                                  bool first, Place* at) {
   const uint32_t chunk = grid.x >> 3;
   const bool whole = 8 * static_cast<uint64_t>(chunk) >= static_cast<uint64_t>(pairs);
   const uint32_t pz = whole ? 0 : at_block.z, iz = whole ? at_block.z : 0;
@@ -127,13 +130,13 @@ __host__ __device__ __forceinline__ bool place_at(dim3 grid, dim3 at_block, int 
   if (e >= static_cast<uint32_t>(pairs)) return false;
   at->b = static_cast<int>(e) / H;
   const int x = static_cast<int>(e) - at->b * H;
-  at->h = H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
+  at->h = group > 1 && H % 8 == 0 ? (x & 7) * (H >> 3) + (x >> 3) : x;
   const uint32_t i = iz * grid.y + at_block.y, blocks = grid.y * (whole ? grid.z : 1);
   at->i = static_cast<int>(first ? i : blocks - 1 - i);
   return true;
 }
-__device__ __forceinline__ bool place(int H, int pairs, bool first, Place* at) {
-  return place_at(gridDim, blockIdx, H, pairs, first, at);
+__device__ __forceinline__ bool place(int H, int group, int pairs, bool first, Place* at) {
+  return place_at(gridDim, blockIdx, H, group, pairs, first, at);
 }
 
 constexpr uint32_t kGridYZ = 65535;  // HIP's limit on a grid's y and z

@@ -28,12 +28,13 @@ void check_place(int H, int B, int max_len, int T, int causal, int block) {
   CHECK_TRUE(g.y <= 65535 && g.z <= 65535 && 512ull * g.x <= 0xffffffffull);
   const int blocks = (max_len + block - 1) / block;
   for (int first = 0; first < 2; ++first) {
+    const int group = first && H % 2 == 0 ? 2 : 1;
     std::vector<unsigned char> hit(static_cast<size_t>(B) * H * blocks, 0);
     for (uint32_t z = 0; z < g.z; ++z)
       for (uint32_t y = 0; y < g.y; ++y)
         for (uint32_t x = 0; x < g.x; ++x) {
           zsa::Place at;
-          if (!zsa::place_at(g, dim3(x, y, z), H, H * B, first != 0, &at)) continue;
+          if (!zsa::place_at(g, dim3(x, y, z), H, group, H * B, first != 0, &at)) continue;
           if (at.i >= blocks) continue;  // past every sequence: the kernels return
           if (at.b < 0 || at.b >= B || at.h < 0 || at.h >= H || at.i < 0) CHECK_TRUE(!"out of range");
           if (hit[(static_cast<size_t>(at.b) * H + at.h) * blocks + at.i]++) CHECK_TRUE(!"reached twice");
@@ -63,10 +64,25 @@ void places() {
   }
 }
 
+// An XCD (workgroup number mod 8) takes neighbouring heads where they share
+// key/value heads, and every eighth one where they share nothing
+void head_order() {
+  const int H = 32, B = 4;
+  const dim3 g = zsa::place_grid(H, B, 128, B * 128, 0, 128);
+  for (int group : {1, 4})
+    for (uint32_t z = 0; z < g.z; ++z)
+      for (uint32_t x = 0; x < g.x; ++x) {
+        zsa::Place at;
+        if (!zsa::place_at(g, dim3(x, 0, z), H, group, H * B, false, &at)) continue;
+        CHECK_TRUE(static_cast<int>(x & 7) == (group == 1 ? at.h % 8 : at.h / (H / 8)));
+      }
+}
+
 }  // namespace
 
 int main() {
   places();
+  head_order();
   printf("ok %d\n", g_checks);
   return 0;
 }
