@@ -877,6 +877,23 @@ hipError_t f32_dispatch(hipStream_t s, const void* q, const void* k, const void*
 
 }  // namespace
 
+// Whether attn_wide_kernel takes the call: from the lengths on at which it
+// pays (its comment), but not where the grid of 256-query blocks leaves CUs
+// with one workgroup or none and the other kernel's waves wait less. us, the
+// other kernel / this one, head dim 64 under the mask: 12 heads, 1 x 500 rows
+// 13.3 / 14.7, 8 x 400 (192 workgroups) 13.3 / 14.2, 16 x 300 (384) 15.7 /
+// 15.0; 32 heads, 4 x 500 (256) 15.4 / 16.5, 8 x 400 (512) 19.7 / 18.8;
+// without it the two are alike there (12 heads, 1 x 500 13.7 / 13.6, 1 x 2048
+// 40.2 / 39.6) and from one workgroup per CU on this one is ahead (32 heads, 1
+// x 2048 48.3 / 46.6). Head dim 128 up to 512 rows, 16 heads: 1 x 500 (32
+// workgroups) 15.8 / 16.9, 4 x 500 (128) 17.4 / 18.4, 8 x 400 (256) 23.7 /
+// 20.4; past 512 rows it is ahead on any grid (1 x 1000 34.5 / 27.6).
+bool attention_wide(int hd, int H, int B, int max_len, int causal, int cus) {
+  const int64_t wgs = (static_cast<int64_t>(max_len) + 255) / 256 * H * B;
+  if (hd == 64) return max_len > 256 && (!causal || wgs > cus);
+  return max_len > 384 && (max_len > 512 || wgs >= cus);
+}
+
 hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void* k,
                             const void* v, int64_t row_stride, int H, int kv_group, int hd,
                             int causal, float scale, int B, int max_len, int T,
@@ -890,13 +907,13 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
                     static_cast<const bf16_t*>(v), row_stride, kv_group, causal, sl, cu_dev,
                     static_cast<bf16_t*>(out), out_stride, lse, T, H, H * B);
     };
-    // lengths from which the wide kernel pays: its comment
+    const bool wide = attention_wide(hd, H, B, max_len, causal, device_cu_count());
     if (hd == 64) {
-      if (max_len > 256) return go(attn_wide_kernel<64, 2, 4>, 256, 256);
+      if (wide) return go(attn_wide_kernel<64, 2, 4>, 256, 256);
       if (max_len > 128) return go(attn_mfma_kernel<64, 8>, 256, 512);
       return go(attn_mfma_kernel<64, 4>, 128, 256);
     }
-    if (max_len > 384) return go(attn_wide_kernel<128, 1, 8>, 256, 512);
+    if (wide) return go(attn_wide_kernel<128, 1, 8>, 256, 512);
     return go(attn_mfma_kernel<128, 4>, 128, 256);
   }
   if (dtype == 1)

@@ -268,6 +268,9 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
                             int causal, float scale, int B, int max_len, int T,
                             const int32_t* cu_dev, void* out, int64_t out_stride, float* lse);
 
+// the long-sequence kernel takes this bf16 call (head_dim 64 or 128)
+bool attention_wide(int hd, int H, int B, int max_len, int causal, int cus);
+
 // writes G partial score vectors [G][T] (G = head groups); returns G via *groups
 hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
                         int64_t row_stride, const float* lse, int H, int kv_group, int hd,

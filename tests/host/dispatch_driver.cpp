@@ -1,5 +1,6 @@
-// Host checks of how calls are laid out on the GPU: launch grids within HIP's
-// limits, every block of work reached exactly once. Prints "ok <checks>" and exits 0 when every check holds.
+// Host checks of how calls are laid out on the GPU and which kernel takes
+// them: launch grids within HIP's limits, every block of work reached exactly
+// once. Prints "ok <checks>" and exits 0 when every check holds.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -78,11 +79,26 @@ void head_order() {
       }
 }
 
+// Which attention kernel takes a call (256 CUs)
+void attentions() {
+  using zsa::attention_wide;
+  // head dim 64: past 256 rows, under the mask from more than one workgroup per CU on
+  CHECK_TRUE(!attention_wide(64, 12, 64, 256, 0, 256) && !attention_wide(64, 12, 64, 256, 1, 256));
+  CHECK_TRUE(attention_wide(64, 12, 1, 257, 0, 256) && attention_wide(64, 12, 16, 257, 1, 256));
+  CHECK_TRUE(!attention_wide(64, 12, 8, 500, 1, 256) && !attention_wide(64, 32, 4, 500, 1, 256));
+  CHECK_TRUE(attention_wide(64, 32, 8, 300, 1, 256) && attention_wide(64, 32, 8, 2048, 1, 256));
+  // head dim 128: past 512 rows, past 384 from one workgroup per CU on
+  CHECK_TRUE(!attention_wide(128, 32, 64, 384, 1, 256) && !attention_wide(128, 32, 1, 500, 0, 256));
+  CHECK_TRUE(!attention_wide(128, 16, 4, 500, 1, 256) && attention_wide(128, 16, 8, 400, 1, 256));
+  CHECK_TRUE(attention_wide(128, 1, 1, 513, 0, 256));
+}
+
 }  // namespace
 
 int main() {
   places();
   head_order();
+  attentions();
   printf("ok %d\n", g_checks);
   return 0;
 }

@@ -55,6 +55,27 @@ def test_attention_tiles_and_order(hd, causal, lens, H, hkv):
 
 
 @pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("lens,H,hkv", [([575, 576, 577, 0, 1, 33, 64, 449], 12, 4),  # tile edges, ragged, empty
+                                        ([512] * 5, 32, 32)])                         # whole tiles, heads in plain order
+def test_attention_causal_full_grid(hd, lens, H, hkv):
+    """Grids of more 256-query blocks than CUs, from where on head dim 64
+    takes the long-sequence kernel under the mask (and 128 up to 512 rows)."""
+    check(lens, H, hkv, hd, True, seed=hd + H)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_attention_moving_reference_full_grid(hd):
+    """As below, on such a grid."""
+    def rise(a, d, kvd):
+        i = np.arange(a.shape[0]) % 700
+        a[:, d:d + kvd] *= 0.2
+        a[:, d] = np.floor(i / 100.0) * 3.0
+        a[:, 0] = np.where(i % 3 == 0, 8.0 * math.sqrt(hd) / 8.0, 0.1)
+        return a
+    check([700] * 6, 16, 16, hd, True, seed=13 + hd, sharp=1.0, shape_scores=rise)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
 def test_attention_moving_reference(hd, causal):
     """Keys whose scores rise in steps along the sequence, far enough (20 exp2
