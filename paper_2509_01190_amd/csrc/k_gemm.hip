@@ -2744,16 +2744,25 @@ bool skinny_ok(int dtype, int M, int N, int K, const EpiParams& ep) {
 //   1024 x 768 x 768               /   8.5     10.3
 //   1024 x 768 x 3072              /  20.2     22.8
 // so it takes M <= 16, and up to 1024 rows while the 128 x 128 output
-// tiles are fewer than 64 (past 512 rows: 768-column outputs) and the 64 x
-// 64 ones fewer than 150, from where those (short_grid) are faster: few-row /
+// tiles are fewer than 64 (past 512 rows: 768-column outputs). Where
+// short_grid can give the product 64-wide tiles (wide_tiles_only below), it
+// leaves it those from 150 of them on: few-row /
 // 64 x 64, us, 640 x 768 x 3072 (120 tiles) 15.0 / 16.6, 160 x 3072 x 768
 // with GELU (144) 7.1 / 7.5, 800 x 768 x 3072 (156) 19.7 / 16.3, 800 x 768 x
-// 768 9.7 / 7.4, 300 x 2304 x 768 (180) 9.1 / 7.1.
-bool skinny_pays(int M, int N, int K) {
-  (void)K;
+// 768 9.7 / 7.4, 300 x 2304 x 768 (180) 9.1 / 7.1. Without such tiles the
+// few-row kernel stays ahead of what is left: rotary heads of 128, 100 x 6144
+// x 4096 28.8 against 41.5 on 128 x 128 tiles, 256 x 3072 x 1024 14.6 against
+// 19.3; K not a multiple of 64, 800 x 768 x 3104 20.1 against 69.0 on the
+// fp32 matrix instructions, 300 x 2304 x 800 8.6 against 22.3.
+bool wide_tiles_only(int K, const EpiParams& ep) {
+  // whole K slices; a rotary head must lie within a tile's columns
+  return K % kBK != 0 || (ep.epi == EPI_ROPE && ep.head_dim > 64);
+}
+
+bool skinny_pays(int M, int N, int K, const EpiParams& ep) {
   const long tiles128 = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
   const long tiles64 = static_cast<long>((M + 63) / 64) * ((N + 63) / 64);
-  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64 && tiles64 < 150);
+  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64 && (tiles64 < 150 || wide_tiles_only(K, ep)));
 }
 
 // Tile shape of a product whose 128 x 128 tiles are at most one per CU (none
@@ -2782,15 +2791,16 @@ bool skinny_pays(int M, int N, int K) {
 //   1300 x 2048 x 8192       76.5 / 74.6 / 77.7 / 72.8   (176 of 128 x 128)
 //   900 x 4096 x 14336       144 / 176 / 148 / 133       (256 of 128 x 128)
 // `split`: the caller's workspace lets the product split K, which keeps
-// longer K on under 0.7 of a 128 x 128 tile per CU.
-enum ShortGrid { kNoShort, kShort64, kShort128x64, kShort128 };
+// longer K on under 0.7 of a 128 x 128 tile per CU, and there also the rotary
+// heads of 128 (split / 128 x 128 on 8 waves: 128 x 12288 x 4096, 96 tiles,
+// 33.2 / 42.8; 300 x 6144 x 4096, 144 tiles, 38.1 / 43.5; one tile per CU or
+// nearly: 512 x 6144 x 4096, 192 tiles, 128 x 128 on 4 waves 56.1 / 47.2).
 ShortGrid short_grid(int M, int N, int K, const EpiParams& ep, bool split) {
   if (K % kBK != 0) return kNoShort;
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const long cus = device_cus(), t64 = tiles(64, 64);
-  if (tiles(128, 128) > cus || (split && K > 4096)) return kNoShort;
-  // a rotary head must lie within a tile's columns
-  const bool narrow = ep.epi != EPI_ROPE || ep.head_dim <= 64;
+  const bool narrow = !wide_tiles_only(K, ep);
+  if (tiles(128, 128) > cus || (split && (K > 4096 || !narrow))) return kNoShort;
   if (narrow && t64 <= 2 * cus)
     return K >= 2048 && t64 > cus && tiles(128, 64) <= cus ? kShort128x64 : kShort64;
   return K >= 2048 ? kShort128 : kNoShort;
@@ -2914,7 +2924,7 @@ hipError_t launch_rope_table(hipStream_t s, const int32_t* pos, int M, const Epi
 }
 
 bool gemm_takes_skinny(int dtype, int M, int N, int K, const EpiParams& ep) {
-  return gemm_tile_override() == 0 && skinny_ok(dtype, M, N, K, ep) && skinny_pays(M, N, K);
+  return gemm_tile_override() == 0 && skinny_ok(dtype, M, N, K, ep) && skinny_pays(M, N, K, ep);
 }
 
 hipError_t launch_gemm(hipStream_t s, int dtype, const void* x, int M, int K, const void* w,

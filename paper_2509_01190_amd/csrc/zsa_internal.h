@@ -255,8 +255,11 @@ struct PreNorm {
   float eps;
 };
 bool skinny_ok(int dtype, int M, int N, int K, const EpiParams& ep);
-bool skinny_pays(int M, int N, int K);  // launch_gemm takes it for such shapes
+bool skinny_pays(int M, int N, int K, const EpiParams& ep);  // launch_gemm takes it for such shapes
 bool skinny_norm_ok(int M, int N, int K);
+// tiles launch_gemm takes for a bf16 product of few output tiles
+enum ShortGrid { kNoShort, kShort64, kShort128x64, kShort128 };
+ShortGrid short_grid(int M, int N, int K, const EpiParams& ep, bool split);
 // launch_gemm runs this product on the few-row kernel
 bool gemm_takes_skinny(int dtype, int M, int N, int K, const EpiParams& ep);
 hipError_t launch_gemm_skinny(hipStream_t s, const void* x, int M, int K, const void* w, int N,

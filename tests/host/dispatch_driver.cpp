@@ -79,6 +79,43 @@ void head_order() {
       }
 }
 
+// Which kernel takes a bf16 product of few output tiles (256 CUs)
+void products() {
+  using namespace zsa;
+  auto ep = [](int epi, int head_dim) {
+    EpiParams e{};
+    e.epi = epi;
+    e.head_dim = head_dim;
+    return e;
+  };
+  struct Case { int M, N, K, epi, head_dim; bool few_row; ShortGrid split, whole; };
+  const Case cases[] = {
+      {16, 768, 768, EPI_NONE, 0, true, kShort64, kShort64},
+      // either side of 150 64 x 64 tiles
+      {640, 768, 3072, EPI_RESIDUAL, 0, true, kShort64, kShort64},
+      {800, 768, 3072, EPI_RESIDUAL, 0, false, kShort64, kShort64},
+      {300, 2304, 768, EPI_ROPE, 64, false, kShort64, kShort64},
+      // K no multiple of 64: no tiled bf16 kernel takes it
+      {640, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},
+      {800, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},
+      {300, 2304, 800, EPI_NONE, 0, true, kNoShort, kNoShort},
+      // rotary heads of 128 lie in no 64-wide tile
+      {65, 6144, 4096, EPI_ROPE, 128, true, kNoShort, kShort128},
+      {128, 6144, 4096, EPI_ROPE, 128, true, kNoShort, kShort128},
+      {256, 3072, 1024, EPI_ROPE, 128, true, kNoShort, kNoShort},
+      {128, 12288, 4096, EPI_ROPE, 128, false, kNoShort, kShort128},
+      {512, 6144, 4096, EPI_ROPE, 128, false, kNoShort, kShort128},
+      {1100, 2048, 4160, EPI_NONE, 0, false, kNoShort, kShort128},
+  };
+  for (const Case& c : cases) {
+    fprintf(stderr, "product: %d x %d x %d, epilogue %d, heads of %d\n", c.M, c.N, c.K, c.epi, c.head_dim);
+    const EpiParams e = ep(c.epi, c.head_dim);
+    CHECK_TRUE(gemm_takes_skinny(1, c.M, c.N, c.K, e) == c.few_row);
+    CHECK_TRUE(short_grid(c.M, c.N, c.K, e, true) == c.split);
+    CHECK_TRUE(short_grid(c.M, c.N, c.K, e, false) == c.whole);
+  }
+}
+
 // Which attention kernel takes a call (256 CUs)
 void attentions() {
   using zsa::attention_wide;
@@ -98,6 +135,7 @@ void attentions() {
 int main() {
   places();
   head_order();
+  products();
   attentions();
   printf("ok %d\n", g_checks);
   return 0;

@@ -54,3 +54,29 @@ def test_linear_short_grids(m, n, k, epi, split):
     elif epi == zsa.EPI_ROPE:
         z[:, :cols] = O.rope(z[:, :cols], pos[rows].astype(np.int64), cols // hd, 1e4)
     assert_close(f64(y[rt]), z, 1e-2, f"{m}x{n}x{k} epilogue {epi}")
+
+
+@pytest.mark.parametrize("m,n,k,hd", [(640, 768, 3104, 0),    # K no multiple of 64, either side of 150 64x64 tiles
+                                      (800, 768, 3104, 0),
+                                      (100, 6144, 4096, 128),  # rotary heads of 128: few-row
+                                      (256, 3072, 1024, 128),  # ... its most rows at this width
+                                      (130, 12288, 2112, 128), # ... split K, or 128x128 tiles without the room for it
+                                      (512, 6144, 2048, 128)]) # ... 128x128 tiles on most CUs
+@pytest.mark.parametrize("split", [True, False])
+def test_linear_without_narrow_tiles(m, n, k, hd, split):
+    """Products that no 64-wide tile takes."""
+    g = np.random.default_rng(m + n + k)
+    xd = to_dev(g.standard_normal((m, k)).astype(np.float32), "bf16")
+    wd = to_dev((g.standard_normal((n, k)) / math.sqrt(k)).astype(np.float32), "bf16")
+    bd = to_dev((0.1 * g.standard_normal(n)).astype(np.float32), "bf16")
+    pos = g.integers(0, 4096, m).astype(np.int32)
+    cols = n // 2 // hd * hd if hd else 0
+    y = zsa.linear(xd, wd, bd, zsa.EPI_ROPE if hd else zsa.EPI_NONE,
+                   pos=torch.from_numpy(pos).to(dev()) if hd else None, head_dim=hd, rope_cols=cols, rope_theta=1e4,
+                   split=split)
+    rows = np.unique(np.concatenate([np.arange(17), np.arange(m - 33, m), g.integers(0, m, 16)]))
+    rt = torch.from_numpy(rows).to(dev())
+    z = f64(xd[rt]) @ f64(wd).T + f64(bd)
+    if hd:
+        z[:, :cols] = O.rope(z[:, :cols], pos[rows].astype(np.int64), cols // hd, 1e4)
+    assert_close(f64(y[rt]), z, 1e-2, f"{m}x{n}x{k}, rotary heads of {hd}")
