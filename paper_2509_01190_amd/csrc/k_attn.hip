@@ -278,24 +278,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
           // pb's slots 0..3 hold keys kb + 4 half + 0..3 and slots 4..7 keys
           // kb + 8 + 4 half + 0..3 (kb = 32 ks + 16 (g & 1)); the V^T
           // fragment gives channel ct * 32 + l32 the same keys in the same
-          // slots. A transposing read gives each lane of a 16-lane group
-          // element c (its lane number in the group) of four 16-element
-          // rows, row r pieced together from the 4-element runs at the
-          // addresses of the group's lanes 4r .. 4r + 3: so the group's
-          // lanes point at key rows kb + 4 half + r and channel runs
-          // 16 ((lane / 16) & 1) + 4 (lane & 3).
-          typedef short s16x4 __attribute__((ext_vector_type(4)));
-          typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-          typedef __attribute__((address_space(3))) const char lds_char;
+          // slots: a 16-lane group's lanes point at key rows kb + 4 half + r
+          // and channel runs 16 ((lane / 16) & 1) + 4 (lane & 3).
           const bf16_t* tr0 = Vt + (ks * 32 + (g & 1) * 16 + 4 * half + ((lane & 15) >> 2)) * KLD +
                               16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
           for (int ct = 0; ct < HD / 32; ++ct) {
             const bf16_t* vr = tr0 + ct * 32;
-            const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)vr));
-            const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(vr + 8 * KLD)));
-            const uint2 l2 = __builtin_bit_cast(uint2, lo4), h2 = __builtin_bit_cast(uint2, hi4);
-            const u32x4 av = {l2.x, l2.y, h2.x, h2.y};
+            const u32x4 av = lds_read_columns(vr, vr + 8 * KLD);
             o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av), pb, o[ct], 0, 0, 0);
           }
           continue;
@@ -361,12 +351,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
 //    are both taken relative to the reference.
 //  * K and V tiles of 64 keys go straight to LDS, two tiles ahead, one
 //    barrier per tile: staged through registers they cost 50 of 310 us (8 x
-//    2048 rows, 16 heads of 128). The loads are asm without outputs, as the
-//    compiler waits for a load it knows to write LDS before any later LDS
-//    read; turn_over() waits for them. Rows are unpadded; 16-byte chunk c of
+//    2048 rows, 16 heads of 128). Rows are unpadded; 16-byte chunk c of
 //    row r lies at c ^ ksw(r) (K: the 16 rows of a read phase fall on all 64
 //    banks) or c ^ vsw(r) (V: the four rows a transposing read takes do).
-// Same box, us, this kernel against the register-staged one below in the same
+// Same box, us, this kernel against the register-staged one above in the same
 // workgroup order: 4 x 4096 causal, 32 heads of 128, 543 / 603; 8 x 2048, 32
 // heads of 64, 186 / 205 causal, 291 / 331 without; 32 x 512, 12 heads of 64,
 // 37.2 / 40.7; 4 x 500 causal, 32 heads of 128, 20.7 / 22.7; and where it
@@ -384,9 +372,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int RPL = 1024 / RB, LPW = HALF / 1024 / NW;  // rows per load, loads per wave and operand
   static_assert(LPW * NW * 1024 == HALF && NW % 4 == 0, "tile split");
   __shared__ __align__(1024) unsigned char smem[SBYTES];
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  typedef __attribute__((address_space(3))) const char lds_char;
 
   Place at;
   if (!place(H, kv_group, pairs, false, &at)) return;
@@ -402,30 +387,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int hk = h / kv_group;
   const uint32_t row_bytes = static_cast<uint32_t>(rs * 2);
   const uint32_t seq_bytes = static_cast<uint32_t>(n) * row_bytes;
-  auto resource = [&](const bf16_t* p) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p + static_cast<int64_t>(lo) * rs + hk * HD);
-    const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(seq_bytes))), 0x00020000u};
-    return r;
-  };
-  const u32x4 kres = resource(K), vres = resource(V);
+  const u32x4 kres = buffer_resource(K + static_cast<int64_t>(lo) * rs + hk * HD, seq_bytes);
+  const u32x4 vres = buffer_resource(V + static_cast<int64_t>(lo) * rs + hk * HD, seq_bytes);
   // K row r keeps its 16-byte chunk c at c ^ ksw(r), V row r at c ^ vsw(r)
   auto ksw = [](int r) { return HD == 64 ? (r >> 1) & 7 : r & 15; };
   auto vsw = [](int r) { return HD == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
   const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
   const uint32_t koff = lrow * row_bytes + (((lane % CPR) ^ ksw(lrow)) << 4);
   const uint32_t voff = lrow * row_bytes + (((lane % CPR) ^ vsw(lrow)) << 4);
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
-  // (m0, which the loads take their LDS address from, is set by the compiler
-  // right before each use of its own)
+  const uint32_t lds0 = lds_address(smem) + wave * 1024;
   auto load_tile = [&](int t, int buf) {
     const uint32_t t0 = static_cast<uint32_t>(t) * (BK * row_bytes);
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const uint32_t d = lds0 + buf * BUF + i * (NW * 1024), so = t0 + i * (NW * RPL) * row_bytes;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(koff + so), "s"(kres) : "memory");
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(voff + so), "s"(vres) : "memory");
+      lds_load16(d, koff + so, kres);
+      lds_load16(d + HALF, voff + so, vres);
     }
   };
 
@@ -475,11 +452,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   };
   auto read_v = [&](const unsigned char* base, int g, int ct) {
     const unsigned char* vr = base + vaddr[ct] + g * (16 * RB);
-    const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)vr));
-    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(vr + 8 * RB)));
-    const uint2 l2 = __builtin_bit_cast(uint2, lo4), h2 = __builtin_bit_cast(uint2, hi4);
-    const u32x4 av = {l2.x, l2.y, h2.x, h2.y};
-    return __builtin_bit_cast(bf16x8_t, av);
+    return __builtin_bit_cast(bf16x8_t, lds_read_columns(vr, vr + 8 * RB));
   };
   const f32x16_t zero = {};
   auto row_max = [&](const f32x16_t& s) {
@@ -585,12 +558,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       pf[qb][0] = __builtin_bit_cast(bf16x8_t, pn[qb][0]);
       pf[qb][1] = __builtin_bit_cast(bf16x8_t, pn[qb][1]);
     }
-  };
-  // every wave's loads have landed, and all are past the tile before last
-  auto turn_over = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
   };
 
   int bp = 2, bc = 0, bn = 1;  // buffers of tiles t - 1, t, t + 1

@@ -440,24 +440,12 @@ __global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, int64_
 // ---------------------------------------------------------------------------
 // attention backward
 // ---------------------------------------------------------------------------
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(3))) const char lds_char;
-
 // Tile row r keeps its 16-byte chunk c at c ^ swizzle(r). The 16 rows of a
 // row read's phase fall on all 64 banks, and so do the four rows r .. r + 3
 // (r a multiple of four) by four chunks of a transposing read's.
 template <int HD>
 __device__ __forceinline__ constexpr int bwd_swizzle(int r) {
   return HD == 64 ? ((r >> 1) & 1) << 2 | ((r >> 2) & 1) << 1 | ((r >> 3) & 1) : (r & 3) << 2 | ((r >> 2) & 3);
-}
-
-__device__ __forceinline__ u32x4 buffer_resource(const void* p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
-                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
-                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
-  return r;
 }
 
 // The reading side of a tile of HD-wide rows: a lane's offsets of the row
@@ -472,9 +460,6 @@ struct TileReads {
     const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) row[kk] = l32 * RB + (((2 * kk + half) ^ bwd_swizzle<HD>(l32)) << 4);
-    // a transposing read gives each lane of a 16-lane group element (its
-    // number in the group) of four 16-element rows, row r pieced together
-    // from the runs at the addresses of the group's lanes 4r .. 4r + 3
     const int r = 4 * half + ((lane & 15) >> 2), ch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -487,11 +472,7 @@ struct TileReads {
   }
   // tile rows 16 g + ...
   __device__ __forceinline__ bf16x8_t cols(const unsigned char* tile, int g, int ct) const {
-    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(tile + lo[ct] + g * (16 * RB))));
-    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(tile + hi[ct] + g * (16 * RB))));
-    const uint2 a2 = __builtin_bit_cast(uint2, a), b2 = __builtin_bit_cast(uint2, b);
-    const u32x4 v = {a2.x, a2.y, b2.x, b2.y};
-    return __builtin_bit_cast(bf16x8_t, v);
+    return __builtin_bit_cast(bf16x8_t, lds_read_columns(tile + lo[ct] + g * (16 * RB), tile + hi[ct] + g * (16 * RB)));
   }
 };
 
@@ -502,22 +483,8 @@ __device__ __forceinline__ bf16x8_t pack_slots(const f32x16_t& v, int g) {
   return __builtin_bit_cast(bf16x8_t, w);
 }
 
-// every wave's tile loads have landed, and all waves are past the last tile
-__device__ __forceinline__ void bwd_turn_over() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 // Rows per tile: 64 at head dim 64, 32 at 128 (8 KB an operand either way),
-// two tiles in LDS. Loads are asm without outputs: the compiler would wait
-// for a load it knows to write LDS before any later LDS read. (m0 is set by
-// the compiler right before each use of its own.)
-#define ZSA_LDS_LOAD(width, lds, off, res)                                                              \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_" width " %1, %2, 0 offen lds" ::"s"(lds), \
-               "v"(off), "s"(res)                                                                       \
-               : "memory")
-
+// two tiles in LDS.
 template <int HD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -547,7 +514,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
   const uint32_t lchunk = ((lane % CPR) ^ bwd_swizzle<HD>(lrow)) << 4;
   const uint32_t qoff = lrow * q_row + lchunk, ooff = lrow * o_row + lchunk;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem));
+  const uint32_t lds0 = lds_address(smem);
   // queries before the first key see none of the keys (causal)
   const int qs = causal ? j0 : 0;
   const int ntile = (n - qs + QT - 1) / QT;
@@ -560,13 +527,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const uint32_t d = lds0 + buf * BUF + wave * 1024 + i * 4096;
-      ZSA_LDS_LOAD("dwordx4", d, qoff + static_cast<uint32_t>(i0 + i * 4 * RPL) * q_row, qres);
-      ZSA_LDS_LOAD("dwordx4", d + TB, ooff + static_cast<uint32_t>(i0 + i * 4 * RPL) * o_row, ores);
+      lds_load16(d, qoff + static_cast<uint32_t>(i0 + i * 4 * RPL) * q_row, qres);
+      lds_load16(d + TB, ooff + static_cast<uint32_t>(i0 + i * 4 * RPL) * o_row, ores);
     }
     if (wave < QT / 32) {
       const u32x4 lres = buffer_resource(LD + static_cast<int64_t>(h) * T + lo, static_cast<uint32_t>(n) * 8u);
-      ZSA_LDS_LOAD("dword", lds0 + buf * BUF + 2 * TB + wave * 256, static_cast<uint32_t>(i0) * 8u + (wave * 64 + lane) * 4u,
-                   lres);
+      lds_load4(lds0 + buf * BUF + 2 * TB + wave * 256, static_cast<uint32_t>(i0) * 8u + (wave * 64 + lane) * 4u, lres);
     }
   };
   load_tile(0, 0);
@@ -585,7 +551,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   const TileReads<HD> rd(lane);
   const f32x16_t zero = {};
   for (int t = 0; t < rounds; ++t) {
-    bwd_turn_over();
+    turn_over();
     if (t + 1 < rounds) load_tile(t + 1, (t + 1) & 1);
     const int i_tile = qs + (t % ntile) * QT;
     const unsigned char* tq = smem + (t & 1) * BUF;
@@ -685,7 +651,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   const uint32_t row_bytes = static_cast<uint32_t>(rs * 2);
   const int lrow = wave * RPL + lane / CPR;  // tile row of the wave's first load
   const uint32_t off = lrow * row_bytes + (((lane % CPR) ^ bwd_swizzle<HD>(lrow)) << 4);
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
+  const uint32_t lds0 = lds_address(smem) + wave * 1024;
   // keys past the sequence read as zeros (masked)
   const u32x4 kres = buffer_resource(K + static_cast<int64_t>(lo) * rs + hk * HD, static_cast<uint32_t>(n) * row_bytes);
   const u32x4 vres = buffer_resource(V + static_cast<int64_t>(lo) * rs + hk * HD, static_cast<uint32_t>(n) * row_bytes);
@@ -693,8 +659,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const uint32_t d = lds0 + buf * BUF + i * 4096, o = off + static_cast<uint32_t>(t * KT + i * 4 * RPL) * row_bytes;
-      ZSA_LDS_LOAD("dwordx4", d, o, kres);
-      ZSA_LDS_LOAD("dwordx4", d + TB, o, vres);
+      lds_load16(d, o, kres);
+      lds_load16(d + TB, o, vres);
     }
   };
   load_tile(0, 0);
@@ -714,7 +680,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   const int kend = causal ? min(n, q0 + BQ) : n;
   const int nt = (kend + KT - 1) / KT;
   for (int t = 0; t < nt; ++t) {
-    bwd_turn_over();
+    turn_over();
     if (t + 1 < nt) load_tile(t + 1, (t + 1) & 1);
     const unsigned char* tk = smem + (t & 1) * BUF;
 #pragma unroll 1

@@ -213,7 +213,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   constexpr int RPL = 1024 / RB, LPW = QBYTES / 1024 / NW;  // rows per load, loads per wave
   static_assert(LPW * NW * 1024 == QBYTES, "tile split");
   __shared__ __align__(1024) unsigned char smem[NB * BUF];
-  typedef __attribute__((address_space(3))) const char lds_char;
 
   Place at;
   if (!place(H, kv_group, pairs, true, &at)) return;
@@ -227,16 +226,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   const int wk0 = j0 + wave * KW;  // the wave's first key
 
   const uint32_t row_bytes = static_cast<uint32_t>(rs * 2);
-  auto resource = [](const void* p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
-    return r;
-  };
   // rows past the sequence read as zeros (masked)
-  const u32x4 qres = resource(Q + static_cast<int64_t>(lo) * rs + h * HD, static_cast<uint32_t>(n) * row_bytes);
-  const u32x4 lres = resource(lse + static_cast<int64_t>(h) * T + lo, static_cast<uint32_t>(n) * 4u);
+  const u32x4 qres = buffer_resource(Q + static_cast<int64_t>(lo) * rs + h * HD, static_cast<uint32_t>(n) * row_bytes);
+  const u32x4 lres = buffer_resource(lse + static_cast<int64_t>(h) * T + lo, static_cast<uint32_t>(n) * 4u);
   // row r keeps its 16-byte chunk c at c ^ qsw(r): the 16 rows of a read
   // phase fall on all banks
   auto qsw = [](int r) { return HD == 64 ? (r >> 1) & 7 : r & 15; };
@@ -246,23 +238,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
     const int r = (wave + NW * i) * RPL + lane / CPR;
     qoff[i] = r * row_bytes + (((lane % CPR) ^ qsw(r)) << 4);
   }
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem));
-  // asm without outputs: the compiler would wait for a load it knows to write
-  // LDS before any later LDS read; turn_over() waits. (m0 is set by the
-  // compiler right before each use of its own.)
+  const uint32_t lds0 = lds_address(smem);
   auto load_tile = [&](int t, int buf) {
     const uint32_t t0 = static_cast<uint32_t>(t) * (QT * row_bytes);
 #pragma unroll
-    for (int i = 0; i < LPW; ++i)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(
-                       lds0 + buf * BUF + (wave + NW * i) * 1024),
-                   "v"(qoff[i] + t0), "s"(qres)
-                   : "memory");
-    if (wave == 0)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(
-                       lds0 + buf * BUF + QBYTES),
-                   "v"(static_cast<uint32_t>(t * QT + lane) * 4u), "s"(lres)
-                   : "memory");
+    for (int i = 0; i < LPW; ++i) lds_load16(lds0 + buf * BUF + (wave + NW * i) * 1024, qoff[i] + t0, qres);
+    if (wave == 0) lds_load4(lds0 + buf * BUF + QBYTES, static_cast<uint32_t>(t * QT + lane) * 4u, lres);
   };
 
   const int t0 = causal ? j0 / QT : 0, nt = (n + QT - 1) / QT;
@@ -362,12 +343,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
         colsum[kb] += a;
       }
     }
-  };
-  // every wave's loads have landed, and all are past the tile before last
-  auto turn_over = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
   };
   int bc = 0, bn = 1, bf = 2;  // buffers of tiles t, t + 1, t + 2
   auto turn = [&]() {

@@ -55,9 +55,6 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   constexpr int FM = TILE / 32 / WM, FN = TILE / 32 / WN;  // 32-wide fragments per wave
   static_assert(LPW * NW * 1024 == HALF, "slice split");
   __shared__ __align__(1024) unsigned char smem[NB * BUF];
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  typedef __attribute__((address_space(3))) const char lds_char;
 
   // an XCD (workgroup number mod 8) takes neighbouring tiles of one split,
   // whose rows its L2 then holds
@@ -80,19 +77,15 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   const uint32_t a_row = static_cast<uint32_t>(p.m) * 2, b_row = static_cast<uint32_t>(p.n) * 2;
   const uint32_t lchunk = ((lane % CPR) ^ sw(lrow)) << 4;
   const uint32_t aoff = lrow * a_row + lchunk, boff = lrow * b_row + lchunk;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem)) + wave * 1024;
+  const uint32_t lds0 = lds_address(smem) + wave * 1024;
   // the resource covers this slice's rows from the tile's first column on:
   // rows past the split (or the whole slice, past the last) read as zeros;
   // columns past the matrix read its next row and feed outputs that are not
   // stored
   auto resource = [&](const bf16_t* base, int width, int col, int r0) {
-    const uint64_t at = reinterpret_cast<uint64_t>(base + static_cast<int64_t>(r0) * width + col);
     const int live = max(0, min(BK, r_end - r0));
     const uint32_t bytes = live > 0 ? static_cast<uint32_t>(live) * width * 2 - col * 2 : 0;
-    const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(at))),
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(at >> 32))) & 0xffffu,
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
-    return r;
+    return buffer_resource(base + static_cast<int64_t>(r0) * width + col, bytes);
   };
   auto load_slice = [&](int t, int buf) {
     const int r0 = t < slices ? r_begin + t * BK : r_end;
@@ -100,15 +93,13 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const uint32_t d = lds0 + buf * BUF + i * (NW * 1024);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d), "v"(aoff + i * (NW * RPL) * a_row), "s"(ar) : "memory");
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(d + HALF), "v"(boff + i * (NW * RPL) * b_row), "s"(br) : "memory");
+      lds_load16(d, aoff + i * (NW * RPL) * a_row, ar);
+      lds_load16(d + HALF, boff + i * (NW * RPL) * b_row, br);
     }
   };
 
   // a fragment: columns 32 c + l32 of slice rows 16 g + 4 half + 0 .. 3 and
-  // + 8 of these. A transposing read gives each lane of a 16-lane group
-  // element (its number in the group) of four 16-element rows, row r pieced
-  // together from the runs at the addresses of the group's lanes 4r .. 4r + 3.
+  // + 8 of these
   const int vrow = 4 * half + ((lane & 15) >> 2);
   const int vch = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
   const uint32_t f0 = vrow * RB + (lane & 1) * 8;
@@ -118,11 +109,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
   for (int j = 0; j < FN; ++j) fb[j] = HALF + f0 + (((4 * (wn * FN + j) + vch) ^ sw(vrow)) << 4);
   auto frag = [&](const unsigned char* at) {
-    const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)at));
-    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)(at + 8 * RB)));
-    const uint2 l2 = __builtin_bit_cast(uint2, lo4), h2 = __builtin_bit_cast(uint2, hi4);
-    const u32x4 v = {l2.x, l2.y, h2.x, h2.y};
-    return __builtin_bit_cast(bf16x8_t, v);
+    return __builtin_bit_cast(bf16x8_t, lds_read_columns(at, at + 8 * RB));
   };
 
   f32x16_t acc[FM][FN] = {};

@@ -94,6 +94,57 @@ __device__ __forceinline__ uint4 keep16(const uint4& v, bool keep) {
 }
 
 // ---------------------------------------------------------------------------
+// tiles straight from memory to LDS, and fragments out of them
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) const char lds_char;
+
+// a buffer of `bytes` bytes (wave-uniform): loads past it read as zeros
+__device__ __forceinline__ u32x4 buffer_resource(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const u32x4 r = {static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a))),
+                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) & 0xffffu,
+                   static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes))), 0x00020000u};
+  return r;
+}
+
+// The lanes' 16 (4) bytes at res + off, to 16 (4) bytes a lane from LDS
+// address lds on (wave-uniform). In asm, without outputs: the compiler would
+// wait for a load it knows to write LDS before any later LDS read; the caller
+// waits (turn_over). The LDS address is an operand in m0, so that the compiler
+// sets that register itself and knows what it holds.
+__device__ __forceinline__ void lds_load16(uint32_t lds, uint32_t off, const u32x4& res) {
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(res) : "memory");
+}
+__device__ __forceinline__ void lds_load4(uint32_t lds, uint32_t off, const u32x4& res) {
+  asm volatile("s_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(res) : "memory");
+}
+// address of a __shared__ array for the loads
+__device__ __forceinline__ uint32_t lds_address(const void* smem) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)smem));
+}
+
+// every wave's tile loads have landed, and all waves are past their LDS reads
+__device__ __forceinline__ void turn_over() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Eight rows of a column per lane out of a tile kept in rows: two transposing
+// reads. Each gives a lane of a 16-lane group element (its number in the
+// group) of four 16-element rows, row r pieced together from the 8-byte runs
+// at the addresses of the group's lanes 4r .. 4r + 3.
+__device__ __forceinline__ u32x4 lds_read_columns(const void* first, const void* second) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)first));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((lds_char*)second));
+  const uint2 a2 = __builtin_bit_cast(uint2, a), b2 = __builtin_bit_cast(uint2, b);
+  const u32x4 v = {a2.x, a2.y, b2.x, b2.y};
+  return v;
+}
+
+// ---------------------------------------------------------------------------
 // placement of attention workgroups
 // ---------------------------------------------------------------------------
 // Which (sequence, head, block of queries or keys) an attention or score

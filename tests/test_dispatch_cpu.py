@@ -3,6 +3,7 @@ the host: the placement functions and dispatch rules are compiled into a small
 driver (and, for the rules, linked with the built library), which no GPU is
 needed for."""
 import os
+import re
 import shutil
 import subprocess
 import tempfile
@@ -31,3 +32,20 @@ def test_placement_and_dispatch_rules():
         assert r.stdout.startswith("ok "), r.stdout
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
+
+
+def test_inline_asm_writes_no_unnamed_m0():
+    """m0 holds the LDS address of loads to LDS. The compiler cannot see into
+    an asm text: one that wrote m0 without naming it could break a use of the
+    compiler's own, and it takes no such register as overwritten. So no text
+    writes it; it is an operand."""
+    csrc = os.path.join(ROOT, "paper_2509_01190_amd", "csrc")
+    seen = 0
+    for name in sorted(os.listdir(csrc)):
+        for text in re.findall(r"\basm\b[^;]*?\(((?:[^;]|\\n)*?)\)\s*;", open(os.path.join(csrc, name)).read()):
+            template = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', text.split(":")[0]))
+            assert not re.search(r"\b\w+\s+m0\s*,", template), f"{name}: {template}"
+            if "lds" in template:
+                seen += 1
+                assert '"{m0}"' in text, f"{name}: {template}"
+    assert seen >= 2
