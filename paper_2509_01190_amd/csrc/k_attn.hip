@@ -654,19 +654,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // A vector-ALU kernel with one query per thread held this place: 37.1 us on 4 x
 // 64 rows, 4 heads of 32, and 256 us on 8 ragged sequences of up to 200 rows,
 // 12 heads of 64 (now 5.8 and 22.2).
-template <typename T>
-__device__ __forceinline__ float4 load4(const T* p);
-template <>
-__device__ __forceinline__ float4 load4<float>(const float* p) {
-  return *reinterpret_cast<const float4*>(p);
-}
-template <>
-__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
-  const uint2 v = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
-}
-
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const T* __restrict__ Q,
                                                        const T* __restrict__ K,

@@ -1202,19 +1202,6 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(
 // fp32 GEMM on the fp32 matrix instructions (fp32 storage, and bf16 products
 // whose K no bf16 kernel takes: operands widened on load, fp32 products)
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ float4 load4(const T* p);
-template <>
-__device__ __forceinline__ float4 load4<float>(const float* p) {
-  return *reinterpret_cast<const float4*>(p);
-}
-template <>
-__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
-  const uint2 v = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
-}
-
 // BM x BN tile on four waves (2 x 2, TM x TN blocks of 32 x 32 each), K in
 // 32-wide slices through two LDS stages, the next slice's loads in registers
 // meanwhile. v_mfma_f32_32x32x2_f32: lane l gives row l % 32 and K slots

@@ -393,19 +393,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
 // that summed all heads of a key in one thread held this place: 94 us on
 // 4 x 64 rows, 4 heads of 32, and 1657 us on 8 ragged sequences of up
 // to 200 rows, 12 heads of 64 (now 6.5 and 17.7 with the sum over heads).
-template <typename T>
-__device__ __forceinline__ float4 load4(const T* p);
-template <>
-__device__ __forceinline__ float4 load4<float>(const float* p) {
-  return *reinterpret_cast<const float4*>(p);
-}
-template <>
-__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
-  const uint2 v = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
-}
-
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void score_f32_kernel(const T* __restrict__ Q,
                                                         const T* __restrict__ K, int64_t rs,

@@ -144,6 +144,20 @@ __device__ __forceinline__ u32x4 lds_read_columns(const void* first, const void*
   return v;
 }
 
+// four consecutive elements in fp32
+template <typename T>
+__device__ __forceinline__ float4 load4(const T* p);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* p) {
+  return *reinterpret_cast<const float4*>(p);
+}
+template <>
+__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+
 // ---------------------------------------------------------------------------
 // placement of attention workgroups
 // ---------------------------------------------------------------------------
