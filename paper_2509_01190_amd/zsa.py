@@ -403,8 +403,10 @@ class Stack:
 
     def layer_forward(self, layer: int, hidden: torch.Tensor, pos: torch.Tensor, seqs: Seqs,
                       keep_rate=None, want_scores: bool = False, want_kept: bool = False):
-        """One block (0-based ``layer``); returns a dict with x, pos, seqs
-        and optionally scores / kept_rows."""
+        """One block (0-based ``layer``), queued on the current stream without
+        waiting for it; returns a dict with x, pos, seqs, cu_dev (the offsets
+        on the device, a tensor of the caller's own) and optionally scores /
+        kept_rows."""
         _require_cuda(hidden, pos)
         dev = hidden.device
         T = seqs.total
@@ -430,7 +432,9 @@ class Stack:
             _stream(dev), ctypes.byref(self.cfg), ctypes.byref(w), _p(hidden), _p(pos),
             seqs.batch, _hp32(seqs.host), _p(seqs.dev), kr_p, _p(x_out), _p(pos_out),
             _hp32(cu_out), _p(cu_out_dev), _p(scores), _p(kept), _p(ws), wsz))
-        out_seqs = Seqs._of(cu_out, cu_out_dev)
+        # the offsets go on to the next block: what the caller does to cu_dev must not
+        # reach them (the sum takes 1.5 us on the stream, clone()'s copy 5)
+        out_seqs = Seqs._of(cu_out, cu_out_dev + 0)
         res = {"x": x_out[:t_out], "pos": pos_out[:t_out], "seqs": out_seqs,
                "cu_dev": cu_out_dev}
         if want_scores:

@@ -135,3 +135,19 @@ def test_layers_chained_without_waiting(mark):
     assert a["seqs"].lengths == (lens if mark else [int(c) for c in zsa.keep_schedule(lens, rates, 5, 1)[0]])
     assert np.array_equal(a["seqs"].dev.cpu().numpy(), a["seqs"].host)
     assert torch.equal(b["x"], ref["x"]) and torch.equal(b["pos"], ref["pos"])
+
+
+def test_layer_offsets_are_the_callers_own():
+    """Writing into one result (the device offsets) leaves the others as they
+    are: the returned Seqs still drives the next block."""
+    lens, rates = [40, 9], [0.5, 1.0]
+    _, stack, xd, _, _ = _setup(W.ENCODER, "bf16", 256, 4, 512, lens, seed=35)
+    seqs = zsa.Seqs(lens, dev())
+    posd = torch.from_numpy(W.positions(lens)).to(dev())
+    for kr in (rates, None):
+        a = stack.layer_forward(0, xd, posd, seqs, keep_rate=kr)
+        ref = stack.layer_forward(0, a["x"], a["pos"], a["seqs"])["x"].clone()
+        a["cu_dev"].zero_()
+        assert np.array_equal(a["seqs"].dev.cpu().numpy(), a["seqs"].host)
+        assert torch.equal(stack.layer_forward(0, a["x"], a["pos"], a["seqs"])["x"], ref)
+        assert np.array_equal(seqs.dev.cpu().numpy(), seqs.host)
