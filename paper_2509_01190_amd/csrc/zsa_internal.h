@@ -158,6 +158,20 @@ __device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
                      __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
 }
 
+// The sum of column c over the 32 row lanes of a workgroup's partial sums, in
+// pairs: added one after another the 32 roundings add up (k_wgrad.hip has
+// the errors)
+__device__ __forceinline__ float lane_rows_total(const float (&red)[32][33], int c) {
+  float v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = red[k][c] + red[k + 16][c];
+#pragma unroll
+  for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+    for (int k = 0; k < w; ++k) v[k] += v[k + w];
+  return v[0];
+}
+
 // ---------------------------------------------------------------------------
 // placement of attention workgroups
 // ---------------------------------------------------------------------------

@@ -68,3 +68,21 @@ def test_weight_gradients(kind, heads, hd, ff, lens, prune):
             assert rel_l2(got[p.d_model * 2:], v[p.d_model * 2:]) <= 2e-2
         else:
             assert rel_l2(got, v) <= 2e-2, name
+
+
+@pytest.mark.parametrize("d,ff,rows", [(768, 3072, 4000),   # 128-wide tiles, three row splits
+                                       (768, 768, 4000),    # 64-wide
+                                       (2048, 8192, 2100)]) # 256-wide
+def test_bias_gradient_precision(d, ff, rows):
+    """The down projection's bias gradient is the column sums of dy, whose
+    bf16 rows are given: of the same sign, where the roundings of a long chain
+    of additions add up. In levels the sums stay within one unit, 2^-24, of
+    the 64-bit ones (2-norm over the columns); in one chain per wave they were
+    8.0e-8 off at the first size."""
+    p = W.shrink(W.PRESETS["dec1b"], kind=W.ENCODER, causal=False, n_layers=1, d_model=d, n_heads=d // 64,
+                 d_ff=ff, batch=rows // 100, prune_after=(), n_kv_heads=0)
+    lens, stack, xd, posd, _, _ = build(p, 5, [100] * (rows // 100), sharp=2.0)
+    g = np.random.default_rng(7)
+    dy = to_dev(np.abs(g.standard_normal((sum(lens), d))).astype(np.float32), "bf16")
+    _, grads = stack.backward(xd, posd, zsa.Seqs(lens, dev()), (), [1.0] * len(lens), dy)
+    assert rel_l2(f64(grads[0]["b_down"]), f64(dy).sum(axis=0)) <= 2.0 ** -24
