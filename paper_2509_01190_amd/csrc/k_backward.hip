@@ -41,27 +41,11 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* v);
-template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float* v) {
+__device__ __forceinline__ void load8(const bf16_t* p, float* v) {
   unpack16(*reinterpret_cast<const uint4*>(p), v, bf16_t());
 }
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, float* v) {
-  unpack16(reinterpret_cast<const uint4*>(p)[0], v, 0.f);
-  unpack16(reinterpret_cast<const uint4*>(p)[1], v + 4, 0.f);
-}
-template <typename T>
-__device__ __forceinline__ void store8(T* p, const float* v);
-template <>
-__device__ __forceinline__ void store8<bf16_t>(bf16_t* p, const float* v) {
+__device__ __forceinline__ void store8(bf16_t* p, const float* v) {
   *reinterpret_cast<uint4*>(p) = pack16(v, bf16_t());
-}
-template <>
-__device__ __forceinline__ void store8<float>(float* p, const float* v) {
-  reinterpret_cast<uint4*>(p)[0] = pack16(v, 0.f);
-  reinterpret_cast<uint4*>(p)[1] = pack16(v + 4, 0.f);
 }
 
 // ---------------------------------------------------------------------------
@@ -224,13 +208,13 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const bf16_t* __restrict_
       const int c = col(k);
       if (c < d) {
         float o[8], rv[8];
-        if (res != nullptr) load8<bf16_t>(res + base + c, rv);
+        if (res != nullptr) load8(res + base + c, rv);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float xh = (unpack(xv[k], e) - mean) * rstd;
           o[e] = rstd * (unpack(dv[k], e) * unpack(gv[k], e) - m1 - xh * m2) + (res != nullptr ? rv[e] : 0.f);
         }
-        store8<bf16_t>(out + base + c, o);
+        store8(out + base + c, o);
       }
     }
   }
@@ -315,11 +299,11 @@ __global__ __launch_bounds__(256) void act_bwd_kernel(const bf16_t* __restrict__
   const int64_t r = i / F;
   const int f = static_cast<int>(i - r * F);
   float g[8], a[8];
-  load8<bf16_t>(dF + i, g);
+  load8(dF + i, g);
   if (swiglu) {
     float u0[8], u1[8], o0[8], o1[8];
-    load8<bf16_t>(u + r * 2 * F + 2 * f, u0);       // gate, up of outputs f .. f+3
-    load8<bf16_t>(u + r * 2 * F + 2 * f + 8, u1);   // ... of f+4 .. f+7
+    load8(u + r * 2 * F + 2 * f, u0);       // gate, up of outputs f .. f+3
+    load8(u + r * 2 * F + 2 * f + 8, u1);   // ... of f+4 .. f+7
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float z0 = u0[2 * e], up0 = u0[2 * e + 1], e0 = 1.0f + expf(-z0), s0 = 1.0f / e0;
@@ -331,11 +315,11 @@ __global__ __launch_bounds__(256) void act_bwd_kernel(const bf16_t* __restrict__
       a[e] = z0 / e0 * up0;
       a[4 + e] = z1 / e1 * up1;
     }
-    store8<bf16_t>(du + r * 2 * F + 2 * f, o0);
-    store8<bf16_t>(du + r * 2 * F + 2 * f + 8, o1);
+    store8(du + r * 2 * F + 2 * f, o0);
+    store8(du + r * 2 * F + 2 * f + 8, o1);
   } else {
     float z[8], o[8];
-    load8<bf16_t>(u + i, z);
+    load8(u + i, z);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float cdf = 0.5f * (1.0f + erff(z[e] * 0.70710678118654752f));
@@ -343,9 +327,9 @@ __global__ __launch_bounds__(256) void act_bwd_kernel(const bf16_t* __restrict__
       o[e] = g[e] * (cdf + z[e] * pdf);
       a[e] = z[e] * cdf;
     }
-    store8<bf16_t>(du + i, o);
+    store8(du + i, o);
   }
-  store8<bf16_t>(fo + i, a);
+  store8(fo + i, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -400,8 +384,8 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const bf16_t* __restrict__ 
   float s = 0.f;
   if (live) {
     float va[8], vb[8];
-    load8<bf16_t>(dO + static_cast<int64_t>(r) * ld + c8 * 8, va);
-    load8<bf16_t>(O + static_cast<int64_t>(r) * ld + c8 * 8, vb);
+    load8(dO + static_cast<int64_t>(r) * ld + c8 * 8, va);
+    load8(O + static_cast<int64_t>(r) * ld + c8 * 8, vb);
 #pragma unroll
     for (int e = 0; e < 8; ++e) s = fmaf(va[e], vb[e], s);
   }
@@ -416,8 +400,7 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const bf16_t* __restrict__ 
 
 // inverse rotary rotation of the gradient, in place, on the first `cols`
 // columns (whole heads) of rows of a [rows, ld] array
-template <typename T>
-__global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, int64_t ld, int rows,
+__global__ __launch_bounds__(256) void rope_bwd_kernel(bf16_t* __restrict__ g, int64_t ld, int rows,
                                                        int cols, int hd,
                                                        const int32_t* __restrict__ pos,
                                                        EpiParams ep) {
@@ -432,8 +415,8 @@ __global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, int64_
   float sn, cs;
   rope_angle(pos[r], ep.inv_freq[k], &sn, &cs);
   const float x = to_f32(g[a]), y = to_f32(g[a + half]);
-  g[a] = from_f32<T>(x * cs + y * sn);
-  g[a + half] = from_f32<T>(y * cs - x * sn);
+  g[a] = f32_to_bf16(x * cs + y * sn);
+  g[a + half] = f32_to_bf16(y * cs - x * sn);
 }
 
 // ---------------------------------------------------------------------------
@@ -815,12 +798,9 @@ hipError_t launch_rope_bwd(hipStream_t s, int dtype, void* g, int64_t ld, int ro
                            int hd, const int32_t* pos, const EpiParams& ep) {
   const int64_t total = static_cast<int64_t>(rows) * (cols / 2);
   if (total == 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((total + 255) / 256));
-  if (dtype == 1)
-    return launch(K_MISC, rope_bwd_kernel<bf16_t>, grid, dim3(256), 0, s, static_cast<bf16_t*>(g),
-                  ld, rows, cols, hd, pos, ep);
-  return launch(K_MISC, rope_bwd_kernel<float>, grid, dim3(256), 0, s, static_cast<float*>(g), ld,
-                rows, cols, hd, pos, ep);
+  if (dtype != 1) return hipErrorInvalidValue;
+  return launch(K_MISC, rope_bwd_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s,
+                static_cast<bf16_t*>(g), ld, rows, cols, hd, pos, ep);
 }
 
 hipError_t launch_attention_bwd(hipStream_t s, const void* q, const void* k, const void* v,

@@ -232,7 +232,7 @@ template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_mfma_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, int M, int N, int K,
     EpiParams ep) {
-  static_assert(BM % 64 == 0 && (BN == 64 || BN == 128 || BN == 256), "tile shape");
+  static_assert(BM % 128 == 0 && (BN == 128 || BN == 256), "tile shape");
   constexpr int NT = WM * WN * 64;
   constexpr int kTileLd = BN + 4;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -2732,16 +2732,15 @@ bool skinny_ok(int dtype, int M, int N, int K, const EpiParams& ep) {
 //   1024 x 768 x 3072              /  20.2     22.8
 // so it takes M <= 16, and up to 1024 rows while the 128 x 128 output
 // tiles are fewer than 64 (past 512 rows: 768-column outputs). Where
-// short_grid can give the product 64-wide tiles (wide_tiles_only below), it
-// leaves it those from 150 of them on: few-row /
-// 64 x 64, us, 640 x 768 x 3072 (120 tiles) 15.0 / 16.6, 160 x 3072 x 768
+// short_grid can give the product 64-wide tiles (not no_narrow_tiles), those
+// have it from 150 of them on: few-row / 64 x 64, us, 640 x 768 x 3072 (120 tiles) 15.0 / 16.6, 160 x 3072 x 768
 // with GELU (144) 7.1 / 7.5, 800 x 768 x 3072 (156) 19.7 / 16.3, 800 x 768 x
 // 768 9.7 / 7.4, 300 x 2304 x 768 (180) 9.1 / 7.1. Without such tiles the
 // few-row kernel stays ahead of what is left: rotary heads of 128, 100 x 6144
 // x 4096 28.8 against 41.5 on 128 x 128 tiles, 256 x 3072 x 1024 14.6 against
 // 19.3; K not a multiple of 64, 800 x 768 x 3104 20.1 against 69.0 on the
 // fp32 matrix instructions, 300 x 2304 x 800 8.6 against 22.3.
-bool wide_tiles_only(int K, const EpiParams& ep) {
+bool no_narrow_tiles(int K, const EpiParams& ep) {
   // whole K slices; a rotary head must lie within a tile's columns
   return K % kBK != 0 || (ep.epi == EPI_ROPE && ep.head_dim > 64);
 }
@@ -2749,7 +2748,7 @@ bool wide_tiles_only(int K, const EpiParams& ep) {
 bool skinny_pays(int M, int N, int K, const EpiParams& ep) {
   const long tiles128 = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
   const long tiles64 = static_cast<long>((M + 63) / 64) * ((N + 63) / 64);
-  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64 && (tiles64 < 150 || wide_tiles_only(K, ep)));
+  return M <= kSkMaxM || (M <= 1024 && tiles128 < 64 && (tiles64 < 150 || no_narrow_tiles(K, ep)));
 }
 
 // Tile shape of a product whose 128 x 128 tiles are at most one per CU (none
@@ -2786,7 +2785,7 @@ ShortGrid short_grid(int M, int N, int K, const EpiParams& ep, bool split) {
   if (K % kBK != 0) return kNoShort;
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const long cus = device_cus(), t64 = tiles(64, 64);
-  const bool narrow = !wide_tiles_only(K, ep);
+  const bool narrow = !no_narrow_tiles(K, ep);
   if (tiles(128, 128) > cus || (split && (K > 4096 || !narrow))) return kNoShort;
   if (narrow && t64 <= 2 * cus)
     return K >= 2048 && t64 > cus && tiles(128, 64) <= cus ? kShort128x64 : kShort64;
