@@ -88,3 +88,24 @@ def test_attention_moving_reference(hd, causal):
         a[:, 0] = np.where(np.arange(n) % 3 == 0, 8.0 * math.sqrt(hd) / 8.0, 0.1)
         return a
     check([700], 2, 2, hd, causal, seed=11 + hd, sharp=1.0, shape_scores=rise)
+
+
+def test_attention_many_equal_sequences():
+    """More equal sequences of two rows, unmasked, than a grid's z holds at one
+    chunk of heads each (12 heads: 43,690): the bounds of check()."""
+    n, H, hd = 44000, 12, 64
+    g = torch.Generator(device=dev()).manual_seed(3)
+    q, k, v = torch.randn((2 * n, 3 * H * hd), generator=g, device=dev()).to(torch.bfloat16).split(H * hd, dim=1)
+    out, lse, scores = zsa.attention_with_scores(q, k, v, H, zsa.Seqs([2] * n, dev()), False)
+    q64, k64, v64 = (t.to(torch.float64).reshape(n, 2, H, hd) for t in (q, k, v))
+    s = torch.stack([(q64 * k64[:, j:j + 1]).sum(dim=3) for j in (0, 1)], dim=3) / math.sqrt(hd)  # [n, 2, H, key]
+    l = torch.logsumexp(s, dim=3)
+    p = torch.exp(s - l[..., None])
+    o = sum(p[..., j:j + 1] * v64[:, j:j + 1] for j in (0, 1))
+    av = sum(p[..., j:j + 1] * v64[:, j:j + 1].abs() for j in (0, 1))
+    off = (out.to(torch.float64).reshape(n, 2, H, hd) - o).abs() / (2.0 ** -8 * (av + o.abs()))
+    assert off.max().item() <= 1.01
+    l = l.reshape(2 * n, H).t()
+    assert ((lse.to(torch.float64) - l).abs() / l.abs().clamp(min=1.0)).max().item() <= 1e-5
+    sc = p.sum(dim=(1, 2)).reshape(-1)
+    assert ((scores.to(torch.float64) - sc).abs() / sc.clamp(min=1.0)).max().item() <= 1e-4
