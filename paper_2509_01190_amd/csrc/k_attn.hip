@@ -13,8 +13,9 @@
 //  * attn_wide_kernel (longer sequences): 32-key steps, each step's
 //    exponentials interleaved with the products of its neighbours, K/V tiles
 //    loaded straight into LDS;
-//  * attn_mfma_kernel (shorter ones): one workgroup of NW waves per 32
-//    NW-query block, 64-key tiles staged through registers.
+//  * attn_mfma_kernel (shorter ones, and grids of few workgroups:
+//    attention_wide): one workgroup of NW waves per 32 NW-query block, 64-key
+//    tiles staged through registers.
 //
 // fp32 (and bf16 at any other head_dim): the same transposed scores on the
 // fp32 matrix instruction, four waves sharing 32 queries' keys.
@@ -33,14 +34,17 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// Shorter sequences: four waves per SIMD at head dim 64 (128 registers), two
+// Shorter sequences (up to 256 rows at head dim 64, 384 at 128) and, up to
+// 512 rows at 128 and under the mask of any length at 64, grids of few
+// workgroups. Four waves per SIMD at head dim 64 (128 registers), two
 // at 128, walking 64-key tiles staged in LDS (K row-major; V transposed at
 // head dim 64, row-major at 128 and read through transposing LDS reads). A
 // workgroup reads every K and V row of its sequence and head once, so the bytes moved
 // per query fall as the query block grows: the loads, not the MFMAs or the
-// exponentials, bound the kernel at these lengths (a copy without any of
-// the compute takes 35 of the 48.5 us of 32 sequences x 12 heads x 512 rows
-// with 4 waves). 8 waves (256 queries, two workgroups per CU) halve them.
+// exponentials, bound the kernel where the chip is full (32 sequences x 12
+// heads x 512 rows, which the long-sequence kernel has now: a copy without
+// any of the compute took 35 of 48.5 us with 4 waves). 8 waves (256 queries,
+// two workgroups per CU; head dim 64 past 128 rows) halve them: 45.9.
 template <int HD, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 4 : 2))) void attn_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -55,25 +59,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HD == 6
   // the transposing writes of a wave (rows 8j + e of 8 channel blocks j, 8
   // key pairs) then cover all 64 banks once, where rows j and j + 4
   // otherwise met in one bank (2-way), while the 32 rows of a fragment read
-  // share one XOR and stay conflict-free (head_dim 64: 292.8 against
-  // 296.1 us on 8 x 2048 causal rows, 32 heads). Head dim 128 keeps the
-  // plain layout: the swizzle there measured 2 % slower.
+  // share one XOR and stay conflict-free (1 % at head dim 64 over 2048 rows).
   constexpr int VLD = BKEY + 4;
   constexpr int VSW = HD == 64 ? 4 : 0;
   // Head dim 128 stores V as it comes (key rows, the K tile's row stride)
   // and reads the V^T fragments with gfx950's transposing LDS reads
-  // (ds_read_b64_tr_b16): 4 x 4096 causal rows, 32 heads, 986 -> 929 us.
-  // At head dim 64 the same reads took 296 -> 296 us on 8 x 2048 causal
-  // rows and 40.6 -> 42.2 us on 32 x 512, so it keeps the transposed tile.
+  // (ds_read_b64_tr_b16): 6 % over 4096 rows. At head dim 64 the same reads
+  // gained nothing over 2048 rows and lost 4 % over 512 (40.6 -> 42.2 us on
+  // 32 x 512, 12 heads), so it keeps the transposed tile.
   constexpr bool VTR = HD == 128;
   constexpr int OLD = HD + 8;    // output staging row stride
   constexpr int KBYTES = BKEY * KLD * 2, VBYTES = VTR ? KBYTES : HD * VLD * 2;
   constexpr int BUF = KBYTES + VBYTES;
-  // K/V tile buffers: eight-wave blocks keep four (tiles stored two ahead,
-  // a barrier after every second tile: 297.0 -> 292.2 us on 8 x 2048 causal
-  // rows, 83.7 -> 80.8 on 8 x 1024, 11.2 -> 10.2 on 8 x 256, head dim 128
-  // on 4 x 4096 rows 1017 -> 994); four-wave blocks two (one ahead, a
-  // barrier per tile), which keeps four of them on a CU
+  // K/V tile buffers: eight-wave blocks (head dim 64) keep four (tiles stored
+  // two ahead, a barrier after every second tile: 11.2 -> 10.2 us on 8 x 256
+  // causal rows, 32 heads); four-wave blocks two (one ahead, a barrier per
+  // tile), which keeps four of them on a CU
   constexpr int NB = NW == 8 ? 4 : 2, LA = NB / 2;
   constexpr int SBYTES = NB * BUF > NW * 32 * OLD * 2 ? NB * BUF : NW * 32 * OLD * 2;
   constexpr int KITEMS = BKEY * HD / 8;        // 16-byte K chunks per tile

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void transpose64_kernel(const TransposeArgs p)
 }
 
 // ---------------------------------------------------------------------------
-// norm backward: one wave per row.
+// norm backward: one wave per row, four past 2048 columns (WPR).
 //   LN:  dx = rstd (g dh - mean(g dh) - xhat mean(g dh xhat))
 //   RMS: dx = rstd (g dh - xhat mean(g dh xhat))
 // out = res + dx (res may alias out, or be NULL). The gain and shift

@@ -2669,20 +2669,17 @@ int gemm_tile_override() {
 
 }  // namespace
 
-// (Up to K = 4096 launch_gemm takes short_grid's tiles instead.)
 // Split K when the 128 x 128 output tiles fill under 0.7 of the CUs once
 // and K is long (at least kMinSplitK): S slices of at least
 // kMinSplitSteps K steps, S x tiles <= 512 workgroups (one round, no tail).
-// Every slice is non-empty and all but the last have kchunk columns. Per
-// projection (both launches), M x 768 x 3072 with a residual: 256 rows 26.6
-// -> 15.9 us, 2048 rows 31.7 -> 27.1, 3584 rows (168 tiles) 34.0 -> 32.5,
-// 3904 rows (186 tiles) 34.9 -> 39.6 (not split), 4096 rows (192 tiles)
-// 32.1 -> 35.5 (not split); 1024 x 2048 x 8192 71.5
-// (persistent 128 x 128) -> 53.4. Up to K = 2048 launch_gemm leaves the
-// products the persistent 128x128 kernel takes unsplit (1024 x 2048 x 2048
-// with a residual: split 27.7 against 22.8 us on that kernel), but the
-// rotary products of the same grids, which it does not take, need the
-// split (the 1B-shaped decoder at keep rate 0.1 9.66 -> 9.73 ms without).
+// Every slice is non-empty and all but the last have kchunk columns.
+// launch_gemm splits what short_grid leaves of these products: K past 4096
+// (1024 x 2048 x 8192 71.5 us on persistent 128 x 128 tiles, 53.4 split),
+// rotary heads of 128 (its comment), and below K = 2048 grids of more than
+// two 64 x 64 tiles per CU that the persistent 128 x 128 kernel does not take
+// (it beats the split up to K = 2048: 1024 x 2048 x 2048 with a residual 22.8
+// against 27.7). The size queries do not know the epilogue, so they count the
+// partial products of every plan.
 void splitk_plan(int M, int N, int K, int* S, int* kchunk) {
   *S = 1;
   *kchunk = K;
@@ -2767,6 +2764,7 @@ bool skinny_pays(int M, int N, int K, const EpiParams& ep) {
 //   1030 x 768 x 3072        24.9 / 17.5 / 21.2 / 31.8   (204)
 //   2048 x 768 x 3072        29.1 / 23.1 / 22.3 / 32.0   (384)
 //   3500 x 768 x 3072        36.4 / 33.6 / 34.0 / 33.4   (660)
+//   4096 x 768 x 3072        33.5 /             / 31.0   (768; the other two not taken)
 //   4500 x 768 x 3072        36.8 / 42.9 / 35.9 / 34.3   (852)
 //   500 x 2048 x 2048        21.9 / 12.1 / 15.0 / 21.5   (256)
 //   600 x 3072 x 2048        22.2 / 16.2 / 15.4 / 21.9   (480)
@@ -2929,7 +2927,7 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* x, int M, int K, co
       }
     }
     // (K <= 2048: the persistent 128x128 kernel beats the split where it
-    // takes the epilogue; see splitk_plan)
+    // takes the product; see splitk_plan)
     if (S > 1 && ws != nullptr && ws_bytes >= splitk_bytes(S, M, N) &&
         !(K <= 2048 && persist_ok(M, N, K, ep))) {
       float* part = static_cast<float*>(ws);
@@ -2970,15 +2968,15 @@ hipError_t launch_gemm(hipStream_t s, int dtype, const void* x, int M, int K, co
     // 2304, 3072; K = 768, 3072; M = 2048 .. 16384): the persistent
     // four-wave kernel where w4p_width finds a tile width that pays, the
     // persistent 128x128 kernel otherwise. For longer K (the decoders, K =
-    // 4096 .. 14336): the persistent four-wave kernel from one round of its
-    // tiles on (8192 x 4096 x 14336: 754 against 994 us for the 8-wave
-    // kernel below; 4096 x 6144 x 4096: 173 against 210 us), else -- and for
+    // 4096 .. 14336): the persistent four-wave kernel from 0.68 of a round of
+    // its tiles on (8192 x 4096 x 14336: 754 against 994 us for the 8-wave
+    // kernel below; 4096 x 6144 x 4096: 173 against 210 us; 3276 x 4096 x
+    // 14336, 0.81 of a round: 320 against 430), else -- and for
     // the rotary and SwiGLU epilogues -- direct-to-LDS 256x256 tiles over 8
     // waves (128x64 per wave) once the grid holds at least four rounds of
     // them, else the persistent 128x128 kernel (1632 x 2048 x 8192: 74.5
     // against 81.3 us direct-to-LDS 128x128; 1472 x 4096 x 4096 61.8 against
-    // 65.7; 3276 x 4096 x 14336 432 against 430), or direct-to-LDS 128x128
-    // tiles for the epilogues it lacks.
+    // 65.7), or direct-to-LDS 128x128 tiles for the epilogues it lacks.
     const int bn = w4p_width(M, N, K, ep);
     if (bn == 256) return launch_w4p<256>(s, x, M, K, w, N, ep);
     if (bn == 192) return launch_w4p<192>(s, x, M, K, w, N, ep);

@@ -39,7 +39,7 @@ struct WgradArgs {
   const bf16_t *a, *b;   // dY [rows, m], X [rows, n]
   int rows, m, n;
   int tm, tn, splits;    // tiles of m and n, row splits
-  int chunk;             // rows per split, a multiple of the slice
+  int chunk;             // rows per split, a multiple of 64 (the last slice may be part-filled)
   float* out;            // splits == 1: [m, n]; else [splits][m, n]
   float* bias;           // [splits * wave columns * min(tn, kBiasTiles)][m], or null
 };
