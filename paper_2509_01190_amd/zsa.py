@@ -433,8 +433,10 @@ class Stack:
             seqs.batch, _hp32(seqs.host), _p(seqs.dev), kr_p, _p(x_out), _p(pos_out),
             _hp32(cu_out), _p(cu_out_dev), _p(scores), _p(kept), _p(ws), wsz))
         # the offsets go on to the next block: what the caller does to cu_dev must not
-        # reach them (the sum takes 1.5 us on the stream, clone()'s copy 5)
-        out_seqs = Seqs._of(cu_out, cu_out_dev + 0)
+        # reach them. A block that keeps every row leaves the ones it was called with;
+        # others get a tensor of their own (2 us on the stream, clone()'s copy 5).
+        same = keep_rate is None or self.cfg.mark_only
+        out_seqs = Seqs._of(cu_out, seqs.dev if same else cu_out_dev + 0)
         res = {"x": x_out[:t_out], "pos": pos_out[:t_out], "seqs": out_seqs,
                "cu_dev": cu_out_dev}
         if want_scores:
