@@ -10,7 +10,7 @@
 // rows, so the column sum is in-lane adds. One partial vector per head
 // ([H][T]); the top-k kernel adds the H partials in a fixed order. No
 // atomics: the result is bitwise reproducible. score_wide_kernel: a wave
-// owns 64 keys and goes over all queries; score_mfma_kernel (few
+// owns 64 keys and goes over all queries; score_mfma_kernel (grids of few
 // workgroups): a workgroup's eight waves share 128 keys and stride over the
 // queries. Under the causal mask both start at the first query that can see
 // their keys.
@@ -187,14 +187,14 @@ __global__ __launch_bounds__(64 * kScoreWaves) __attribute__((amdgpu_waves_per_e
   }
 }
 
-// Longer sequences. A wave owns 64 keys, their operand in registers, and goes
+// Grids of enough workgroups (launch_score). A wave owns 64 keys, their operand in registers, and goes
 // over the queries in steps of 32: in step u it issues the products
 // S(u + 1) = Q K^T one at a time with the exponentials and sums of step u
 // between them (scheduling barriers fix the order), three waves per SIMD (two
 // at head dim 128, where a third spills) so that each fills the others' gaps. Query tiles of 64 rows and their
 // log-sum-exp go straight to LDS two tiles ahead, shared by the four waves
 // (256 keys), as K and V do in the attention kernel. A key's sum is one
-// wave's, in query order: no reduction over waves. The earlier kernel below
+// wave's, in query order: no reduction over waves. The earlier kernel above
 // split a block's queries over eight waves that each staged its own tiles
 // through registers.
 // Same box, us with the sum over heads, earlier kernel / this one: 8 x 2048
@@ -483,7 +483,13 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
     const bf16_t* kp = static_cast<const bf16_t*>(k);
     const float sl = scale * kLog2e;
     // the wide kernel from two of its workgroups per CU on (its comment), one
-    // at head dim 128 (4 x 500 causal rows, 32 heads: 32.1 -> 26.0 us)
+    // at head dim 128 (4 x 500 causal rows, 32 heads: 32.1 -> 26.0 us), at any
+    // length: short sequences leave some of its waves without keys and are
+    // still faster on it (us with the sum over heads, the other kernel / this
+    // one: 32 heads of 64, no mask, 128 x 20 rows 34.5 / 25.1, 64 x 64 17.8 /
+    // 14.6, 64 x 128 21.7 / 20.9, 64 x 256 46.6 / 35.6; causal 64 x 64 19.2 /
+    // 13.2, 64 x 256 47.1 / 45.7, at worst 64 x 128 23.6 / 25.2; 32 heads of 128
+    // on 8, 64 x 64 34.0 / 22.1, 64 x 128 causal 46.7 / 37.9)
     const long wide = static_cast<long>((max_len + 255) / 256) * H * B;
     const bool take = wide >= (hd == 64 ? 2 : 1) * device_cu_count();
     const dim3 grid = place_grid(H, B, max_len, T, causal, take ? 256 : 128);
