@@ -163,12 +163,12 @@ def summarize_pmc(args):
 
 # kernel classes by kernel-name fragment (the timing hook's classes)
 KERNEL_CLASS_TAGS = (
-    ("gemm", ("gemm_bf16_", "gemm_skinny_", "gemm_valu", "splitk_reduce")),
-    ("attention", ("attn_mfma", "attn_valu")),
-    ("score", ("score_mfma", "score_valu")),
+    ("gemm", ("gemm_bf16_", "gemm_skinny_", "gemm_f32_", "splitk_reduce")),
+    ("attention", ("attn_wide", "attn_mfma", "attn_f32")),
+    ("score", ("score_wide", "score_mfma", "score_f32")),
     ("select", ("select_kernel",)),
     ("gather", ("gather_rows", "gather_pos")),
-    ("norm", ("norm_kernel",)),
+    ("norm", ("norm_kernel", "norm_few")),
 )
 
 

@@ -49,3 +49,21 @@ def test_inline_asm_writes_no_unnamed_m0():
                 seen += 1
                 assert '"{m0}"' in text, f"{name}: {template}"
     assert seen >= 2
+
+
+def test_bench_knows_every_forward_kernel():
+    """The profile summaries put each kernel of a forward into its class: a
+    kernel they do not know counts as "misc" and its class's figures are
+    wrong."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2509_01190_amd", "csrc")
+    classes = {"k_attn.hip": "attention", "k_score.hip": "score", "k_norm.hip": "norm", "k_gemm.hip": "gemm"}
+    seen = 0
+    for name, cls in classes.items():
+        text = open(os.path.join(csrc, name)).read()
+        for kernel in set(re.findall(r"\b([a-z0-9_]+_kernel)\(\s*\n?\s*const [A-Za-z0-9_]+\* __restrict__", text)):
+            if kernel == "rope_table_kernel":  # positions, not a product
+                continue
+            seen += 1
+            assert bench.kernel_class(f"void zsa::(anonymous namespace)::{kernel}<64, 2>(int)") == cls, kernel
+    assert seen >= 12
