@@ -95,6 +95,14 @@ void products() {
       {640, 768, 3072, EPI_RESIDUAL, 0, true, kShort64, kShort64},
       {800, 768, 3072, EPI_RESIDUAL, 0, false, kShort64, kShort64},
       {300, 2304, 768, EPI_ROPE, 64, false, kShort64, kShort64},
+      {300, 1856, 1024, EPI_NONE, 0, true, kShort64, kShort64},
+      {1000, 576, 768, EPI_GELU, 0, true, kShort64, kShort64},
+      // past two 64 x 64 tiles per CU, and past one 128 x 128
+      {4000, 768, 3072, EPI_RESIDUAL, 0, false, kShort128, kShort128},
+      {6001, 768, 3072, EPI_NONE, 0, false, kNoShort, kNoShort},
+      {1100, 384, 4608, EPI_NONE, 0, false, kNoShort, kShort64},
+      {2100, 768, 4160, EPI_NONE, 0, false, kNoShort, kShort128x64},
+      {2500, 2048, 8192, EPI_NONE, 0, false, kNoShort, kNoShort},
       // K no multiple of 64: no tiled bf16 kernel takes it
       {640, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},
       {800, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},

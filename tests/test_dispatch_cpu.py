@@ -16,7 +16,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 DRIVER = os.path.join(ROOT, "tests", "host", "dispatch_driver.cpp")
 
 
-@pytest.mark.skipif(not os.path.exists(_build.HIPCC), reason="ROCm compilers not installed")
+@pytest.mark.skipif(not os.path.exists(_build.HIPCC) or not os.path.exists(DRIVER),
+                    reason="ROCm compilers or the driver's source not there")
 def test_placement_and_dispatch_rules():
     tmp = tempfile.mkdtemp(prefix="zsa_dispatch_")
     try:

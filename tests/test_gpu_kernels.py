@@ -168,7 +168,8 @@ def test_linear_zero_rows(epi, split):
     assert tuple(y.shape) == (0, n // 2 if epi == zsa.EPI_SWIGLU else n)
 
 
-@pytest.mark.parametrize("m,n,k", [(1100, 384, 3072), (1500, 768, 8192), (2100, 768, 3072)])
+@pytest.mark.parametrize("m,n,k", [(1100, 384, 3072), (1500, 768, 8192), (2100, 768, 3072),  # (3072: short-grid tiles)
+                                   (1100, 384, 4608), (2100, 768, 4160)])
 @pytest.mark.parametrize("epi", [zsa.EPI_NONE, zsa.EPI_GELU, zsa.EPI_SWIGLU, zsa.EPI_RESIDUAL,
                                  zsa.EPI_ROPE])
 def test_linear_split_k(m, n, k, epi):
@@ -222,7 +223,11 @@ def test_linear_split_k(m, n, k, epi):
                                    (300, 2304, 1024),   # ragged rows, two column blocks
                                    (500, 1000, 2048),   # odd column blocks: the last pair half past N
                                    (512, 768, 3072),    # two column blocks, double-buffered
-                                   (1000, 768, 768)])   # ragged, near the last row count
+                                   (1000, 768, 768),    # ragged, near the last row count
+                                   # the few-row kernel's largest: under 150 tiles of 64 x 64
+                                   (256, 2304, 768),
+                                   (300, 1856, 1024),   # ragged rows, two column blocks
+                                   (1000, 576, 768)])   # ragged, near the last row count
 @pytest.mark.parametrize("epi", [zsa.EPI_NONE, zsa.EPI_GELU, zsa.EPI_SWIGLU, zsa.EPI_RESIDUAL])
 @pytest.mark.parametrize("split", [True, False])
 def test_linear_short_products(m, n, k, epi, split):
@@ -260,10 +265,13 @@ def test_linear_short_products(m, n, k, epi, split):
                                          (4001, 2304, 768, False),    # persistent 256x192: 0.75 round
                                          (4097, 4096, 4096, False),   # persistent 256x256: K > 3072
                                          (12289, 3072, 768, False),   # persistent 128x128
-                                         (1000, 768, 768, False),
-                                         (4000, 768, 3072, False),
-                                         (16385, 2304, 768, False),
-                                         (1500, 2048, 8192, False),   # persistent 128x128, long K
+                                         (6001, 768, 768, False),
+                                         (6001, 768, 3072, False),
+                                         (1000, 768, 768, False),     # short grids: 64x64
+                                         (4000, 768, 3072, False),    # 128x128
+                                         (16385, 2304, 768, False),   # persistent 128x128 (some epilogues)
+                                         (2500, 2048, 8192, False),   # persistent 128x128, long K
+                                         (1500, 2048, 8192, False),   # short grids: 128x128
                                          (1000, 2048, 8192, True)])   # split K over 4 slices
 @pytest.mark.parametrize("epi", [zsa.EPI_NONE, zsa.EPI_GELU, zsa.EPI_RESIDUAL, zsa.EPI_SWIGLU])
 @pytest.mark.parametrize("with_bias", [True, False])
