@@ -2675,7 +2675,7 @@ int gemm_tile_override() {
 // Every slice is non-empty and all but the last have kchunk columns.
 // launch_gemm splits what short_grid leaves of these products: K past 4096
 // (1024 x 2048 x 8192 71.5 us on persistent 128 x 128 tiles, 53.4 split),
-// rotary heads of 128 (its comment), and below K = 2048 grids of more than
+// rotary heads of 128 and grids of few tiles (its comment), and below K = 2048 grids of more than
 // two 64 x 64 tiles per CU that the persistent 128 x 128 kernel does not take
 // (it beats the split up to K = 2048: 1024 x 2048 x 2048 with a residual 22.8
 // against 27.7). The size queries do not know the epilogue, so they count the
@@ -2779,15 +2779,21 @@ bool skinny_pays(int M, int N, int K, const EpiParams& ep) {
 // heads of 128 (split / 128 x 128 on 8 waves: 128 x 12288 x 4096, 96 tiles,
 // 33.2 / 42.8; 300 x 6144 x 4096, 144 tiles, 38.1 / 43.5; one tile per CU or
 // nearly: 512 x 6144 x 4096, 192 tiles, 128 x 128 on 4 waves 56.1 / 47.2).
+// So do products of few columns, whose tiles are too few for their K (split /
+// these tiles: 1030 x 64 x 3072, 17 tiles of 64 x 64, 9.6 / 12.7; 3000 x 64 x
+// 3072, 47 tiles, 16.6 / 13.0; 1616 x 128 x 4096, 52 tiles, 16.4 / 18.1; 3000 x
+// 128 x 4096, 94 tiles, 19.2 / 19.0), and at K = 4096 grids of 128 x 128 tiles
+// on under 0.6 of the CUs (2100 x 1024 x 4096, 136 tiles, 35.2 / 37.2; 6000 x
+// 512 x 4096, 188 tiles, 43.9 / 39.4).
 ShortGrid short_grid(int M, int N, int K, const EpiParams& ep, bool split) {
   if (K % kBK != 0) return kNoShort;
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const long cus = device_cus(), t64 = tiles(64, 64);
+  const long cus = device_cus(), t64 = tiles(64, 64), t128 = tiles(128, 128), steps = K / kBK;
   const bool narrow = !no_narrow_tiles(K, ep);
-  if (tiles(128, 128) > cus || (split && (K > 4096 || !narrow))) return kNoShort;
+  if (t128 > cus || (split && (K > 4096 || !narrow || 64 * t64 <= steps * steps))) return kNoShort;
   if (narrow && t64 <= 2 * cus)
     return K >= 2048 && t64 > cus && tiles(128, 64) <= cus ? kShort128x64 : kShort64;
-  return K >= 2048 ? kShort128 : kNoShort;
+  return K >= 2048 && !(split && K >= 4096 && 5 * t128 < 3 * cus) ? kShort128 : kNoShort;
 }
 
 // The folded pre-norm: every workgroup normalises the x fragments it

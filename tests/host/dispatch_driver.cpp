@@ -103,6 +103,14 @@ void products() {
       {1100, 384, 4608, EPI_NONE, 0, false, kNoShort, kShort64},
       {2100, 768, 4160, EPI_NONE, 0, false, kNoShort, kShort128x64},
       {2500, 2048, 8192, EPI_NONE, 0, false, kNoShort, kNoShort},
+      // few columns and a long K: either side of (K / 64)^2 / 64 tiles of 64 x 64
+      {1616, 64, 3520, EPI_RESIDUAL, 0, false, kNoShort, kShort64},
+      {1616, 128, 3072, EPI_NONE, 0, false, kShort64, kShort64},
+      {4096, 64, 4096, EPI_NONE, 0, false, kNoShort, kShort64},
+      {2100, 128, 4096, EPI_NONE, 0, false, kShort64, kShort64},
+      // K = 4096: either side of 0.6 of a 128 x 128 tile per CU
+      {2100, 1024, 4096, EPI_NONE, 0, false, kNoShort, kShort128},
+      {4096, 640, 4096, EPI_NONE, 0, false, kShort128, kShort128},
       // K no multiple of 64: no tiled bf16 kernel takes it
       {640, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},
       {800, 768, 3104, EPI_NONE, 0, true, kNoShort, kNoShort},
