@@ -2630,7 +2630,9 @@ hipError_t launch_dma(hipStream_t s, const void* x, int M, int K, const void* w,
 // 32 split-K kernel where the 64 x 64
 // tiles would leave CUs without one and a rotary head lies within its 32
 // columns; 128 x 128 tiles (half the operand bytes per FLOP) from two of
-// them per CU on, and where a rotary head is wider than 64.
+// them per CU on; where a rotary head is wider than 64, 64 x 128 ones below
+// that (244 x 4224 x 96 bf16, rotary heads of 128, 66 of the larger: 28.3 -> 16.7 us;
+// the vector-ALU kernel 24.9).
 template <typename T>
 hipError_t launch_f32(hipStream_t s, const void* x, int M, int K, const void* w, int N,
                       const EpiParams& ep) {
@@ -2643,9 +2645,12 @@ hipError_t launch_f32(hipStream_t s, const void* x, int M, int K, const void* w,
     return launch(K_GEMM, gemm_f32_direct_kernel<T>, dim3((M + 31) / 32, (N + 31) / 32), dim3(512),
                   0, s, xp, wp, M, N, K, kchunk, ep);
   }
-  if (head > 64 || tiles(128) >= 2 * device_cus())
+  if (tiles(128) >= 2 * device_cus())
     return launch(K_GEMM, gemm_f32_tile_kernel<T, 2, 2>, dim3((M + 127) / 128, (N + 127) / 128),
                   dim3(256), 0, s, xp, wp, M, N, K, ep);
+  if (head > 64)
+    return launch(K_GEMM, gemm_f32_tile_kernel<T, 1, 2>, dim3((M + 63) / 64, (N + 127) / 128), dim3(256),
+                  0, s, xp, wp, M, N, K, ep);
   return launch(K_GEMM, gemm_f32_tile_kernel<T, 1, 1>, dim3((M + 63) / 64, (N + 63) / 64), dim3(256),
                 0, s, xp, wp, M, N, K, ep);
 }

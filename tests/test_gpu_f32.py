@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
                                       (1030, 1040, 68, 16),     # 64 x 64 tiles, K not a whole slice
                                       (700, 768, 96, 64),       # rotary heads of 64: 64 x 64 tiles
                                       (2100, 4112, 36, 16),     # 128 x 128 tiles, ragged
-                                      (130, 256, 40, 128)])     # rotary heads of 128: 128 x 128 tiles
+                                      (130, 256, 40, 128),      # rotary heads of 128: 64 x 128 tiles
+                                      (4200, 2176, 36, 128)])   # ... 128 x 128 tiles
 @pytest.mark.parametrize("epi", [zsa.EPI_NONE, zsa.EPI_GELU, zsa.EPI_SWIGLU, zsa.EPI_RESIDUAL, zsa.EPI_ROPE])
 def test_linear_f32_tiles(m, n, k, hd, epi):
     g = np.random.default_rng(m + n + k + epi)
