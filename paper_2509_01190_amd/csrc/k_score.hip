@@ -472,6 +472,26 @@ int score_groups(int dtype, int H, int hd, int T) {
   return H;
 }
 
+// The wide kernel from two of its workgroups per CU on (its comment), one at
+// head dim 128 (4 x 500 causal rows, 32 heads: 32.1 -> 26.0 us). Past 1024 rows,
+// where a workgroup takes long, those that hold keys count, of which a ragged
+// batch's grid has fewer: about half a block a sequence more than its rows
+// fill (3 sequences of up to 2344 causal rows, 20 heads of 64, 600
+// workgroups in the grid, about 380 live: the other kernel 44.3, this one 48.7
+// us; 8 of up to 2553, 4 heads of 128, 320 and 212: 42.7 and 58.0; but 8 of up to
+// 500, 16 heads of 128, 256 and 208: 17.6 and 15.7). At any length: short sequences leave some of
+// its waves without keys and are still faster on it (us with the sum over
+// heads, the other kernel / this one: 32 heads of 64, no mask, 128 x 20 rows
+// 34.5 / 25.1, 64 x 64 17.8 / 14.6, 64 x 128 21.7 / 20.9, 64 x 256 46.6 / 35.6;
+// causal 64 x 64 19.2 / 13.2, 64 x 256 47.1 / 45.7, at worst 64 x 128 23.6 /
+// 25.2; 32 heads of 128 on 8, 64 x 64 34.0 / 22.1, 64 x 128 causal 46.7 / 37.9).
+bool score_wide(int hd, int H, int B, int max_len, int T, int cus) {
+  int64_t blocks = (static_cast<int64_t>(max_len) + 255) / 256 * B;
+  if (max_len > 1024 && static_cast<int64_t>(B) * max_len != T)
+    blocks = std::min<int64_t>(blocks, std::max(B, T / 256 + B / 2));
+  return blocks * H >= static_cast<int64_t>(hd == 64 ? 2 : 1) * cus;
+}
+
 hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
                         int64_t row_stride, const float* lse, int H, int kv_group, int hd, int causal,
                         float scale, int B, int max_len, int T, const int32_t* cu_dev,
@@ -482,16 +502,7 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
     const bf16_t* qp = static_cast<const bf16_t*>(q);
     const bf16_t* kp = static_cast<const bf16_t*>(k);
     const float sl = scale * kLog2e;
-    // the wide kernel from two of its workgroups per CU on (its comment), one
-    // at head dim 128 (4 x 500 causal rows, 32 heads: 32.1 -> 26.0 us), at any
-    // length: short sequences leave some of its waves without keys and are
-    // still faster on it (us with the sum over heads, the other kernel / this
-    // one: 32 heads of 64, no mask, 128 x 20 rows 34.5 / 25.1, 64 x 64 17.8 /
-    // 14.6, 64 x 128 21.7 / 20.9, 64 x 256 46.6 / 35.6; causal 64 x 64 19.2 /
-    // 13.2, 64 x 256 47.1 / 45.7, at worst 64 x 128 23.6 / 25.2; 32 heads of 128
-    // on 8, 64 x 64 34.0 / 22.1, 64 x 128 causal 46.7 / 37.9)
-    const long wide = static_cast<long>((max_len + 255) / 256) * H * B;
-    const bool take = wide >= (hd == 64 ? 2 : 1) * device_cu_count();
+    const bool take = score_wide(hd, H, B, max_len, T, device_cu_count());
     const dim3 grid = place_grid(H, B, max_len, T, causal, take ? 256 : 128);
     auto go = [&](auto kernel, int threads) {
       return launch(K_SCORE, kernel, grid, dim3(threads), 0, s, qp, kp, row_stride, lse, H, kv_group, causal,

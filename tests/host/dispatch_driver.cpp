@@ -146,6 +146,16 @@ void attentions() {
   CHECK_TRUE(attention_wide(128, 1, 1, 513, 0, 256));
 }
 
+// Which score kernel takes a call (256 CUs)
+void scores() {
+  using zsa::score_wide;
+  CHECK_TRUE(score_wide(64, 12, 43, 20, 43 * 20, 256) && !score_wide(64, 12, 42, 20, 42 * 20, 256));
+  CHECK_TRUE(score_wide(128, 32, 4, 500, 4 * 500, 256) && !score_wide(128, 32, 3, 500, 3 * 500, 256));
+  CHECK_TRUE(score_wide(64, 20, 3, 2344, 3 * 2344, 256) && !score_wide(64, 20, 3, 2344, 4681, 256));
+  CHECK_TRUE(score_wide(128, 16, 8, 500, 2450, 256));
+  CHECK_TRUE(score_wide(128, 4, 8, 2553, 8 * 2553, 256) && !score_wide(128, 4, 8, 2553, 12600, 256));
+}
+
 }  // namespace
 
 int main() {
@@ -153,6 +163,7 @@ int main() {
   head_order();
   products();
   attentions();
+  scores();
   printf("ok %d\n", g_checks);
   return 0;
 }
