@@ -856,11 +856,19 @@ hipError_t launch_attention(hipStream_t s, int dtype, const void* q, const void*
   if (B == 0 || max_len == 0) return hipSuccess;
   if (dtype == 1 && (hd == 64 || hd == 128)) {
     const float sl = scale * kLog2e;
+    // Heads of 128 that share no keys: an XCD with 80 pairs or more walks
+    // eight at a time (place_grid). us, all of them / eight, causal, 32 heads:
+    // 80 x 380 rows 327 / 256, 160 x 200 307 / 254, 48 x 512 234 / 198, 20 x 1024
+    // 252 / 220; with fewer pairs the tail of each eight costs more (32 heads
+    // on 8, 8 x 300 23.5 / 28.0; 16 heads, 16 x 257 25.9 / 28.3). Head dim 64, half
+    // the bytes a pair, 32 heads: 48 x 512 112 / 121, 20 x 1024 126 / 131.
+    const int most = hd == 128 && kv_group == 1 ? 8 : 0;
     auto go = [&](auto kernel, int bq, int threads) {
-      return launch(K_ATTENTION, kernel, place_grid(H, B, max_len, T, causal, bq), dim3(threads), 0, s,
+      const PlaceGrid at = place_grid(H, kv_group, B, max_len, T, causal, bq, most);
+      return launch(K_ATTENTION, kernel, at.grid, dim3(threads), 0, s,
                     static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
                     static_cast<const bf16_t*>(v), row_stride, kv_group, causal, sl, cu_dev,
-                    static_cast<bf16_t*>(out), out_stride, lse, T, H, H * B);
+                    static_cast<bf16_t*>(out), out_stride, lse, T, H, at.pairs);
     };
     const bool wide = attention_wide(hd, H, B, max_len, causal, device_cu_count());
     if (hd == 64) {

@@ -817,12 +817,14 @@ hipError_t launch_attention_bwd(hipStream_t s, const void* q, const void* k, con
     auto* vp = static_cast<const bf16_t*>(v);
     auto* op = static_cast<const bf16_t*>(dO);
     auto* lp = reinterpret_cast<const float2*>(LD);
-    const hipError_t e = launch(K_ATTENTION, dkdv, place_grid(Hkv, B, max_len, T, causal, 128), dim3(256), 0, s, qp,
+    // (a key/value head's queries are one workgroup's in dkdv: nothing is shared between its pairs)
+    const PlaceGrid ak = place_grid(Hkv, 1, B, max_len, T, causal, 128), aq = place_grid(H, kv_group, B, max_len, T, causal, 128);
+    const hipError_t e = launch(K_ATTENTION, dkdv, ak.grid, dim3(256), 0, s, qp,
                                 kp, vp, rs, op, ors, lp, T, Hkv, kv_group, causal, scale, sl, cu_dev,
-                                static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), grs, Hkv * B);
+                                static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), grs, ak.pairs);
     if (e != hipSuccess) return e;
-    return launch(K_ATTENTION, dq_kernel, place_grid(H, B, max_len, T, causal, 128), dim3(256), 0, s, qp, kp, vp, rs,
-                  op, ors, lp, T, H, kv_group, causal, scale, sl, cu_dev, static_cast<bf16_t*>(dq), grs, H * B);
+    return launch(K_ATTENTION, dq_kernel, aq.grid, dim3(256), 0, s, qp, kp, vp, rs,
+                  op, ors, lp, T, H, kv_group, causal, scale, sl, cu_dev, static_cast<bf16_t*>(dq), grs, aq.pairs);
   };
   return hd == 64 ? go(attn_bwd_dkdv_kernel<64>, attn_bwd_dq_kernel<64>)
                   : go(attn_bwd_dkdv_kernel<128>, attn_bwd_dq_kernel<128>);

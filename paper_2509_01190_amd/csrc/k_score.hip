@@ -503,10 +503,10 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
     const bf16_t* kp = static_cast<const bf16_t*>(k);
     const float sl = scale * kLog2e;
     const bool take = score_wide(hd, H, B, max_len, T, device_cu_count());
-    const dim3 grid = place_grid(H, B, max_len, T, causal, take ? 256 : 128);
+    const PlaceGrid at = place_grid(H, kv_group, B, max_len, T, causal, take ? 256 : 128);
     auto go = [&](auto kernel, int threads) {
-      return launch(K_SCORE, kernel, grid, dim3(threads), 0, s, qp, kp, row_stride, lse, H, kv_group, causal,
-                    sl, cu_dev, T, partials, H * B);
+      return launch(K_SCORE, kernel, at.grid, dim3(threads), 0, s, qp, kp, row_stride, lse, H, kv_group, causal,
+                    sl, cu_dev, T, partials, at.pairs);
     };
     if (take) return hd == 64 ? go(score_wide_kernel<64, 4>, 256) : go(score_wide_kernel<128, 4>, 256);
     return hd == 64 ? go(score_mfma_kernel<64, 128>, 64 * kScoreWaves)

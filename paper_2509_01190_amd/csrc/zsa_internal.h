@@ -194,7 +194,16 @@ __device__ __forceinline__ float lane_rows_total(const float (&red)[32][33], int
 // sequence is as long and the neighbours' K and V are still in L2, 8 x 2048
 // of 64 267 / 263 / 282, 32 x 512, 12 heads, 36.0 / 35.8 / 37.4. So all of
 // them (the longest blocks first, the shortest at the end) under the mask or
-// with sequences of several lengths, and a sequence's otherwise.
+// with sequences of several lengths, and a sequence's otherwise. A caller may
+// cap the former (`most`) where an XCD has many pairs and each much K and V:
+// walked all at once, a pair's are gone from the caches by its next block.
+// Two kinds of calls keep the query block in the fastest dimension (`pairs`
+// negative): sequences of one block and heads that share nothing, where there
+// is no order to choose and the division below costs 4 % (107 x 37 rows, 20
+// heads of 128, 26.8 / 27.8), and without a mask pairs that do not spread evenly
+// over the XCDs, which dealing by blocks does (scores of 1 x 2049 rows, 12 heads
+// of 64 on 3, 22.3 / 28.9; attention of 5 ragged sequences of up to 1711 rows,
+// 12 heads of 128, 76 / 85).
 struct Place { int b, h, i; };
 // grid (place_grid): x = 8 * chunk (XCD fastest), y = blocks, z = chunks of
 // pairs, or, with all pairs in x, runs of blocks; i counts the blocks from the
@@ -202,6 +211,12 @@ struct Place { int b, h, i; };
 // first (scores: the keys that most queries see)
 __host__ __device__ __forceinline__ bool place_at(dim3 grid, dim3 at_block, int H, int group, int pairs,
                                                   bool first, Place* at) {
+  if (pairs < 0) {
+    at->b = static_cast<int>(at_block.z);
+    at->h = static_cast<int>(at_block.y);
+    at->i = static_cast<int>(first ? at_block.x : grid.x - 1 - at_block.x);
+    return true;
+  }
   const uint32_t chunk = grid.x >> 3;
   const bool whole = 8 * static_cast<uint64_t>(chunk) >= static_cast<uint64_t>(pairs);
   const uint32_t pz = whole ? 0 : at_block.z, iz = whole ? at_block.z : 0;
@@ -220,17 +235,30 @@ __device__ __forceinline__ bool place(int H, int group, int pairs, bool first, P
 
 constexpr uint32_t kGridYZ = 65535;  // HIP's limit on a grid's y and z
 
-inline dim3 place_grid(int H, int B, int max_len, int T, int causal, int block) {
+struct PlaceGrid {
+  dim3 grid;
+  int pairs;  // H * B, or -1: blocks in x, heads in y, sequences in z
+};
+// (most: pairs an XCD walks at a time where it has 80 or more; 0: no cap. Not for short sequences of several lengths,
+// whose missing blocks leave gaps in every chunk: 300 of up to 130 rows, 32 heads of 128, 165 us all at once, 176 in eights)
+inline PlaceGrid place_grid(int H, int group, int B, int max_len, int T, int causal, int block, int most = 0) {
   const int64_t p8 = (static_cast<int64_t>(H) * B + 7) / 8;  // pairs per XCD
   const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
-  int64_t chunk = alike ? std::min<int64_t>(p8, std::max(1, H / 8)) : p8;
+  const int64_t blocks = (static_cast<int64_t>(max_len) + block - 1) / block, spare = 8 * p8 - static_cast<int64_t>(H) * B;
+  if ((blocks == 1 && group == 1) || (!causal && 20 * spare > static_cast<int64_t>(H) * B))
+    if (H <= static_cast<int>(kGridYZ) && B <= static_cast<int>(kGridYZ))
+      return {dim3(static_cast<uint32_t>(blocks), static_cast<uint32_t>(H), static_cast<uint32_t>(B)), -1};
+  // (a sequence's pairs only where they divide evenly: slots left over in the last chunk go out between others, which
+  // an XCD's shader engines take in turn, and one of them gets more of the work: 2 x 2959 rows, 20 heads of 64, one pair
+  // at a time 117 us, two 140)
+  int64_t chunk = alike ? (H % 8 == 0 ? std::min<int64_t>(p8, H / 8) : 1) : p8;
+  if (most > 0 && !alike && p8 >= 80 && (max_len > 256 || static_cast<int64_t>(B) * max_len == T)) chunk = most;
   // the chunks number at most 65535, and at 512 threads a workgroup x stays below 2^32 threads
   chunk = std::min<int64_t>(std::max(chunk, (p8 + kGridYZ - 1) / kGridYZ), (1 << 20) - 1);
-  const int64_t blocks = (static_cast<int64_t>(max_len) + block - 1) / block;
   // sequences of more blocks than y holds (8.4 M rows in 128-row blocks): all pairs in x, the blocks in y and z
   if (blocks > kGridYZ)
-    return dim3(static_cast<uint32_t>(8 * p8), kGridYZ, static_cast<uint32_t>((blocks + kGridYZ - 1) / kGridYZ));
-  return dim3(static_cast<uint32_t>(8 * chunk), static_cast<uint32_t>(blocks), static_cast<uint32_t>((p8 + chunk - 1) / chunk));
+    return {dim3(static_cast<uint32_t>(8 * p8), kGridYZ, static_cast<uint32_t>((blocks + kGridYZ - 1) / kGridYZ)), H * B};
+  return {dim3(static_cast<uint32_t>(8 * chunk), static_cast<uint32_t>(blocks), static_cast<uint32_t>((p8 + chunk - 1) / chunk)), H * B};
 }
 
 // ---------------------------------------------------------------------------

@@ -22,20 +22,21 @@ void check(bool ok, const char* what, int line) {
 #define CHECK_TRUE(cond) check((cond), #cond, __LINE__)
 
 // every (sequence, head, block) has exactly one workgroup of a legal grid
-void check_place(int H, int B, int max_len, int T, int causal, int block) {
+void check_place(int H, int B, int max_len, int T, int causal, int block, int most = 0) {
   fprintf(stderr, "place: %d heads, %d sequences of up to %d rows, %d in all, causal %d, blocks of %d\n", H, B,
           max_len, T, causal, block);
-  const dim3 g = zsa::place_grid(H, B, max_len, T, causal, block);
-  CHECK_TRUE(g.y <= 65535 && g.z <= 65535 && 512ull * g.x <= 0xffffffffull);
   const int blocks = (max_len + block - 1) / block;
   for (int first = 0; first < 2; ++first) {
     const int group = first && H % 2 == 0 ? 2 : 1;
+    const zsa::PlaceGrid pg = zsa::place_grid(H, group, B, max_len, T, causal, block, most);
+    const dim3 g = pg.grid;
+    CHECK_TRUE(g.y <= 65535 && g.z <= 65535 && 512ull * g.x <= 0xffffffffull);
     std::vector<unsigned char> hit(static_cast<size_t>(B) * H * blocks, 0);
     for (uint32_t z = 0; z < g.z; ++z)
       for (uint32_t y = 0; y < g.y; ++y)
         for (uint32_t x = 0; x < g.x; ++x) {
           zsa::Place at;
-          if (!zsa::place_at(g, dim3(x, y, z), H, group, H * B, first != 0, &at)) continue;
+          if (!zsa::place_at(g, dim3(x, y, z), H, group, pg.pairs, first != 0, &at)) continue;
           if (at.i >= blocks) continue;  // past every sequence: the kernels return
           if (at.b < 0 || at.b >= B || at.h < 0 || at.h >= H || at.i < 0) CHECK_TRUE(!"out of range");
           if (hit[(static_cast<size_t>(at.b) * H + at.h) * blocks + at.i]++) CHECK_TRUE(!"reached twice");
@@ -53,12 +54,15 @@ void places() {
       check_place(H, 5, 300, 5 * 300, causal, 128);
       check_place(H, 5, 300, 5 * 300 - 7, causal, 256);
       check_place(H, 33, 1000, 33 * 1000, causal, 128);
+      check_place(H, 33, 1000, 33 * 1000 - 5, causal, 128, 8);
+      check_place(H, 700, 300, 700 * 300 - 5, causal, 128, 8);
     }
     // as many sequences as a grid's z once held, one pair of rows each
     check_place(12, 65535, 2, 2 * 65535, causal, 128);
     check_place(7, 65535, 2, 2 * 65535, causal, 256);
     check_place(2, 65535, 3, 3 * 65535, causal, 256);
     check_place(16, 43700, 1, 43700, causal, 128);
+    check_place(12, 65535, 2, 2 * 65535, causal, 128, 8);
     // one sequence of more blocks than a grid's y holds
     check_place(1, 1, 9000000, 9000000, causal, 128);
     check_place(3, 2, 8388481, 8388482, causal, 128);
@@ -69,14 +73,31 @@ void places() {
 // key/value heads, and every eighth one where they share nothing
 void head_order() {
   const int H = 32, B = 4;
-  const dim3 g = zsa::place_grid(H, B, 128, B * 128, 0, 128);
-  for (int group : {1, 4})
-    for (uint32_t z = 0; z < g.z; ++z)
-      for (uint32_t x = 0; x < g.x; ++x) {
-        zsa::Place at;
-        if (!zsa::place_at(g, dim3(x, 0, z), H, group, H * B, false, &at)) continue;
-        CHECK_TRUE(static_cast<int>(x & 7) == (group == 1 ? at.h % 8 : at.h / (H / 8)));
-      }
+  for (int rows : {128, 300})  // one block: heads that share nothing keep their own order
+    for (int group : {1, 4}) {
+      const zsa::PlaceGrid pg = zsa::place_grid(H, group, B, rows, B * rows, 0, 128);
+      const dim3 g = pg.grid;
+      CHECK_TRUE((pg.pairs < 0) == (rows == 128 && group == 1));
+      for (uint32_t z = 0; z < g.z; ++z)
+        for (uint32_t y = 0; y < g.y; ++y)
+          for (uint32_t x = 0; x < g.x; ++x) {
+            zsa::Place at;
+            if (!zsa::place_at(g, dim3(x, y, z), H, group, pg.pairs, false, &at)) continue;
+            const uint32_t xcd = (x + g.x * (y + g.y * z)) % 8;
+            CHECK_TRUE(static_cast<int>(xcd) == (group == 1 ? at.h % 8 : at.h / (H / 8)));
+          }
+    }
+}
+
+// Equal sequences without a mask: no workgroup without work but for the pairs
+// that fill up the XCDs' last one
+void no_gaps() {
+  for (int H : {1, 3, 8, 12, 16, 20, 24, 32})
+    for (int B : {1, 2, 5, 33}) {
+      const zsa::PlaceGrid g = zsa::place_grid(H, 2, B, 300, B * 300, 0, 128);
+      if (g.pairs < 0) CHECK_TRUE((H * B + 7) / 8 * 8 - H * B > H * B / 20);
+      else CHECK_TRUE(g.grid.x / 8 * g.grid.z == static_cast<uint32_t>((H * B + 7) / 8));
+    }
 }
 
 // Which kernel takes a bf16 product of few output tiles (256 CUs)
@@ -161,6 +182,7 @@ void scores() {
 int main() {
   places();
   head_order();
+  no_gaps();
   products();
   attentions();
   scores();
