@@ -203,7 +203,15 @@ __device__ __forceinline__ float lane_rows_total(const float (&red)[32][33], int
 // heads of 128, 26.8 / 27.8), and without a mask pairs that do not spread evenly
 // over the XCDs, which dealing by blocks does (scores of 1 x 2049 rows, 12 heads
 // of 64 on 3, 22.3 / 28.9; attention of 5 ragged sequences of up to 1711 rows,
-// 12 heads of 128, 76 / 85).
+// 12 heads of 128, 76 / 85). So do long sequences of several lengths whose heads
+// do not divide by eight: an XCD then meets some of the sequences more often
+// than others (with 4 heads every second one), and the call ends with the one
+// that has the longest. By blocks / by pairs: 16 ragged sequences of up to 2494
+// rows, 12 heads of 64, 154 / 205 and their scores 111 / 155; 8 of up to 3114,
+// 4 heads of 128, 101 / 138 and 68 / 117. From 24 heads on the difference is
+// under a fourth and the keys that stay in an XCD's L2 count for more (20 of up
+// to 1962, 36 heads of 64, 449 / 352), as they do in shorter sequences (scores
+// of 48 of up to 600, 4 heads of 64, 24.6 / 20.7).
 struct Place { int b, h, i; };
 // grid (place_grid): x = 8 * chunk (XCD fastest), y = blocks, z = chunks of
 // pairs, or, with all pairs in x, runs of blocks; i counts the blocks from the
@@ -245,7 +253,8 @@ inline PlaceGrid place_grid(int H, int group, int B, int max_len, int T, int cau
   const int64_t p8 = (static_cast<int64_t>(H) * B + 7) / 8;  // pairs per XCD
   const bool alike = !causal && static_cast<int64_t>(B) * max_len == T;
   const int64_t blocks = (static_cast<int64_t>(max_len) + block - 1) / block, spare = 8 * p8 - static_cast<int64_t>(H) * B;
-  if ((blocks == 1 && group == 1) || (!causal && 20 * spare > static_cast<int64_t>(H) * B))
+  const bool uneven = 20 * spare > static_cast<int64_t>(H) * B || (!alike && max_len > 1024 && H % 8 != 0 && H < 24);
+  if ((blocks == 1 && group == 1) || (!causal && uneven))
     if (H <= static_cast<int>(kGridYZ) && B <= static_cast<int>(kGridYZ))
       return {dim3(static_cast<uint32_t>(blocks), static_cast<uint32_t>(H), static_cast<uint32_t>(B)), -1};
   // (a sequence's pairs only where they divide evenly: slots left over in the last chunk go out between others, which

@@ -89,6 +89,31 @@ void head_order() {
     }
 }
 
+// Long sequences of several lengths without a mask: no XCD gets more than 1.2
+// times its share of the blocks that have rows, however the lengths alternate
+void long_ragged() {
+  const int longest = 2494, B = 16, block = 128;
+  for (int H : {4, 6, 8, 12, 20})
+    for (int period : {2, 4}) {
+      auto len = [&](int b) { return b % period == 0 ? longest : 300; };
+      int T = 0;
+      for (int b = 0; b < B; ++b) T += len(b);
+      const zsa::PlaceGrid pg = zsa::place_grid(H, 1, B, longest, T, 0, block);
+      const dim3 g = pg.grid;
+      int per_xcd[8] = {}, all = 0;
+      for (uint32_t z = 0; z < g.z; ++z)
+        for (uint32_t y = 0; y < g.y; ++y)
+          for (uint32_t x = 0; x < g.x; ++x) {
+            zsa::Place at;
+            if (!zsa::place_at(g, dim3(x, y, z), H, 1, pg.pairs, false, &at) || at.i * block >= len(at.b)) continue;
+            ++per_xcd[(x + g.x * (y + g.y * z)) % 8];
+            ++all;
+          }
+      fprintf(stderr, "long ragged: %d heads, every %dth sequence long\n", H, period);
+      for (int n : per_xcd) CHECK_TRUE(8 * n <= 1.2 * all);
+    }
+}
+
 // Equal sequences without a mask: no workgroup without work but for the pairs
 // that fill up the XCDs' last one
 void no_gaps() {
@@ -181,6 +206,7 @@ void scores() {
 
 int main() {
   places();
+  long_ragged();
   head_order();
   no_gaps();
   products();
