@@ -479,17 +479,24 @@ int score_groups(int dtype, int H, int hd, int T) {
 // fill (3 sequences of up to 2344 causal rows, 20 heads of 64, 600
 // workgroups in the grid, about 380 live: the other kernel 44.3, this one 48.7
 // us; 8 of up to 2553, 4 heads of 128, 320 and 212: 42.7 and 58.0; but 8 of up to
-// 500, 16 heads of 128, 256 and 208: 17.6 and 15.7). At any length: short sequences leave some of
+// 500, 16 heads of 128, 256 and 208: 17.6 and 15.7). Long sequences under the
+// mask need 1.6 per CU at head dim 128: the first keys' workgroups see every
+// query and run about twice the mean, and below that the call waits for them
+// alone (162 calls of 1100..4096 rows with one to two live per CU, 1.05 of the
+// faster kernel's time with the line at 1.2, 1.01 at 1.6, 1.02 at 2; 2 of 4096, 12
+// heads, ragged, 67.1 / 88.8; 6 of up to 3300, 6 heads, 52.8 / 74.7; above
+// it 7 of up to 4096, 6 heads, 108 / 91). At any length: short sequences leave some of
 // its waves without keys and are still faster on it (us with the sum over
 // heads, the other kernel / this one: 32 heads of 64, no mask, 128 x 20 rows
 // 34.5 / 25.1, 64 x 64 17.8 / 14.6, 64 x 128 21.7 / 20.9, 64 x 256 46.6 / 35.6;
 // causal 64 x 64 19.2 / 13.2, 64 x 256 47.1 / 45.7, at worst 64 x 128 23.6 /
 // 25.2; 32 heads of 128 on 8, 64 x 64 34.0 / 22.1, 64 x 128 causal 46.7 / 37.9).
-bool score_wide(int hd, int H, int B, int max_len, int T, int cus) {
+bool score_wide(int hd, int H, int B, int max_len, int T, int causal, int cus) {
   int64_t blocks = (static_cast<int64_t>(max_len) + 255) / 256 * B;
   if (max_len > 1024 && static_cast<int64_t>(B) * max_len != T)
     blocks = std::min<int64_t>(blocks, std::max(B, T / 256 + B / 2));
-  return blocks * H >= static_cast<int64_t>(hd == 64 ? 2 : 1) * cus;
+  const int64_t five = hd == 64 ? 10 : causal && max_len > 1024 ? 8 : 5;  // fifths of a workgroup per CU
+  return 5 * blocks * H >= five * cus;
 }
 
 hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
@@ -502,7 +509,7 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
     const bf16_t* qp = static_cast<const bf16_t*>(q);
     const bf16_t* kp = static_cast<const bf16_t*>(k);
     const float sl = scale * kLog2e;
-    const bool take = score_wide(hd, H, B, max_len, T, device_cu_count());
+    const bool take = score_wide(hd, H, B, max_len, T, causal, device_cu_count());
     const PlaceGrid at = place_grid(H, kv_group, B, max_len, T, causal, take ? 256 : 128);
     auto go = [&](auto kernel, int threads) {
       return launch(K_SCORE, kernel, at.grid, dim3(threads), 0, s, qp, kp, row_stride, lse, H, kv_group, causal,

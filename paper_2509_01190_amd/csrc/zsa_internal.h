@@ -397,7 +397,7 @@ hipError_t launch_score(hipStream_t s, int dtype, const void* q, const void* k,
                         const int32_t* cu_dev, float* partials, int groups);
 int score_groups(int dtype, int H, int hd, int T);
 // the kernel of 256-key workgroups takes this bf16 call (head_dim 64 or 128)
-bool score_wide(int hd, int H, int B, int max_len, int T, int cus);
+bool score_wide(int hd, int H, int B, int max_len, int T, int causal, int cus);
 
 hipError_t launch_score_finalize(hipStream_t s, const float* partials, int groups, int T,
                                  float* scores);

@@ -195,11 +195,15 @@ void attentions() {
 // Which score kernel takes a call (256 CUs)
 void scores() {
   using zsa::score_wide;
-  CHECK_TRUE(score_wide(64, 12, 43, 20, 43 * 20, 256) && !score_wide(64, 12, 42, 20, 42 * 20, 256));
-  CHECK_TRUE(score_wide(128, 32, 4, 500, 4 * 500, 256) && !score_wide(128, 32, 3, 500, 3 * 500, 256));
-  CHECK_TRUE(score_wide(64, 20, 3, 2344, 3 * 2344, 256) && !score_wide(64, 20, 3, 2344, 4681, 256));
-  CHECK_TRUE(score_wide(128, 16, 8, 500, 2450, 256));
-  CHECK_TRUE(score_wide(128, 4, 8, 2553, 8 * 2553, 256) && !score_wide(128, 4, 8, 2553, 12600, 256));
+  CHECK_TRUE(score_wide(64, 12, 43, 20, 43 * 20, 0, 256) && !score_wide(64, 12, 42, 20, 42 * 20, 0, 256));
+  CHECK_TRUE(score_wide(128, 32, 4, 500, 4 * 500, 0, 256) && !score_wide(128, 32, 3, 500, 3 * 500, 0, 256));
+  CHECK_TRUE(score_wide(64, 20, 3, 2344, 3 * 2344, 0, 256) && !score_wide(64, 20, 3, 2344, 4681, 0, 256));
+  CHECK_TRUE(score_wide(128, 16, 8, 500, 2450, 0, 256));
+  CHECK_TRUE(score_wide(128, 4, 8, 2553, 8 * 2553, 0, 256) && !score_wide(128, 4, 8, 2553, 12600, 0, 256));
+  // long sequences under the mask, heads of 128: from 1.6 workgroups with keys per CU on
+  CHECK_TRUE(score_wide(128, 12, 3, 3300, 3 * 3300, 1, 256) && !score_wide(128, 12, 2, 3300, 2 * 3300, 1, 256));
+  CHECK_TRUE(score_wide(128, 12, 2, 3300, 2 * 3300, 0, 256) && !score_wide(128, 6, 6, 3300, 12000, 1, 256));
+  CHECK_TRUE(score_wide(128, 32, 4, 1000, 4 * 1000, 1, 256) && score_wide(64, 12, 4, 3300, 4 * 3300, 1, 256));
 }
 
 }  // namespace
